@@ -266,7 +266,8 @@ zr_status zr_thiele_slices(uint64_t p, uint32_t T, uint32_t nk, const uint64_t* 
 
 /* One transposed Vandermonde system (§1, §2.2) through the one-system solve
  * of the plain reconstruction: master polynomial, synthetic-division dot
- * products (the pass chosen by zr_solve_variant), Horner and scaling.  Solves
+ * products (the pass chosen by zr_solve_variant; large systems are first split
+ * into blocks of rows by a subproduct tree), denominators and scaling.  Solves
  *      sum_l a_l * m_l^i = v_i,   i = 1..t
  * for each of R right-hand sides.
  *   d_mono   device [t], distinct nonzero values < p
@@ -280,8 +281,8 @@ zr_status zr_vandermonde_solve(uint64_t p, uint32_t t, uint32_t R, const uint64_
 
 /* zr_vandermonde_solve for callers that cannot allocate device memory (code
  * under stream capture, serving loops that forbid hipMalloc): same arguments,
- * same results, same kernels, but the master polynomial and the solve's
- * workspace live in one fixed 64 MiB device array inside the library (one per
+ * same results, the quadratic pass at every size, but the master polynomial and
+ * the solve's workspace live in one fixed 64 MiB device array inside the library (one per
  * GPU, held until the process ends) instead of memory from the allocator.  The
  * call allocates nothing and launches no memset: its status word is cleared by
  * a kernel, and every workspace word is written before it is read, so nothing
@@ -336,7 +337,10 @@ zr_status zippel_reconstruct_batch(uint32_t n, const zr_params* params, zr_black
  * running the synthetic division chain with carry-free 64-bit
  * multiply-accumulates; 1 (default) a producer wave runs the chain once per
  * row block and publishes it through LDS to one consumer wave per tile
- * (systems with at most 10 right-hand sides run as 0).  Same results for
+ * (systems with at most 10 right-hand sides run as 0), and large systems (from
+ * about 10^4 unknowns, up to 2^21) are first cut into independent blocks of rows by
+ * a subproduct tree with exact number-theoretic transforms, so that the
+ * quadratic pass covers only the blocks.  Same results for
  * both.  Any other value returns ZR_EINVAL and leaves the choice unchanged. */
 zr_status zr_solve_variant(int variant);
 
@@ -447,7 +451,8 @@ void zr_timing_reset(void);
 /* Returns the number of timed launches of `kernel` and their total in ms. */
 uint64_t zr_timing_get(const char* kernel, double* total_ms);
 
-/* Algorithmic work counters of the last zippel_* call on this thread. */
+/* Algorithmic work counters of the last zippel_* call on this thread: the work of the
+ * method as the paper states it (O(t^2) per system), whichever pass ran. */
 typedef struct {
   uint64_t mulmods;       /* algorithmic modular products (each multiply-accumulate counts 1) */
   uint64_t solve_mulmods; /* of which in the Vandermonde solves: R t^2 + 2 t(t-1) per system */

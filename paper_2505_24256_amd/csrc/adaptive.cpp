@@ -22,6 +22,7 @@
 #include "driver.hpp"
 #include "field.hpp"
 #include "kernels.hpp"
+#include "tree.hpp"
 #include "kernels_dev.hpp"
 
 namespace zr {
@@ -144,14 +145,9 @@ void reconstruct_adaptive(const zr_params* params, uint32_t confirm, zr_blackbox
       check(fill_i32((int32_t*)d_nz, 0, maxm + 1, s));
       if (k == 1) call_bb(bb, ctx, P, 1, 1, P.y.data(), X.data(), 1, vals, s);
       else check(copy_u64(vals, cur.coef, t, s));
-      // one master polynomial for all of the stage's solves
+      // one master polynomial for all of the stage's quadratic solves
       uint64_t* Mc = nullptr;
-      if (k >= 2 && t) {
-        Mc = A.alloc<uint64_t>(t);
-        uint64_t* tmp = A.alloc<uint64_t>(master_tmp_words(t));
-        check(master_poly(P.M, t, cur.mono, Mc, tmp, s));
-        C.mulmods += (uint64_t)t * (t - 1) / 2;
-      }
+      if (k >= 2 && t) C.mulmods += (uint64_t)t * (t - 1) / 2;
       uint32_t m = 0, run = 0, stop = 0;
       uint32_t batch = k >= 2 ? std::min(std::max(kBatchFirst, prevD + confirm), kBatchGuess) : kBatchFirst;
       std::vector<uint32_t> nz(maxm + 1);
@@ -167,9 +163,18 @@ void reconstruct_adaptive(const zr_params* params, uint32_t confirm, zr_blackbox
         if (k >= 2 && t) {
           // rows m+1..m+B in place
           DevArena W(s);
-          const VsolvePlan plan = vsolve_plan(t, B, device_cus());
-          uint64_t* work = W.alloc<uint64_t>(vsolve_workspace_words(plan));
-          check(vsolve(P.M, plan, cur.mono, Mc, rows, t, rows, t, work, d_status, s));
+          if (tree_applies(t, B)) {
+            tree_solve(P.M, t, B, cur.mono, rows, t, rows, t, d_status, W, s);
+          } else {
+            if (!Mc) {
+              Mc = A.alloc<uint64_t>(t);
+              uint64_t* tmp = A.alloc<uint64_t>(master_tmp_words(t));
+              check(master_poly(P.M, t, cur.mono, Mc, tmp, s));
+            }
+            const VsolvePlan plan = vsolve_plan(t, B, device_cus());
+            uint64_t* work = W.alloc<uint64_t>(vsolve_workspace_words(plan));
+            check(vsolve(P.M, plan, cur.mono, Mc, rows, t, rows, t, work, d_status, s));
+          }
           count_solve(t, B);
           C.mulmods -= (uint64_t)t * (t - 1) / 2;  // the master polynomial is counted once per stage
         }

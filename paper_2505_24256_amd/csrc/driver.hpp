@@ -98,6 +98,10 @@ uint32_t lift_stage(const Params& P, uint32_t kvar, const Skeleton& S, const uin
                     int32_t* d_status);
 void check_probes(const Params& P, zr_blackbox_fn bb, void* ctx, const Skeleton& N, const Skeleton* D,
                   hipStream_t s);
+// One transposed Vandermonde system: mono [t], rhs and out [R][t] (may be equal),
+// by the subproduct tree or the quadratic pass, whichever is faster at its size.
+void solve_system(const zr_mod& M, uint32_t t, uint32_t R, const uint64_t* mono, const uint64_t* rhs, uint64_t* out,
+                  int32_t* d_status, hipStream_t s);
 void solve_stage(const Params& P, const Skeleton& S, uint64_t* vals, uint32_t R, hipStream_t s, int32_t* d_status);
 void download(const Skeleton& S, hipStream_t s, zr_poly* out);
 // Upload the caller's stage-(P.first - 1) skeleton (P.start) and compute its

@@ -482,6 +482,143 @@ hipError_t vsolve(const zr_mod& M, const VsolvePlan& P, const uint64_t* mono, co
 }
 
 // ============================================================================
+// Leaf blocks of the subproduct tree: every block of `block` rows is a system
+// of its own, whose samples and master polynomial stand at the block's indices
+// of F and leafM, so the producer/consumer pass runs over them as it runs over
+// one system, each workgroup over the steps of its own block.
+// ============================================================================
+
+// D_c of m M'(m) for every chunk
+__global__ void __launch_bounds__(256) k_vs_chain_d(VsArgs a) {
+  const uint32_t l = blockIdx.x * blockDim.x + threadIdx.x;
+  if (l < a.t) vs_chain_cl<false, true>(a, l, blockIdx.y);
+}
+
+namespace {
+struct LeafPlan {
+  VsolvePlan P;     // right-hand-side groups and tiles
+  uint32_t L, S;    // chunks of the denominators
+  uint32_t words;   // packed words per step
+};
+LeafPlan leaf_plan(uint32_t t, uint32_t R, bool sums) {
+  LeafPlan q{};
+  VsolvePlan& P = q.P;
+  P.t = t;
+  P.R = R;
+  P.ng = cdiv(R, kPcMaxR);
+  P.Rg = cdiv(R, P.ng);
+  P.pc = 1;
+  P.ntile = pc_tiles_for(P.Rg);
+  P.RT = cdiv(P.Rg, P.ntile);
+  P.dchain = 1;
+  P.S = P.Sd = 1;
+  P.L = t;
+  pc_widths(P.Rg, P.ntile, P.RT, true, P.tw);
+  if (plan_uneven(P) && dots_pc_blocks_per_cu(P.RT, P.ntile, true) < dots_pc_blocks_per_cu(P.RT, P.ntile, false))
+    for (uint32_t k = 0; k < P.ntile; ++k) P.tw[k] = P.RT;
+  for (uint32_t k = 0; k < P.ntile; ++k) q.words += pc_ldv(P.tw[k]);
+  P.vt32 = (size_t)q.words * t;
+  // chunks of the denominators' sums: about 1024 workgroups, at least 128 steps each
+  q.S = std::max<uint32_t>(1, std::min<uint32_t>(t / 128, cdiv(1024, cdiv(t, 256))));
+  q.L = cdiv(t, q.S);
+  q.S = sums ? 0 : cdiv(t, q.L);
+  return q;
+}
+}  // namespace
+
+// denominators and their inverses from the values of the power sums' series
+__global__ void __launch_bounds__(kDeltaBlock) k_leaf_delta(VsArgs a, uint64_t* __restrict__ winv,
+                                                             int32_t* __restrict__ status) {
+  __shared__ uint64_t sh[kDeltaBlock / 64 + 1];
+  const uint32_t l = blockIdx.x * kDeltaBlock + threadIdx.x;
+  const bool live = l < a.t;
+  const uint64_t w = live ? a.spart[l] : 0;
+  if (live && w == 0) atomicCAS(status, 0, -3);  // ZR_ESINGULAR
+  const uint64_t wi = block_inverse(a.M, w, live, sh);
+  if (live) {
+    winv[l] = wi;
+    winv[a.t + l] = wi ? zr_shoup_pre(a.M, wi) : 0;
+  }
+}
+
+size_t vsolve_leaf_words(uint32_t t, uint32_t R1, bool sums) {
+  const LeafPlan q = leaf_plan(t, R1, sums);
+  // VT | mono_p | spart [Rg][t] | D_c [S][t] | winv [2t] | CL [t][6] (32-bit)
+  return vsolve_rhs_words(q.P) + (size_t)t * (1 + q.P.Rg + q.S + 2 + 3) + 64;
+}
+
+hipError_t vsolve_leaf(const zr_mod& M, uint32_t t, uint32_t R1, bool sums, uint32_t block, const uint64_t* mono,
+                       const uint64_t* leafM, const uint64_t* rootM, const uint64_t* F, uint64_t* out, size_t ld_out,
+                       uint64_t* work, int32_t* status, hipStream_t s) {
+  const LeafPlan q = leaf_plan(t, R1, sums);
+  const VsolvePlan& P = q.P;
+  uint64_t* VT = work;
+  uint64_t* mono_p = VT + vsolve_rhs_words(P);
+  uint64_t* spart = mono_p + t;
+  uint64_t* dpart = spart + (size_t)P.Rg * t;
+  uint64_t* winv = dpart + (size_t)q.S * t;
+  uint32_t* CL = (uint32_t*)(winv + 2 * (size_t)t);
+  VsArgs a;
+  a.M = M;
+  a.t = t;
+  a.L = q.L;
+  a.S = q.S;
+  a.Sd = 1;
+  a.R = R1;
+  a.ldv = 0;
+  for (uint32_t k = 0; k < 8; ++k) a.tw[k] = (uint8_t)P.tw[k];
+  a.mono = mono;
+  a.mono_p = mono_p;
+  a.Mc = leafM;
+  a.VT = VT;
+  a.qstart = nullptr;
+  a.Bc = nullptr;
+  a.spart = spart;
+  a.hpart = nullptr;
+  a.CL = CL;
+  a.dpart = dpart;
+  {
+    TimedLaunch tl("vs_chain", s);
+    hipLaunchKernelGGL(k_pack, dim3(cdiv(t, 256)), dim3(256), 0, s, t, R1, 1u, 0u, 2u, F, (size_t)t, rootM, (uint32_t*)VT,
+                       mono, mono_p, CL, M);
+    if (!sums) {
+      hipLaunchKernelGGL(k_vs_chain_d, dim3(cdiv(t, 256), q.S), dim3(256), 0, s, a);
+      hipLaunchKernelGGL(k_vs_delta, dim3(cdiv(t, kDeltaBlock)), dim3(kDeltaBlock), 0, s, a, (const uint64_t*)nullptr,
+                         winv, status);
+    }
+  }
+  a.blk = block;
+  uint32_t wmax = 0;
+  for (uint32_t k = 0; k < P.ntile; ++k) wmax = std::max(wmax, P.tw[k]);
+  DotsPcKernel kp = dots_pc_kernel(P.RT, false, plan_uneven(P));
+  if (!kp) return hipErrorInvalidValue;
+  for (uint32_t g = 0, r0 = 0; g < P.ng; ++g) {
+    const uint32_t Rg = R1 / P.ng + (g < R1 % P.ng ? 1 : 0);
+    a.R = Rg;
+    {
+      TimedLaunch tl("vs_pack", s);
+      hipLaunchKernelGGL(k_pack_pc, dim3(cdiv((size_t)t * pc_ldv(wmax), 256), P.ntile), dim3(256), 0, s, a,
+                         F + (size_t)r0 * t, (size_t)t, (uint32_t*)VT);
+    }
+    {
+      TimedLaunch tl("vs_dots", s);
+      hipLaunchKernelGGL(kp, dim3(cdiv(t, 64), 1), dim3(64 * (1 + P.ntile)), 0, s, a, P.ntile, 0u);
+    }
+    {
+      TimedLaunch tl("vs_finish", s);
+      const bool first = sums && g == 0;  // series 0 holds the denominators
+      if (first) hipLaunchKernelGGL(k_leaf_delta, dim3(cdiv(t, kDeltaBlock)), dim3(kDeltaBlock), 0, s, a, winv, status);
+      VsArgs b = a;
+      b.spart = spart + (first ? t : 0);
+      const uint32_t n = Rg - (first ? 1 : 0), o = r0 - (sums && !first ? 1 : 0);
+      if (n) hipLaunchKernelGGL(k_vs_scale, dim3(cdiv(t, 256), n), dim3(256), 0, s, b, winv, out + (size_t)o * ld_out, ld_out);
+    }
+    r0 += Rg;
+  }
+  return hipGetLastError();
+}
+
+// ============================================================================
 // Master polynomial by a product tree.  Level s multiplies pairs of monic
 // factors of degree <= 2^s; every level stores the non-leading coefficients
 // of all its factors in one array of length t (factor [a, b) at [a, b)).
@@ -508,12 +645,15 @@ size_t master_tmp_words(uint32_t t) {
   return (size_t)t + 1 + 4 * ((size_t)t + 16) + (nic_max > 1 ? (size_t)nic_max * t : 0) + 64;
 }
 
-hipError_t master_poly(const zr_mod& M, uint32_t t, const uint64_t* mono, uint64_t* Mc, uint64_t* tmp,
-                       hipStream_t s) {
+// Levels of the product tree up to factors of degree `block` (t for all of
+// it): the blocks' non-leading coefficients into Mc.
+hipError_t master_levels(const zr_mod& M, uint32_t t, uint32_t block, const uint64_t* mono, uint64_t* Mc, uint64_t* tmp,
+                         hipStream_t s) {
   if (t == 0) return hipSuccess;
   TimedLaunch tl("master", s);
+  const uint32_t top = std::min(t, block);
   uint32_t big = 0;  // levels with half >= 64
-  for (uint32_t half = 64; half < t; half *= 2) ++big;
+  for (uint32_t half = 64; half < top; half *= 2) ++big;
   const size_t t2 = ((size_t)t + 1) & ~(size_t)1;  // keep the limb arrays 16-byte aligned
   uint4* limbs[2] = {(uint4*)(tmp + t2), (uint4*)(tmp + t2 + 2 * ((size_t)t + 16))};
   uint64_t* part = tmp + t2 + 4 * ((size_t)t + 16);
@@ -521,7 +661,7 @@ hipError_t master_poly(const zr_mod& M, uint32_t t, const uint64_t* mono, uint64
   // the level written last must be Mc: the small kernel writes bufs[big % 2]
   uint32_t w = big % 2;
   hipLaunchKernelGGL(k_master_small, dim3(cdiv(t, 64)), dim3(64), 0, s, M, t, mono, bufs[w], limbs[w]);
-  for (uint32_t half = 64; half < t; half *= 2) {
+  for (uint32_t half = 64; half < top; half *= 2) {
     const uint32_t r = w;
     w ^= 1;
     const uint32_t IC = conv_ic(half, cdiv(t, 64));
@@ -532,6 +672,11 @@ hipError_t master_poly(const zr_mod& M, uint32_t t, const uint64_t* mono, uint64
                          limbs[w]);
   }
   return hipGetLastError();
+}
+
+hipError_t master_poly(const zr_mod& M, uint32_t t, const uint64_t* mono, uint64_t* Mc, uint64_t* tmp,
+                       hipStream_t s) {
+  return master_levels(M, t, t, mono, Mc, tmp, s);
 }
 
 // ============================================================================

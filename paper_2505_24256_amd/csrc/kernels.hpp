@@ -47,6 +47,21 @@ size_t master_tmp_words(uint32_t t);
 hipError_t master_poly(const zr_mod& M, uint32_t t, const uint64_t* mono, uint64_t* Mc, uint64_t* tmp,
                        hipStream_t s);
 
+// The tree's levels up to factors of degree `block` only (blocks of that many rows).
+hipError_t master_levels(const zr_mod& M, uint32_t t, uint32_t block, const uint64_t* mono, uint64_t* Mc, uint64_t* tmp,
+                         hipStream_t s);
+
+// Leaf step of the tree solve: block u of `block` rows (a multiple of 64) is a
+// system with samples F[j][block u ..] (R1 series of t words) and master
+// polynomial leafM[block u ..].  Dot products per block, the denominators m M'(m)
+// of the whole system (rootM its polynomial), and the scaling into out.  sums:
+// series 0 holds the power sums, so its values are the denominators and the
+// right-hand sides are series 1..R1-1; else the chain pass makes them.
+size_t vsolve_leaf_words(uint32_t t, uint32_t R1, bool sums);
+hipError_t vsolve_leaf(const zr_mod& M, uint32_t t, uint32_t R1, bool sums, uint32_t block, const uint64_t* mono,
+                       const uint64_t* leafM, const uint64_t* rootM, const uint64_t* F, uint64_t* out, size_t ld_out,
+                       uint64_t* work, int32_t* status, hipStream_t s);
+
 // ---- Newton lift (eq. 1) and skeleton expansion ------------------------------
 // g[d][l] = sum_i W[d][i] vals[i][l] with W the inverse Vandermonde matrix of
 // the stage's nodes; Wl holds W as 22-bit limbs laid out [i][d][3].  cnt[l]

@@ -38,6 +38,9 @@ struct VsArgs {
   // producer/consumer pass: right-hand sides of consumer k's tile; tile k's
   // rows (pc_ldv(tw[k]) words each) follow those of the tiles before it
   uint8_t tw[8] = {};
+  // leaf blocks of the subproduct tree (0: one system): rows [B u, B (u+1)) are
+  // a system of their own, with master polynomial and samples at those indices
+  uint32_t blk = 0;
 };
 
 __device__ __forceinline__ void chunk_range(uint32_t t, uint32_t L, uint32_t c, uint32_t& lo, uint32_t& hi) {
@@ -594,7 +597,12 @@ __device__ __forceinline__ void vs_dots_pc_body(const VsArgs& a, uint32_t rb, ui
   const bool live = l0 < a.t;
   const uint32_t l = live ? l0 : a.t - 1;
   uint32_t lo, hi;
-  chunk_range(a.t, a.L, c, lo, hi);
+  if (a.blk) {
+    lo = rb * 64 / a.blk * a.blk;  // the block of the workgroup's rows
+    hi = min(a.t, lo + a.blk);
+  } else {
+    chunk_range(a.t, a.L, c, lo, hi);
+  }
   const uint32_t nb = (hi - lo + kQB - 1) / kQB;
   const zr_mod M = a.M;
   if (wave == 0) {
@@ -735,7 +743,7 @@ __device__ __forceinline__ void vs_delta_block(const VsArgs& a, uint32_t l, cons
     uint64_t acc = part[l];
     uint64_t mL = 0, mLp = 0;
     if (a.S > 1) {
-      mL = mLv[l];
+      mL = mLv ? mLv[l] : zr_pow(M, m, a.L);
       mLp = zr_shoup_pre(M, mL);
       const uint32_t len_last = a.t - (a.S - 1) * a.L;
       const uint64_t mlast = zr_pow(M, m, len_last);

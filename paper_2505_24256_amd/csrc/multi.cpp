@@ -84,18 +84,11 @@ struct Union {
 };
 
 // All expressions' right-hand sides in one solve over the union skeleton: one
-// master polynomial, and one chain pass and inversion for all (vsolve takes
-// more than kPcMaxR right-hand sides in groups).
+// master polynomial, and one set of denominators for all.
 void solve_groups(const Params& P, const Union& U, uint64_t* rhs, uint32_t R, hipStream_t s, int32_t* d_status) {
   const uint32_t t = U.t;
   if (t == 0 || R == 0) return;
-  DevArena A(s);
-  uint64_t* Mc = A.alloc<uint64_t>(t);
-  uint64_t* tmp = A.alloc<uint64_t>(master_tmp_words(t));
-  check(master_poly(P.M, t, U.mono, Mc, tmp, s));
-  const VsolvePlan plan = vsolve_plan(t, R, device_cus());
-  uint64_t* work = A.alloc<uint64_t>(vsolve_workspace_words(plan));
-  check(vsolve(P.M, plan, U.mono, Mc, rhs, t, rhs, t, work, d_status, s));
+  solve_system(P.M, t, R, U.mono, rhs, rhs, d_status, s);
   count_solve(t, R);
 }
 

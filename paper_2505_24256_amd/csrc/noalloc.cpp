@@ -2,8 +2,9 @@
 // polynomial's levels and the solve's workspace live in one fixed device array
 // of this file, sized at build time, instead of in memory taken from the
 // allocator.  For callers that cannot allocate device memory (code under
-// stream capture, tight serving loops).  The kernels and their arguments are
-// those of zr_vandermonde_solve; only where the workspace comes from differs.
+// stream capture, tight serving loops).  The kernels are
+// those of zr_vandermonde_solve's quadratic pass; only where the workspace comes
+// from differs.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

@@ -20,6 +20,7 @@
 #include "driver.hpp"
 #include "field.hpp"
 #include "kernels.hpp"
+#include "tree.hpp"
 
 namespace zr {
 
@@ -483,14 +484,23 @@ int32_t* host_scratch() {
 void solve_stage(const Params& P, const Skeleton& S, uint64_t* vals, uint32_t R, hipStream_t s, int32_t* d_status) {
   const uint32_t t = S.t;
   if (t == 0 || R == 0) return;
+  solve_system(P.M, t, R, S.mono, vals + t, vals + t, d_status, s);
+  count_solve(t, R);
+}
+
+void solve_system(const zr_mod& M, uint32_t t, uint32_t R, const uint64_t* mono, const uint64_t* rhs, uint64_t* out,
+                  int32_t* d_status, hipStream_t s) {
   DevArena A(s);
+  if (tree_applies(t, R)) {
+    tree_solve(M, t, R, mono, rhs, t, out, t, d_status, A, s);
+    return;
+  }
   uint64_t* Mc = A.alloc<uint64_t>(t);
   uint64_t* tmp = A.alloc<uint64_t>(master_tmp_words(t));
-  check(master_poly(P.M, t, S.mono, Mc, tmp, s));
+  check(master_poly(M, t, mono, Mc, tmp, s));
   VsolvePlan plan = vsolve_plan(t, R, device_cus());
   uint64_t* work = A.alloc<uint64_t>(vsolve_workspace_words(plan));
-  check(vsolve(P.M, plan, S.mono, Mc, vals + t, t, vals + t, t, work, d_status, s));
-  count_solve(t, R);
+  check(vsolve(M, plan, mono, Mc, rhs, t, out, t, work, d_status, s));
 }
 
 uint32_t device_cus() {
@@ -709,14 +719,7 @@ zr_status zr_vandermonde_solve(uint64_t p, uint32_t t, uint32_t R, const uint64_
   try {
     check(fill_i32(d_status, 0, 1, stream));
     if (t == 0 || R == 0) return ZR_OK;
-    const zr_mod M = zr_mod_make(p);
-    DevArena A(stream);
-    uint64_t* Mc = A.alloc<uint64_t>(t);
-    uint64_t* tmp = A.alloc<uint64_t>(master_tmp_words(t));
-    check(master_poly(M, t, d_mono, Mc, tmp, stream));
-    VsolvePlan plan = vsolve_plan(t, R, device_cus());
-    uint64_t* work = A.alloc<uint64_t>(vsolve_workspace_words(plan));
-    check(vsolve(M, plan, d_mono, Mc, d_rhs, t, d_out, t, work, d_status, stream));
+    solve_system(zr_mod_make(p), t, R, d_mono, d_rhs, d_out, d_status, stream);
     return ZR_OK;
   } catch (const Error& e) {
     return (zr_status)e.code;
