@@ -112,8 +112,46 @@ ZR_HD uint64_t zr_pow(const zr_mod& M, uint64_t a, uint64_t e) {
   return r;
 }
 
-// Inverse by Fermat's little theorem (p prime); 0 maps to 0.
-ZR_HD uint64_t zr_inv(const zr_mod& M, uint64_t a) { return zr_pow(M, a, M.p - 2); }
+// Inverse modulo the odd prime p of a < p; 0 maps to 0.  Binary Euclid on (u, v)
+// = (a, p), both odd after each shift, with cofactors that only grow (B. Kaliski,
+// "The Montgomery inverse and its applications", IEEE Trans. Computers 44(8),
+// 1995): throughout u 2^K = x a and v 2^K = -y a modulo p, and u y + v x = p, so
+// x and y stay below p.  At u = v = 1 the inverse is x 2^-K (K <= 126), taken off by
+// two Montgomery reductions by 2^64.  About 44 turns of some 25 one-cycle
+// instructions; the power p - 2 takes about 95 dependent modular products
+// (k_vs_delta at t = 50: 22.7 -> 9.1 us; 5000 Thiele slices: 255 -> 226 us).
+ZR_HD uint64_t zr_inv(const zr_mod& M, uint64_t a) {
+  if (a == 0) return 0;
+  const uint64_t p = M.p;
+  uint32_t K = (uint32_t)__builtin_ctzll(a);
+  uint64_t u = a >> K, v = p, x = 1, y = 0;
+  while (u != v) {
+    const bool lt = u < v;
+    const uint64_t d = lt ? v - u : u - v, s = x + y;
+    const uint32_t k = (uint32_t)__builtin_ctzll(d);
+    u = lt ? u : d >> k;
+    v = lt ? d >> k : v;
+    x = lt ? x << k : s;
+    y = lt ? s : y << k;
+    K += k;
+  }
+  // x 2^(128 - K), then twice divided by 2^64
+  uint64_t ni = 1;  // -1/p modulo 2^64: Newton's iteration doubles the correct bits
+  for (int i = 0; i < 6; ++i) ni *= 2 + p * ni;
+  uint32_t e = 128 - K;  // 2..128
+  uint64_t r = x;
+  while (e) {
+    const uint32_t k = e < 32 ? e : 32;
+    r = zr_mod128(M, r >> (64 - k), r << k);
+    e -= k;
+  }
+  for (int i = 0; i < 2; ++i) {
+    const uint64_t m = r * ni;
+    r = zr_mulhi(m, p) + (r != 0);  // the low words cancel, with a carry unless both are zero
+    r = r >= p ? r - p : r;
+  }
+  return r;
+}
 
 // Exact 192-bit accumulator of products of two values below 2^64.
 struct zr_acc192 {
