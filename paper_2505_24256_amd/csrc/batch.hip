@@ -18,6 +18,7 @@
 #include "field.hpp"
 #include "kernels.hpp"
 #include "kernels_dev.hpp"
+#include "tree.hpp"
 
 namespace zr {
 
@@ -40,8 +41,9 @@ struct BSolve {
   uint64_t* qstart;
   uint64_t* mL;
   uint64_t* winv;
-  const uint64_t* rhs;  // [R][t]
-  uint64_t* out;        // [R][t]
+  const uint64_t* rhs;  // [R][ld]
+  uint64_t* out;        // [R - a.sums][ld]
+  size_t ld;
   int32_t* status;
   uint32_t RT, ntile;
   // offsets of VT, spart and hpart in the batch's shared packed-row and
@@ -56,7 +58,7 @@ __global__ void k_b_pack(uint32_t n, const uint32_t* __restrict__ prefix, const 
   const size_t idx = (size_t)(blockIdx.x - prefix[s]) * blockDim.x + threadIdx.x;
   const uint32_t t = b.a.t;
   if (idx < (size_t)b.ntile * t * b.a.ldv)
-    ((uint32_t*)b.a.VT)[idx] = pack_word(idx, t, b.a.R, b.RT, b.a.ldv, b.rhs, t, b.a.Mc);
+    ((uint32_t*)b.a.VT)[idx] = pack_word(idx, t, b.a.R, b.RT, b.a.ldv, b.rhs, b.ld, b.a.Mc);
   if (idx < t) ((uint64_t*)b.a.mono_p)[idx] = zr_shoup_pre(b.a.M, b.a.mono[idx]);
 }
 
@@ -140,7 +142,7 @@ __global__ void k_b_scale(uint32_t n, const uint32_t* __restrict__ prefix, const
   const BSolve& b = sys[s];
   const uint32_t lb = blockIdx.x - prefix[s], nrb = cdiv(b.a.t, 256);
   const uint32_t l = (lb % nrb) * 256 + threadIdx.x;
-  if (l < b.a.t) vs_scale_body(b.a, l, lb / nrb, b.winv, b.out, b.a.t);
+  if (l < b.a.t) vs_scale_body(b.a, l, b.a.sums + lb / nrb, b.winv, b.out, b.ld);
 }
 
 // Small systems packed into shared wavefronts: lane i of item w handles row
@@ -731,13 +733,75 @@ static BPlan bplan(uint32_t t, uint32_t R, double cap, const Tuning& T) {
   return P;
 }
 
+// Systems from which a batch's tree is built, and the work it has to save (modular
+// products) for its some 60 launches of 5 us.
+constexpr uint32_t kBatchTreeMinT = 1536;
+constexpr double kBatchTreeMinWork = 3e9;
+// A level's transforms cost about as much per row and right-hand side as this many
+// products of the quadratic pass.
+constexpr double kTreeLevelSteps = 190;
+
+// Large systems of a batch through one tree per right-hand-side count: the
+// system's job is replaced by one job per leaf block.
+static void split_large(const zr_mod& M, std::vector<SolveJob>& jobs, std::vector<TreeRun>& trees, DevArena& A,
+                        hipStream_t s) {
+  if (!vsolve_uses_pc()) return;
+  std::vector<uint32_t> cand;
+  for (uint32_t i = 0; i < jobs.size(); ++i)
+    if (jobs[i].t >= kBatchTreeMinT && jobs[i].t <= (1u << (kNttMaxLog - 1))) cand.push_back(i);
+  std::stable_sort(cand.begin(), cand.end(), [&](uint32_t x, uint32_t y) {
+    if (jobs[x].R != jobs[y].R) return jobs[x].R < jobs[y].R;
+    return tree_log_top(jobs[x].t) > tree_log_top(jobs[y].t);
+  });
+  std::vector<SolveJob> leaves;
+  for (size_t i0 = 0, i1; i0 < cand.size(); i0 = i1) {
+    const uint32_t R = jobs[cand[i0]].R;
+    double saved = 0;
+    size_t words = 0;
+    for (i1 = i0; i1 < cand.size() && jobs[cand[i1]].R == R; ++i1) {
+      const double t = jobs[cand[i1]].t;
+      saved += t * R * (t - kTreeLeaf - kTreeLevelSteps * (tree_log_top(jobs[cand[i1]].t) - kTreeLeafLog));
+      words += (size_t)(R + 1) * jobs[cand[i1]].t;
+    }
+    if (saved < kBatchTreeMinWork) continue;
+    trees.emplace_back();
+    TreeRun& T = trees.back();
+    uint64_t* f = A.alloc<uint64_t>(words);
+    for (size_t i = i0; i < i1; ++i) {
+      const SolveJob& j = jobs[cand[i]];
+      TreeSys y{};
+      y.end = j.t;
+      y.rhs = j.rhs;
+      y.ld_rhs = y.ld = j.t;
+      y.f = f;
+      f += (size_t)(R + 1) * j.t;
+      T.sys.push_back(y);
+    }
+    tree_prepare(T, M, R, true, A, s);
+    for (size_t i = i0; i < i1; ++i) {
+      SolveJob& j = jobs[cand[i]];
+      const TreeSys& y = T.sys[i - i0];
+      for (uint32_t b = 0; b < j.t; b += kTreeLeaf)
+        leaves.push_back(SolveJob{std::min(kTreeLeaf, j.t - b), R + 1, j.mono + b, y.f + b, j.status, j.rhs + b, j.t,
+                                  T.leafM + y.off + b});
+      j.t = 0;  // replaced
+    }
+  }
+  jobs.erase(std::remove_if(jobs.begin(), jobs.end(), [](const SolveJob& j) { return !j.t; }), jobs.end());
+  jobs.insert(jobs.end(), leaves.begin(), leaves.end());
+}
+
 void batched_solve(const zr_mod& M, const std::vector<SolveJob>& jobs_in, hipStream_t s) {
   std::vector<SolveJob> jobs;
   for (const auto& j : jobs_in) {
     if (!j.t || !j.R) continue;
     jobs.push_back(j);
+    count_solve(j.t, j.R);
   }
   if (jobs.empty()) return;
+  DevArena A(s);
+  std::vector<TreeRun> trees;
+  split_large(M, jobs, trees, A, s);
   const uint32_t n = (uint32_t)jobs.size();
   const Tuning& T = tuning();
   const uint32_t cus = device_cus();
@@ -748,7 +812,6 @@ void batched_solve(const zr_mod& M, const std::vector<SolveJob>& jobs_in, hipStr
   std::vector<BPlan> plan(n);
   for (uint32_t i = 0; i < n; ++i) plan[i] = bplan(jobs[i].t, jobs[i].R, cap, T);
 
-  DevArena A(s);
   // ---- master polynomials; chunk length of each product-tree level from the
   // level's total number of row blocks
   std::vector<BMaster> bm(n);
@@ -771,7 +834,7 @@ void batched_solve(const zr_mod& M, const std::vector<SolveJob>& jobs_in, hipStr
     b.t = t;
     b.big = big;
     b.mono = jobs[i].mono;
-    b.buf[0] = A.alloc<uint64_t>(t);
+    b.buf[0] = jobs[i].Mc ? jobs[i].Mc : A.alloc<uint64_t>(t);
     b.buf[1] = A.alloc<uint64_t>(t);
     b.limbs[0] = A.alloc<uint4>(t + 16);
     b.limbs[1] = A.alloc<uint4>(t + 16);
@@ -822,7 +885,9 @@ void batched_solve(const zr_mod& M, const std::vector<SolveJob>& jobs_in, hipStr
     b.a.hpart = part_base + b.hp_off;
     b.winv = A.alloc<uint64_t>(2 * t);
     b.rhs = jobs[i].rhs;
-    b.out = jobs[i].rhs;
+    b.out = jobs[i].out ? jobs[i].out : jobs[i].rhs;
+    b.ld = jobs[i].out ? jobs[i].ld : t;
+    b.a.sums = jobs[i].out ? 1 : 0;
     b.status = jobs[i].status;
     b.RT = P.RT;
     b.ntile = P.ntile;
@@ -830,7 +895,7 @@ void batched_solve(const zr_mod& M, const std::vector<SolveJob>& jobs_in, hipStr
     chain.add(S > 1 ? (size_t)cdiv(t, 256) * (S - 1) : 0);
     scan.add(S > 1 ? cdiv(t, 256) : 0);
     rows.add(cdiv(t, kDeltaBlock));
-    scale.add((size_t)cdiv(t, 256) * P.R);
+    scale.add((size_t)cdiv(t, 256) * (P.R - b.a.sums));
   }
   // conv levels
   std::vector<Segs> conv, csum;
@@ -950,6 +1015,7 @@ void batched_solve(const zr_mod& M, const std::vector<SolveJob>& jobs_in, hipStr
     }
     if (fix.total()) hipLaunchKernelGGL(k_b_master_fix, dim3(fix.total()), dim3(256), 0, ls, n, P32(o_fix), d_bm);
   }
+  for (const TreeRun& t : trees) tree_launch(t, ls);
   {
     TimedLaunch tl("batch_pack", ls);
     hipLaunchKernelGGL(k_b_pack, dim3(pack.total()), dim3(256), 0, ls, n, P32(o_pack), d_bs);
@@ -996,7 +1062,6 @@ void batched_solve(const zr_mod& M, const std::vector<SolveJob>& jobs_in, hipStr
     retire_graph(s, g, ge);
   }
   check(hipGetLastError());
-  for (const auto& j : jobs) count_solve(j.t, j.R);
 }
 
 size_t newton_W_words(uint32_t D1) { return (size_t)D1 * D1 * 3 + 24; }

@@ -54,6 +54,12 @@ struct SolveJob {
   const uint64_t* mono;
   uint64_t* rhs;
   int32_t* status;
+  // leaf block of a larger system (tree.hpp), null in a caller's job: series rhs[R]
+  // at stride ld, the power sums first; unknowns of series 1.. into out at stride ld;
+  // master polynomial into Mc
+  uint64_t* out = nullptr;
+  size_t ld = 0;
+  uint64_t* Mc = nullptr;
 };
 
 // Master polynomials and solves of all jobs (enqueued on s, no host sync),

@@ -320,7 +320,7 @@ __global__ void __launch_bounds__(kDeltaBlock) k_vs_delta(VsArgs a, const uint64
 
 __global__ void k_vs_scale(VsArgs a, const uint64_t* __restrict__ winv, uint64_t* __restrict__ out, size_t ld_out) {
   const uint32_t l = blockIdx.x * blockDim.x + threadIdx.x;
-  if (l < a.t) vs_scale_body(a, l, blockIdx.y, winv, out, ld_out);
+  if (l < a.t) vs_scale_body(a, l, a.sums + blockIdx.y, winv, out, ld_out);
 }
 
 typedef void (*DotsKernel)(VsArgs);
@@ -526,21 +526,6 @@ LeafPlan leaf_plan(uint32_t t, uint32_t R, bool sums) {
 }
 }  // namespace
 
-// denominators and their inverses from the values of the power sums' series
-__global__ void __launch_bounds__(kDeltaBlock) k_leaf_delta(VsArgs a, uint64_t* __restrict__ winv,
-                                                             int32_t* __restrict__ status) {
-  __shared__ uint64_t sh[kDeltaBlock / 64 + 1];
-  const uint32_t l = blockIdx.x * kDeltaBlock + threadIdx.x;
-  const bool live = l < a.t;
-  const uint64_t w = live ? a.spart[l] : 0;
-  if (live && w == 0) atomicCAS(status, 0, -3);  // ZR_ESINGULAR
-  const uint64_t wi = block_inverse(a.M, w, live, sh);
-  if (live) {
-    winv[l] = wi;
-    winv[a.t + l] = wi ? zr_shoup_pre(a.M, wi) : 0;
-  }
-}
-
 size_t vsolve_leaf_words(uint32_t t, uint32_t R1, bool sums) {
   const LeafPlan q = leaf_plan(t, R1, sums);
   // VT | mono_p | spart [Rg][t] | D_c [S][t] | winv [2t] | CL [t][6] (32-bit)
@@ -606,12 +591,14 @@ hipError_t vsolve_leaf(const zr_mod& M, uint32_t t, uint32_t R1, bool sums, uint
     }
     {
       TimedLaunch tl("vs_finish", s);
-      const bool first = sums && g == 0;  // series 0 holds the denominators
-      if (first) hipLaunchKernelGGL(k_leaf_delta, dim3(cdiv(t, kDeltaBlock)), dim3(kDeltaBlock), 0, s, a, winv, status);
-      VsArgs b = a;
-      b.spart = spart + (first ? t : 0);
-      const uint32_t n = Rg - (first ? 1 : 0), o = r0 - (sums && !first ? 1 : 0);
-      if (n) hipLaunchKernelGGL(k_vs_scale, dim3(cdiv(t, 256), n), dim3(256), 0, s, b, winv, out + (size_t)o * ld_out, ld_out);
+      a.sums = sums && g == 0 ? 1 : 0;  // series 0 holds the denominators
+      if (a.sums)
+        hipLaunchKernelGGL(k_vs_delta, dim3(cdiv(t, kDeltaBlock)), dim3(kDeltaBlock), 0, s, a, (const uint64_t*)nullptr,
+                           winv, status);
+      const uint32_t o = r0 - (sums && g > 0 ? 1 : 0);
+      if (Rg > a.sums)
+        hipLaunchKernelGGL(k_vs_scale, dim3(cdiv(t, 256), Rg - a.sums), dim3(256), 0, s, a, winv, out + (size_t)o * ld_out,
+                           ld_out);
     }
     r0 += Rg;
   }

@@ -41,6 +41,9 @@ struct VsArgs {
   // leaf blocks of the subproduct tree (0: one system): rows [B u, B (u+1)) are
   // a system of their own, with master polynomial and samples at those indices
   uint32_t blk = 0;
+  // 1: series 0 are the power sums of the whole tree's system, so its values are the
+  // denominators m M'(m), and the right-hand sides are series 1..R-1
+  uint32_t sums = 0;
 };
 
 __device__ __forceinline__ void chunk_range(uint32_t t, uint32_t L, uint32_t c, uint32_t& lo, uint32_t& hi) {
@@ -735,7 +738,10 @@ __device__ __forceinline__ void vs_delta_block(const VsArgs& a, uint32_t l, cons
   const zr_mod M = a.M;
   const bool live = l < a.t;
   uint64_t w = 0;
-  if (live) {
+  if (live && a.sums) {
+    for (uint32_t c = 0; c < a.Sd; ++c) w = zr_add(M, w, a.spart[(size_t)c * a.R * a.t + l]);
+    if (w == 0) atomicCAS(status, 0, -3);
+  } else if (live) {
     const uint64_t m = a.mono[l];
     // chunk partials from the top chunk (c = 0) down, Horner in m^L (m^len
     // for the last, shorter chunk)
@@ -767,14 +773,14 @@ __device__ __forceinline__ void vs_delta_block(const VsArgs& a, uint32_t l, cons
   }
 }
 
-// Combine chunks, part 2 for row l and right-hand side j:
+// Combine chunks, part 2 for row l and series j (right-hand side j, or j - 1 behind power sums):
 // a^(j)_l = (sum_c s^(j)_{l,c}) / (m_l delta_l).
 __device__ __forceinline__ void vs_scale_body(const VsArgs& a, uint32_t l, uint32_t j, const uint64_t* __restrict__ winv,
                                               uint64_t* __restrict__ out, size_t ld_out) {
   const zr_mod M = a.M;
   uint64_t s = 0;
   for (uint32_t c = 0; c < a.Sd; ++c) s = zr_add(M, s, a.spart[((size_t)c * a.R + j) * a.t + l]);
-  out[(size_t)j * ld_out + l] = zr_shoup(M, s, winv[l], winv[a.t + l]);
+  out[(size_t)(j - a.sums) * ld_out + l] = zr_shoup(M, s, winv[l], winv[a.t + l]);
 }
 
 // ---- master polynomial (product tree) -------------------------------------------

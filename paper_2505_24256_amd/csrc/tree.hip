@@ -21,22 +21,24 @@
 // both evaluate the same polynomial identities exactly.
 //
 // Whole solve, quadratic against tree, one MI355X: t = 9 997, R = 30: 1.07 ->
-// 0.56 ms; t = 100 003, R = 17: 49.7 -> 2.27 ms; t = 300 007, R = 40: 781 -> 14.6 ms
-// (transforms 11 ms, bound by integer issue and by the residues' traffic; the
-// leaves' dot products 1.9 ms).
+// 0.50 ms; t = 100 003, R = 17: 49.6 -> 1.80 ms; t = 300 007, R = 40: 781 -> 10.0 ms
+// (rows 3.9 ms, bound by integer issue; columns and Chinese remainder 3.0 ms, by the
+// residues' traffic; the leaves' dot products 1.9 ms).  256 uneven systems of 10 to
+// 20 000 unknowns, R = 30, the large ones through one tree: 52.0 -> 10.5 ms.
 //
 // A node of 2^k rows uses cyclic products of length N = 2^k: sums over i + k <= n
 // do not wrap for the coefficients wanted, the upper half of the product of the
 // reversed series with the sibling's polynomial.  Transforms of up to 2^12 points run in one
 // workgroup's LDS; a longer one is a matrix of N1 rows by 2^12 columns: the
 // first log2(N1) layers on columns (the same constants for every column), then
-// each row b, twisted by w_N^(rev(b) j) so that it uses the constants of a
-// plain transform.
+// each row b, twisted by w_N^(rev(b) j) at the column pass so that it uses the constants
+// of a plain transform.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include <algorithm>
 
+#include "batch.hpp"
 #include "driver.hpp"
 #include "field.hpp"
 #include "kernels.hpp"
@@ -50,8 +52,8 @@ namespace {
 
 constexpr int kRowLog = 12;                  // longest transform of one workgroup
 constexpr uint32_t kRow = 1u << kRowLog;
-constexpr uint32_t kLeafLog = 9;             // leaf blocks of 512 rows
-constexpr uint32_t kLeaf = 1u << kLeafLog;
+constexpr uint32_t kLeafLog = kTreeLeafLog;
+constexpr uint32_t kLeaf = kTreeLeaf;
 static_assert(kLeafLog + 1 >= 10, "the shortest row transform has 2^10 points");
 
 // T[i], 1/T[i], and the powers w^e of the root of order 2^22 in two digits of
@@ -125,59 +127,82 @@ struct ColLds {
   }
 };
 
-// Series or polynomials that a level reads: array j at p + j ld, or px for j = jx.
-struct Src {
-  const uint64_t* p;
-  size_t ld;
-  const uint64_t* px;
-  uint32_t jx;
-  __device__ __forceinline__ const uint64_t* at(uint32_t j) const { return j == jx ? px : p + (size_t)j * ld; }
-};
-
-// One level of the tree: nodes of N rows, children of h = N/2; nn nodes have
-// two children (a last node of at most h rows passes through unchanged).
+// One level of the tree: nodes of N rows, children of h = N/2.  Rows of all
+// systems stand in one index space, each system at a multiple of its own top
+// node's size (TreeSys::off), largest tops first, so nodes of N rows are the
+// aligned ranges of a prefix of it.  A node of at most h rows passes through
+// unchanged; one without rows is skipped.
 struct Level {
-  uint32_t t, logN, N, h, nn;
+  uint32_t logN, N, h, nn;
   uint32_t R;          // series of the call
-  Src f;               // parents' series
-  uint64_t* fout;      // children's series [R][t]
+  uint32_t j0;         // the first of them
+  TreeSys one;         // the only system (sys null), or
+  const TreeSys* sys;  // the systems, and the system of each leaf block
+  const uint32_t* sys_of;
+  const uint64_t* sums;  // power sums, series 0 (null: none)
   const uint64_t* poly;  // children's polynomials
   uint64_t* pout;      // parents' polynomials
   uint32_t* X;         // column-transformed residues [prime][series or child][node N + s]
   uint32_t* Y;         // products [prime][series][side][...]
   uint32_t* K;         // children's transforms [prime][child][N] times 2^32 / N
   size_t ldX, ldY, ldK;  // words per prime
-  // power series of the power sums (one product at a time, nn = 1)
-  const uint64_t* root;  // coefficients of M
-  uint64_t* g;           // 1/Q, Q the reversed M
+  const uint32_t* tw;  // twist factors, 2^twLog words per direction and prime
+  uint32_t twLog;
+  // power series of the power sums: one product per system, systems item0..
+  uint32_t item0;
+  uint64_t* g;    // 1/Q, Q the reversed M
   uint64_t* aux;
-  uint32_t len;          // terms of a plain source
+  uint32_t full;  // kInverse: all t terms (else the first h)
 };
 
+// row is the same for all lanes of a wave
+__device__ __forceinline__ TreeSys sys_at(const Level& a, uint32_t row) {
+  return a.sys ? a.sys[a.sys_of[__builtin_amdgcn_readfirstlane(row) >> kLeafLog]] : a.one;
+}
+__device__ __forceinline__ TreeSys sys_item(const Level& a, uint32_t item) {
+  return a.sys ? a.sys[__builtin_amdgcn_readfirstlane(a.item0 + item)] : a.one;
+}
+__device__ __forceinline__ bool splits(const Level& a, const TreeSys& y, uint32_t node) {
+  return y.end > node * a.N + a.h;
+}
+
 // What a transform reads at point s:
-//   kSeries  series j of a node, reversed: f_i at point N - i, zero beyond its n
+//   kSeries  series j of a node, reversed: f_i at point N - i, zero beyond its n;
+//            the top node's are the samples (series 0 the power sums, where they are made)
 //   kChild   a child's polynomial: its coefficients and the leading 1
-//   kInverse the first len terms of g; kAux the first len terms of aux
+//   kInverse the first h (or t) terms of g; kAux the first h terms of aux
 //   kRev     Q = rev(M), Q_0 = 1, Q_s = M_(t-s)
 //   kDeriv   -Q', coefficients -(s+1) M_(t-1-s), s < t
 enum Source { kSeries, kChild, kInverse, kAux, kRev, kDeriv };
 template <int SRC>
-__device__ __forceinline__ uint64_t source_point(const Level& a, const zr_mod& M, uint32_t j, uint32_t item, uint32_t s) {
+__device__ __forceinline__ uint64_t source_point(const Level& a, const TreeSys& y, const zr_mod& M, uint32_t j,
+                                                 uint32_t item, uint32_t s) {
+  const uint32_t t = y.end - y.off;
   if constexpr (SRC == kSeries) {
-    const size_t i = (size_t)item * a.N + (a.N - 1 - s);
-    return i < a.t ? a.f.at(j)[i] : 0;
+    const uint32_t row = item * a.N + (a.N - 1 - s);
+    const uint32_t jj = a.j0 + j;
+    const uint64_t* f;
+    if (a.logN != y.logTop) f = y.f + (size_t)jj * y.ld;
+    else if (a.sums) f = jj == 0 ? a.sums + y.off : y.rhs + (size_t)(jj - 1) * y.ld_rhs;
+    else f = y.rhs + (size_t)jj * y.ld_rhs;
+    return row < y.end ? f[row - y.off] : 0;
   } else if constexpr (SRC == kChild) {
-    const uint32_t n = std::min(a.h, a.t - item * a.h);
-    return s < n ? a.poly[(size_t)item * a.h + s] : (s == n ? 1 : 0);
+    const uint32_t row = item * a.h, n = row < y.end ? std::min(a.h, y.end - row) : 0;
+    return s < n ? a.poly[row + s] : (s == n ? 1 : 0);
   } else if constexpr (SRC == kInverse) {
-    return s < a.len ? a.g[s] : 0;
+    return s < (a.full ? t : a.h) ? a.g[y.off + s] : 0;
   } else if constexpr (SRC == kAux) {
-    return s < a.len ? a.aux[s] : 0;
+    return s < a.h ? a.aux[y.off + s] : 0;
   } else if constexpr (SRC == kRev) {
-    return s == 0 ? 1 : (s <= a.t ? a.root[a.t - s] : 0);
+    return s == 0 ? 1 : (s <= t ? a.poly[y.end - s] : 0);
   } else {
-    return s < a.t ? zr_neg(M, zr_mul(M, (s + 1) % M.p, a.root[a.t - 1 - s])) : 0;
+    return s < t ? zr_neg(M, zr_mul(M, (s + 1) % M.p, a.poly[y.end - 1 - s])) : 0;
   }
+}
+// the system an item of a source belongs to
+template <int SRC>
+__device__ __forceinline__ TreeSys source_sys(const Level& a, uint32_t item) {
+  return SRC == kSeries ? sys_at(a, item * a.N) : SRC == kChild ? sys_at(a, item * a.h) : sys_item(a, item);
 }
 
 // Where the product's point s goes:
@@ -187,23 +212,29 @@ __device__ __forceinline__ uint64_t source_point(const Level& a, const zr_mod& M
 //   kSums     the first t terms into aux
 enum Dest { kChildren, kParent, kHigh, kGrow, kSums };
 template <int DST>
-__device__ __forceinline__ void store_point(const Level& a, const zr_mod& M, uint32_t j, uint32_t side, uint32_t node,
-                                            uint32_t s, uint64_t v) {
+__device__ __forceinline__ void store_point(const Level& a, const TreeSys& y, const zr_mod& M, uint32_t j, uint32_t side,
+                                            uint32_t node, uint32_t s, uint64_t v) {
   if constexpr (DST == kChildren) {
-    const size_t pos = (size_t)node * a.N + side * a.h + (a.N - 1 - s);
-    if (pos < a.t) a.fout[(size_t)j * a.t + pos] = v;
+    const uint32_t row = node * a.N + side * a.h + (a.N - 1 - s);
+    if (row < y.end) y.f[(size_t)(a.j0 + j) * y.ld + (row - y.off)] = v;
   } else if constexpr (DST == kParent) {
-    const size_t pos = (size_t)node * a.N + s;
-    if (pos >= a.t) return;
-    if (s == 0 && a.t - node * a.N >= a.N) v = zr_sub(M, v, 1 % M.p);
-    a.pout[pos] = v;
+    const uint32_t row = node * a.N + s;
+    if (row >= y.end) return;
+    if (s == 0 && y.end - node * a.N >= a.N) v = zr_sub(M, v, 1 % M.p);
+    a.pout[row] = v;
   } else if constexpr (DST == kHigh) {
-    a.aux[s - a.h] = v;
+    a.aux[y.off + s - a.h] = v;
   } else if constexpr (DST == kGrow) {
-    if (s < a.h) a.g[a.h + s] = zr_neg(M, v);
+    if (s < a.h) a.g[y.off + a.h + s] = zr_neg(M, v);
   } else {
-    if (s < a.t) a.aux[s] = v;
+    if (s < y.end - y.off) a.aux[y.off + s] = v;
   }
+}
+template <int DST>
+__device__ __forceinline__ TreeSys dest_sys(const Level& a, uint32_t node, bool& live) {
+  const TreeSys y = DST == kChildren || DST == kParent ? sys_at(a, node * a.N) : sys_item(a, node);
+  live = DST == kChildren || DST == kParent ? splits(a, y, node) : true;
+  return y;
 }
 
 struct RowK {
@@ -211,23 +242,16 @@ struct RowK {
 };
 __device__ __forceinline__ RowK row_mod(const NttMods& m, uint32_t c) { return RowK{m.q[c], m.ni[c], m.r1[c], m.r2[c]}; }
 
-// Twist factors of row b of N1 = N / 2^12 at the thread's points j = r + 256 k:
-// w_N^(+-rev(b) j)
-template <bool INV>
-__device__ __forceinline__ void row_twist(uint32_t (&w)[16], uint32_t logN, uint32_t b, uint32_t r, uint32_t c, const RowK& m) {
-  const uint32_t a = logN - kRowLog;
-  const uint32_t rev = a ? __brev(b) >> (32 - a) : 0;
+// Twist factors of the column transforms, w_N^(rev(b) j) at row b, column j, and
+// their inverses, as [dir][prime][row 2^12 + column].  rev counts the bits of b
+// below N/2^12; one table serves every N, since halving N halves rev(b) and squares w_N.
+__global__ void __launch_bounds__(256) k_tree_twist(uint32_t* __restrict__ tw, uint32_t logN, NttMods mods) {
+  const uint32_t e = blockIdx.x * 256 + threadIdx.x, c = blockIdx.y, inv = blockIdx.z, a = logN - kRowLog;
+  const RowK m = row_mod(mods, c);
   constexpr uint32_t mask = (1u << kNttMaxLog) - 1;
-  auto power = [&](uint32_t e) {  // w_N^e or its inverse, Montgomery form
-    uint32_t x = (e << (kNttMaxLog - logN)) & mask;
-    if (INV) x = (0u - x) & mask;
-    return red(mmul(g_tab.P0[c][x & 2047], g_tab.P1[c][x >> 11], m.q, m.ni), m.q);
-  };
-  w[0] = power(rev * r);
-  const uint32_t s1 = power(rev * 256), s2 = power(rev * 512);
-  w[1] = red(mmul(w[0], s1, m.q, m.ni), m.q);
-#pragma unroll
-  for (int k = 2; k < 16; ++k) w[k] = red(mmul(w[k - 2], s2, m.q, m.ni), m.q);
+  uint32_t x = ((__brev(e >> kRowLog) >> (32 - a)) * (e & (kRow - 1)) << (kNttMaxLog - logN)) & mask;
+  if (inv) x = (0u - x) & mask;
+  tw[((size_t)(inv * kNp + c) << logN) + e] = red(mmul(g_tab.P0[c][x & 2047], g_tab.P1[c][x >> 11], m.q, m.ni), m.q);
 }
 
 // Where point p of a transform's block-ordered output is kept in K: four
@@ -248,7 +272,7 @@ template <int LOGN, bool DIRECT, int SRC>
 __global__ void __launch_bounds__(256) k_tree_kernels(Level a, NttMods mods, uint32_t items) {
   constexpr uint32_t NT = 1u << (LOGN - 4), PER = 256 / NT;
   __shared__ __align__(16) uint32_t sh[PER * kRowWords<LOGN>];
-  const uint32_t sub = threadIdx.x / NT, r = threadIdx.x % NT, c = blockIdx.y;
+  const uint32_t sub = __builtin_amdgcn_readfirstlane(threadIdx.x / NT), r = threadIdx.x % NT, c = blockIdx.y;
   const uint32_t it0 = blockIdx.x * PER + sub;
   const bool live = it0 < items;
   const uint32_t it = live ? it0 : items - 1;
@@ -256,14 +280,13 @@ __global__ void __launch_bounds__(256) k_tree_kernels(Level a, NttMods mods, uin
   const RowLds lds{sh + sub * kRowWords<LOGN>};
   uint32_t x[16];
   if constexpr (DIRECT) {
+    const TreeSys y = source_sys<SRC>(a, it);
 #pragma unroll
-    for (int k = 0; k < 16; ++k) x[k] = ntt_residue(source_point<SRC>(a, zr_mod{}, 0, it, r + NT * k), m.q, m.ni, m.r1, m.r2);
+    for (int k = 0; k < 16; ++k) x[k] = ntt_residue(source_point<SRC>(a, y, zr_mod{}, 0, it, r + NT * k), m.q, m.ni, m.r1, m.r2);
   } else {
-    uint32_t w[16];
-    row_twist<false>(w, a.logN, it & ((1u << (a.logN - kRowLog)) - 1), r, c, m);
     const uint32_t* src = a.X + c * a.ldX + (size_t)it * kRow;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) x[k] = mmul(src[r + NT * k], w[k], m.q, m.ni);
+    for (int k = 0; k < 16; ++k) x[k] = src[r + NT * k];
   }
   ntt_forward<LOGN>(x, r, lds, tab_T(c), m.q, m.ni);
   // times 2^64 / N under one reduction: 2^32 / N
@@ -283,14 +306,14 @@ template <int LOGN, bool DIRECT>
 __global__ void __launch_bounds__(256) k_tree_product(Level a, NttMods mods, uint32_t items) {
   constexpr uint32_t NT = 1u << (LOGN - 4), PER = 256 / NT;
   __shared__ __align__(16) uint32_t sh[PER * kRowWords<LOGN>];
-  const uint32_t sub = threadIdx.x / NT, r = threadIdx.x % NT, c = blockIdx.y;
+  const uint32_t sub = __builtin_amdgcn_readfirstlane(threadIdx.x / NT), r = threadIdx.x % NT, c = blockIdx.y;
   const uint32_t it0 = blockIdx.x * PER + sub;
   const bool live = it0 < items;
   const uint32_t it = live ? it0 : items - 1;
   const RowK m = row_mod(mods, c);
   const RowLds lds{sh + sub * kRowWords<LOGN>};
-  const uint32_t N1 = DIRECT ? 1 : a.N >> kRowLog;
-  const uint32_t node = it / N1, b = it % N1;
+  const uint32_t lg1 = DIRECT ? 0 : a.logN - kRowLog;
+  const uint32_t node = it >> lg1, b = it & ((1u << lg1) - 1);
   uint32_t x[16], y[16];
   const uint32_t* kl = a.K + c * a.ldK + (size_t)(2 * node) * a.N + (size_t)b * (1u << LOGN);
   load_k(x, kl, r, NT);
@@ -300,12 +323,6 @@ __global__ void __launch_bounds__(256) k_tree_product(Level a, NttMods mods, uin
 #pragma unroll
   for (int k = 0; k < 16; ++k) x[k] = mmul(mmul(x[k], y[k], m.q, m.ni), a.N, m.q, m.ni);
   ntt_inverse<LOGN>(x, r, lds, tab_Ti(c), m.q, m.ni);
-  if constexpr (!DIRECT) {
-    uint32_t w[16];
-    row_twist<true>(w, a.logN, b, r, c, m);
-#pragma unroll
-    for (int k = 0; k < 16; ++k) x[k] = mmul(x[k], w[k], m.q, m.ni);
-  }
   if (live) {
     uint32_t* dst = a.Y + c * a.ldY + (size_t)it * (1u << LOGN);
 #pragma unroll
@@ -314,45 +331,46 @@ __global__ void __launch_bounds__(256) k_tree_product(Level a, NttMods mods, uin
 }
 
 // The two products of each node's series, rows: series transform, times the
-// sibling's transform, back, for each child.  blockIdx.y = prime, blockIdx.z =
-// group of `per` series, which share the registers that hold the two kernels.
+// sibling's transform, back, for each child.  About 160 vector instructions per point
+// (three transforms of 12 layers at 8 a butterfly); with the twist factors taken
+// out of this pass and the kernels read where they are used it holds 98 VGPRs without
+// spills: 90 -> 42 us for 5 series of 3*10^5 rows, about 35 at full issue.  blockIdx.y =
+// prime, blockIdx.z = group of `per` series.
 template <int LOGN, bool DIRECT>
 __global__ void __launch_bounds__(256, 4) k_tree_descend(Level a, NttMods mods, uint32_t items, uint32_t per) {
   constexpr uint32_t NT = 1u << (LOGN - 4), PER = 256 / NT;
   __shared__ __align__(16) uint32_t sh[PER * kRowWords<LOGN>];
-  const uint32_t sub = threadIdx.x / NT, r = threadIdx.x % NT, c = blockIdx.y;
+  const uint32_t sub = __builtin_amdgcn_readfirstlane(threadIdx.x / NT), r = threadIdx.x % NT, c = blockIdx.y;
   const uint32_t it0 = blockIdx.x * PER + sub;
-  const bool live = it0 < items;
-  const uint32_t it = live ? it0 : items - 1;
+  const uint32_t it = std::min(it0, items - 1);
   const RowK m = row_mod(mods, c);
   const RowLds lds{sh + sub * kRowWords<LOGN>};
-  const uint32_t N1 = DIRECT ? 1 : a.N >> kRowLog;
-  const uint32_t node = it / N1, b = it % N1;
-  uint32_t kl[16], kr[16], fw[16], iw[16];
+  const uint32_t lg1 = DIRECT ? 0 : a.logN - kRowLog;
+  const uint32_t node = it >> lg1, b = it & ((1u << lg1) - 1);
+  const TreeSys sy = sys_at(a, node * a.N);
+  const bool live = it0 < items && splits(a, sy, node);
+  if (PER == 1 && !live) return;
   const uint32_t* kp = a.K + c * a.ldK + (size_t)(2 * node) * a.N + (size_t)b * (1u << LOGN);
-  load_k(kl, kp, r, NT);
-  load_k(kr, kp + a.N, r, NT);
-  if constexpr (!DIRECT) {
-    row_twist<false>(fw, a.logN, b, r, c, m);
-    row_twist<true>(iw, a.logN, b, r, c, m);
-  }
   const uint32_t j1 = std::min(a.R, (blockIdx.z + 1) * per);
+#pragma unroll 1
   for (uint32_t j = blockIdx.z * per; j < j1; ++j) {
-    uint32_t x[16], y[16];
+    uint32_t y[16];
     if constexpr (DIRECT) {
 #pragma unroll
       for (int k = 0; k < 16; ++k)
-        y[k] = ntt_residue(source_point<kSeries>(a, zr_mod{}, j, node, r + NT * k), m.q, m.ni, m.r1, m.r2);
+        y[k] = ntt_residue(source_point<kSeries>(a, sy, zr_mod{}, j, node, r + NT * k), m.q, m.ni, m.r1, m.r2);
     } else {
       const uint32_t* src = a.X + c * a.ldX + (size_t)j * a.nn * a.N + (size_t)it * kRow;
 #pragma unroll
-      for (int k = 0; k < 16; ++k) y[k] = mmul(src[r + NT * k], fw[k], m.q, m.ni);
+      for (int k = 0; k < 16; ++k) y[k] = src[r + NT * k];
     }
     ntt_forward<LOGN>(y, r, lds, ntt_reload(tab_T(c)), m.q, m.ni);
 #pragma unroll 1
     for (uint32_t side = 0; side < 2; ++side) {
+      uint32_t x[16];
+      load_k(x, kp + (side ? 0 : a.N), r, NT);  // the sibling's
 #pragma unroll
-      for (int k = 0; k < 16; ++k) x[k] = mmul(y[k], side ? kl[k] : kr[k], m.q, m.ni);  // the sibling's
+      for (int k = 0; k < 16; ++k) x[k] = mmul(y[k], x[k], m.q, m.ni);
       ntt_inverse<LOGN>(x, r, lds, ntt_reload(tab_Ti(c)), m.q, m.ni);
       if constexpr (DIRECT) {
         // only the upper half is wanted
@@ -365,42 +383,39 @@ __global__ void __launch_bounds__(256, 4) k_tree_descend(Level a, NttMods mods, 
         uint32_t* dst = a.Y + c * a.ldY + (size_t)(j * 2 + side) * a.nn * a.N + (size_t)it * kRow;
         if (live) {
 #pragma unroll
-          for (int k = 0; k < 16; ++k) dst[r + NT * k] = mmul(x[k], iw[k], m.q, m.ni);
+          for (int k = 0; k < 16; ++k) dst[r + NT * k] = x[k];
         }
       }
     }
   }
 }
 
-// One product: the source's transform times the kernel's, back along the rows.
+// One product per item: the source's transform times the kernel's, back along the rows.
 template <int LOGN, bool DIRECT, int SRC>
-__global__ void __launch_bounds__(256) k_tree_conv(Level a, CrtP C, NttMods mods) {
-  constexpr uint32_t NT = 1u << (LOGN - 4);
-  __shared__ __align__(16) uint32_t sh[256 / NT * kRowWords<LOGN>];
-  const uint32_t r = threadIdx.x % NT, c = blockIdx.y, it = blockIdx.x;
-  const bool live = threadIdx.x < NT;  // the other threads repeat the work
+__global__ void __launch_bounds__(256) k_tree_conv(Level a, CrtP C, NttMods mods, uint32_t items) {
+  constexpr uint32_t NT = 1u << (LOGN - 4), PER = 256 / NT;
+  __shared__ __align__(16) uint32_t sh[PER * kRowWords<LOGN>];
+  const uint32_t sub = __builtin_amdgcn_readfirstlane(threadIdx.x / NT), r = threadIdx.x % NT, c = blockIdx.y;
+  const uint32_t it0 = blockIdx.x * PER + sub;
+  const bool live = it0 < items;
+  const uint32_t it = live ? it0 : items - 1;
   const RowK m = row_mod(mods, c);
-  const RowLds lds{sh + threadIdx.x / NT * kRowWords<LOGN>};
+  const RowLds lds{sh + sub * kRowWords<LOGN>};
   uint32_t x[16], w[16];
   if constexpr (DIRECT) {
+    const TreeSys y = sys_item(a, it);
 #pragma unroll
-    for (int k = 0; k < 16; ++k) x[k] = ntt_residue(source_point<SRC>(a, C.M, 0, 0, r + NT * k), m.q, m.ni, m.r1, m.r2);
+    for (int k = 0; k < 16; ++k) x[k] = ntt_residue(source_point<SRC>(a, y, C.M, 0, it, r + NT * k), m.q, m.ni, m.r1, m.r2);
   } else {
-    row_twist<false>(w, a.logN, it, r, c, m);
     const uint32_t* src = a.X + c * a.ldX + (size_t)it * kRow;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) x[k] = mmul(src[r + NT * k], w[k], m.q, m.ni);
+    for (int k = 0; k < 16; ++k) x[k] = src[r + NT * k];
   }
   ntt_forward<LOGN>(x, r, lds, tab_T(c), m.q, m.ni);
   load_k(w, a.K + c * a.ldK + (size_t)it * (1u << LOGN), r, NT);
 #pragma unroll
   for (int k = 0; k < 16; ++k) x[k] = mmul(x[k], w[k], m.q, m.ni);
   ntt_inverse<LOGN>(x, r, lds, tab_Ti(c), m.q, m.ni);
-  if constexpr (!DIRECT) {
-    row_twist<true>(w, a.logN, it, r, c, m);
-#pragma unroll
-    for (int k = 0; k < 16; ++k) x[k] = mmul(x[k], w[k], m.q, m.ni);
-  }
   if (live) {
     uint32_t* dst = a.Y + c * a.ldY + (size_t)it * (1u << LOGN);
 #pragma unroll
@@ -417,12 +432,15 @@ __global__ void __launch_bounds__(256) k_tree_crt(Level a, CrtP C) {
   const uint32_t w = DST == kChildren ? a.h : a.N;
   if (e >= a.nn * w) return;
   const uint32_t s = e % w + (DST == kChildren ? a.h : 0);
-  if (DST == kHigh && s < a.h) return;
+  if ((DST == kHigh && s < a.h) || (DST == kGrow && s >= a.h)) return;
+  bool live;
+  const TreeSys y = dest_sys<DST>(a, e / w, live);
+  if (!live) return;
   const uint32_t* src = a.Y + (DST == kChildren ? (size_t)(j * 2 + side) * a.nn * a.h : 0) + e;
   uint32_t u[kNp];
 #pragma unroll
   for (int c = 0; c < kNp; ++c) u[c] = src[c * a.ldY];
-  store_point<DST>(a, C.M, j, side, e / w, s, ntt_crt(C, u));
+  store_point<DST>(a, y, C.M, j, side, e / w, s, ntt_crt(C, u));
 }
 
 // ---- column transforms of N1 = 2^A rows -----------------------------------------------
@@ -442,31 +460,30 @@ struct ColGeom {
 };
 
 // A source's columns into X: blockIdx.x over items (nodes, children, one series) and tiles,
-// blockIdx.y = series.
+// blockIdx.y = series, blockIdx.z = prime.
 template <int A, int SRC>
-__global__ void __launch_bounds__(ColGeom<A>::TPB) k_tree_col_fwd(Level a, zr_mod M) {
+__global__ void __launch_bounds__(ColGeom<A>::TPB) k_tree_col_fwd(Level a, zr_mod M, NttMods mods) {
   using G = ColGeom<A>;
   __shared__ uint32_t sh[G::words];
-  const uint32_t item = blockIdx.x / G::tiles, tile = blockIdx.x % G::tiles, j = blockIdx.y;
+  const uint32_t item = blockIdx.x / G::tiles, tile = blockIdx.x % G::tiles, j = blockIdx.y, c = blockIdx.z;
   const uint32_t cl = threadIdx.x % G::C, r = threadIdx.x / G::C, col = tile * G::C + cl;
-  uint64_t v[G::E];
+  const TreeSys y = source_sys<SRC>(a, item);
+  if (SRC == kSeries && !splits(a, y, item)) return;
+  const RowK m = row_mod(mods, c);
+  uint32_t x[G::E], w[G::E];
 #pragma unroll
-  for (int k = 0; k < G::E; ++k) v[k] = source_point<SRC>(a, M, j, item, G::row(r, k) * kRow + col);
-  uint32_t* dst = a.X + ((size_t)j * a.nn + item) * a.N + col;
-#pragma unroll 1
-  for (int c = 0; c < kNp; ++c) {
-    const uint32_t q = kNtt.q[c], ni = kNtt.ni[c];
-    uint32_t x[G::E];
+  for (int k = 0; k < G::E; ++k)
+    x[k] = ntt_residue(source_point<SRC>(a, y, M, j, item, G::row(r, k) * kRow + col), m.q, m.ni, m.r1, m.r2);
 #pragma unroll
-    for (int k = 0; k < G::E; ++k) x[k] = ntt_residue(v[k], q, ni, kNtt.r1[c], kNtt.r2[c]);
-    const NttTable T = tab_T(c);
-    if constexpr (A <= 4)
-      ct_layers<G::E, A, true>(x, q, ni, [&](int, int i) { return T[i]; });
-    else
-      ntt_forward<A>(x, r, ColLds<G::C>{sh, cl}, T, q, ni);
+  for (int k = 0; k < G::E; ++k) w[k] = a.tw[((size_t)c << a.twLog) + G::rowb(r, k) * kRow + col];
+  const NttTable T = tab_T(c);
+  if constexpr (A <= 4)
+    ct_layers<G::E, A, true>(x, m.q, m.ni, [&](int, int i) { return T[i]; });
+  else
+    ntt_forward<A>(x, r, ColLds<G::C>{sh, cl}, T, m.q, m.ni);
+  uint32_t* dst = a.X + c * a.ldX + ((size_t)j * a.nn + item) * a.N + col;
 #pragma unroll
-    for (int k = 0; k < G::E; ++k) dst[c * a.ldX + (size_t)G::rowb(r, k) * kRow] = x[k];
-  }
+  for (int k = 0; k < G::E; ++k) dst[(size_t)G::rowb(r, k) * kRow] = mmul(x[k], w[k], m.q, m.ni);
 }
 
 // Back along the columns and through the Chinese remainder: children's series
@@ -479,6 +496,9 @@ __global__ void __launch_bounds__(ColGeom<A>::TPB) k_tree_col_inv(Level a, CrtP 
   constexpr int K1 = DST == kGrow ? G::E / 2 : G::E;                    // and one past the last
   const uint32_t node = blockIdx.x / G::tiles, tile = blockIdx.x % G::tiles, j = blockIdx.y, side = blockIdx.z;
   const uint32_t cl = threadIdx.x % G::C, r = threadIdx.x / G::C, col = tile * G::C + cl;
+  bool live;
+  const TreeSys y = dest_sys<DST>(a, node, live);
+  if (!live) return;
   const uint32_t* src = a.Y + ((size_t)(DST == kChildren ? j * 2 + side : 0) * a.nn + node) * a.N + col;
   uint32_t u[K1 - K0][kNp];
 #pragma unroll
@@ -486,7 +506,10 @@ __global__ void __launch_bounds__(ColGeom<A>::TPB) k_tree_col_inv(Level a, CrtP 
     const uint32_t q = kNtt.q[c], ni = kNtt.ni[c];
     uint32_t x[G::E];
 #pragma unroll
-    for (int k = 0; k < G::E; ++k) x[k] = src[c * a.ldY + (size_t)G::rowb(r, k) * kRow];
+    for (int k = 0; k < G::E; ++k) {
+      const size_t e = (size_t)G::rowb(r, k) * kRow;
+      x[k] = mmul(src[c * a.ldY + e], a.tw[((size_t)(kNp + c) << a.twLog) + e + col], q, ni);
+    }
     const NttTable T = ntt_reload(tab_Ti(c));
     if constexpr (A <= 4)
       gs_layers<G::E, A, true>(x, q, ni, [&](int, int i) { return T[i]; });
@@ -494,10 +517,12 @@ __global__ void __launch_bounds__(ColGeom<A>::TPB) k_tree_col_inv(Level a, CrtP 
       ntt_inverse<A>(x, r, ColLds<G::C>{sh, cl}, T, q, ni);
 #pragma unroll
     for (int k = K0; k < K1; ++k) u[k - K0][c] = x[k];
+    // one prime's points live at a time: without the fence the loads of all five come first
+    __builtin_amdgcn_sched_barrier(0);
   }
 #pragma unroll
   for (int k = K0; k < K1; ++k)
-    store_point<DST>(a, C.M, j, side, node, G::row(r, k) * kRow + col, ntt_crt(C, u[k - K0]));
+    store_point<DST>(a, y, C.M, j, side, node, G::row(r, k) * kRow + col, ntt_crt(C, u[k - K0]));
 }
 
 // Newton's first 2^9 terms of 1/Q in one workgroup: g <- g (2 - Q g), doubling,
@@ -506,7 +531,8 @@ constexpr uint32_t kBase = 512;
 __global__ void __launch_bounds__(kBase) k_tree_inverse_base(Level a, zr_mod M) {
   __shared__ uint64_t Q[kBase], g[kBase], e[kBase], part[kBase];
   const uint32_t tid = threadIdx.x;
-  Q[tid] = source_point<kRev>(a, M, 0, 0, tid);
+  const TreeSys y = sys_item(a, blockIdx.x);
+  Q[tid] = source_point<kRev>(a, y, M, 0, 0, tid);
   g[tid] = tid == 0 ? 1 % M.p : 0;
   __syncthreads();
   for (uint32_t n = 1; n < kBase; n *= 2) {
@@ -531,7 +557,7 @@ __global__ void __launch_bounds__(kBase) k_tree_inverse_base(Level a, zr_mod M) 
       __syncthreads();
     }
   }
-  a.g[tid] = g[tid];
+  a.g[y.off + tid] = g[tid];
 }
 
 // ---- launches of one level ---------------------------------------------------------------
@@ -539,7 +565,7 @@ __global__ void __launch_bounds__(kBase) k_tree_inverse_base(Level a, zr_mod M) 
 template <int A, int SRC>
 void col_fwd(const Level& a, const zr_mod& M, uint32_t items, uint32_t series, hipStream_t s) {
   using G = ColGeom<A>;
-  hipLaunchKernelGGL((k_tree_col_fwd<A, SRC>), dim3(items * G::tiles, series), dim3(G::TPB), 0, s, a, M);
+  hipLaunchKernelGGL((k_tree_col_fwd<A, SRC>), dim3(items * G::tiles, series, kNp), dim3(G::TPB), 0, s, a, M, kNtt);
 }
 template <int A, int DST>
 void col_inv(const Level& a, const CrtP& C, hipStream_t s) {
@@ -630,62 +656,69 @@ void level_descend(const Level& a, const CrtP& C, hipStream_t s) {
   level_finish<kChildren>(a, C, s);
 }
 
-// a.aux/a.g <- (source SRC) times the kernel in K
+// a.aux or a.g of each of nn systems from item0 <- (source SRC) times the kernel in K
 template <int SRC, int DST>
 void series_product(const Level& a, const CrtP& C, hipStream_t s) {
   if (a.logN > kRowLog) {
-    ZR_COL_CASES(col_fwd, SRC, a, C.M, 1, 1, s)
-    hipLaunchKernelGGL((k_tree_conv<kRowLog, false, SRC>), dim3(1u << (a.logN - kRowLog), kNp), dim3(256), 0, s, a, C, kNtt);
+    ZR_COL_CASES(col_fwd, SRC, a, C.M, a.nn, 1, s)
+    const uint32_t items = a.nn << (a.logN - kRowLog);
+    hipLaunchKernelGGL((k_tree_conv<kRowLog, false, SRC>), dim3(items, kNp), dim3(256), 0, s, a, C, kNtt, items);
   } else if (a.logN == 12) {
-    hipLaunchKernelGGL((k_tree_conv<12, true, SRC>), dim3(1, kNp), dim3(256), 0, s, a, C, kNtt);
+    hipLaunchKernelGGL((k_tree_conv<12, true, SRC>), dim3(a.nn, kNp), dim3(256), 0, s, a, C, kNtt, a.nn);
   } else if (a.logN == 11) {
-    hipLaunchKernelGGL((k_tree_conv<11, true, SRC>), dim3(1, kNp), dim3(256), 0, s, a, C, kNtt);
+    hipLaunchKernelGGL((k_tree_conv<11, true, SRC>), dim3(cdiv(a.nn, kPer<11>), kNp), dim3(256), 0, s, a, C, kNtt, a.nn);
   } else {
-    hipLaunchKernelGGL((k_tree_conv<10, true, SRC>), dim3(1, kNp), dim3(256), 0, s, a, C, kNtt);
+    hipLaunchKernelGGL((k_tree_conv<10, true, SRC>), dim3(cdiv(a.nn, kPer<10>), kNp), dim3(256), 0, s, a, C, kNtt, a.nn);
   }
   level_finish<DST>(a, C, s);
 }
 
-// Power sums p_1..p_t of the rows' monomial values into sums, from M alone:
+// Power sums p_1..p_t of each system's monomial values, from its M alone:
 // sum_i p_i x^(i-1) = -Q'(x)/Q(x), Q the reversed M (Newton's identities), with
-// 1/Q by Newton's iteration.  They are the samples of the right-hand side whose
-// solution is 1 in every row, so that side's value at row l is m_l M'(m_l), the
-// denominator of every other side.
-void power_sums(uint32_t t, const uint64_t* root, uint64_t* sums, uint32_t* X, size_t ldX, uint32_t* Y, size_t ldY,
-                uint32_t* K, size_t ldK, uint64_t* g, const CrtP& C, hipStream_t s) {
-  Level a{};
-  a.t = t;
-  a.nn = 1;
+// 1/Q by Newton's iteration, all systems a step at a time.  They are the samples
+// of the right-hand side whose solution is 1 in every row, so that side's value
+// at row l is m_l M'(m_l), the denominator of every other side.
+void power_sums(const TreeRun& T, Level a, hipStream_t s) {
+  const uint32_t n = (uint32_t)T.sys.size();
   a.R = 1;
-  a.X = X;
-  a.Y = Y;
-  a.K = K;
-  a.ldX = ldX;
-  a.ldY = ldY;
-  a.ldK = ldK;
-  a.root = root;
-  a.g = g;
-  a.aux = sums;
-  hipLaunchKernelGGL(k_tree_inverse_base, dim3(1), dim3(kBase), 0, s, a, C.M);
-  uint32_t lg = 9;
-  for (; (1u << lg) < t; ++lg) {
-    a.logN = lg + 1;
-    a.N = 1u << a.logN;
-    a.h = a.len = 1u << lg;
-    level_kernels<kInverse>(a, C.M, 1, s);
-    series_product<kRev, kHigh>(a, C, s);
-    series_product<kAux, kGrow>(a, C, s);
+  a.K = T.Ks;
+  a.ldK = (size_t)2 * T.V;
+  a.poly = T.poly;
+  a.g = T.g;
+  a.aux = T.sums;
+  a.item0 = 0;
+  a.full = 0;
+  hipLaunchKernelGGL(k_tree_inverse_base, dim3(n), dim3(kBase), 0, s, a, T.C.M);
+  auto at = [&](uint32_t logN, uint32_t i0, uint32_t i1) {
+    a.logN = logN;
+    a.N = 1u << logN;
+    a.h = a.N / 2;
+    a.item0 = i0;
+    a.nn = i1 - i0;
+  };
+  auto tops = [&](uint32_t lg) {  // systems whose top has at least 2^lg rows
+    uint32_t i = 0;
+    while (i < n && T.sys[i].logTop >= lg) ++i;
+    return i;
+  };
+  for (uint32_t lg = 10; lg <= T.sys[0].logTop; ++lg) {
+    at(lg, 0, tops(lg));
+    level_kernels<kInverse>(a, T.C.M, a.nn, s);
+    series_product<kRev, kHigh>(a, T.C, s);
+    series_product<kAux, kGrow>(a, T.C, s);
   }
-  a.logN = lg + 1;
-  a.N = 1u << a.logN;
-  a.h = a.N / 2;
-  a.len = t;
-  level_kernels<kInverse>(a, C.M, 1, s);
-  series_product<kDeriv, kSums>(a, C, s);
+  a.full = 1;
+  for (uint32_t lg = T.sys[0].logTop; lg > kLeafLog; --lg) {
+    at(lg + 1, tops(lg + 1), tops(lg));
+    if (!a.nn) continue;
+    level_kernels<kInverse>(a, T.C.M, a.nn, s);
+    series_product<kDeriv, kSums>(a, T.C, s);
+  }
 }
 
-// Unknowns from which the denominators come from the power sums, one more
-// right-hand side, instead of t^2 steps of the chain pass.
+// Unknowns from which the denominators of one system come from the power sums, one
+// more right-hand side, instead of t^2 steps of the chain pass (t = 33 000: about the
+// same; 100 003: 3.96 against 0.6 ms; 300 007: 34 against 1.1 ms).
 constexpr uint32_t kSumsMinT = 32768;
 
 }  // namespace
@@ -701,85 +734,138 @@ bool tree_applies(uint32_t t, uint32_t R) {
   return t >= 10000 || (t > 4096 && (uint64_t)t * (R + 10) >= 210000);
 }
 
-void tree_solve(const zr_mod& M, uint32_t t, uint32_t R, const uint64_t* mono, const uint64_t* rhs, size_t ld_rhs,
-                uint64_t* out, size_t ld_out, int32_t* status, DevArena& A, hipStream_t s) {
-  uint32_t logTop = kLeafLog;
-  while ((1u << logTop) < t) ++logTop;
-  const uint32_t top = 1u << logTop;
-  CrtP C;
-  C.M = M;
+uint32_t tree_log_top(uint32_t t) {
+  uint32_t lg = kLeafLog;
+  while ((1u << lg) < t) ++lg;
+  return lg;
+}
+
+void tree_prepare(TreeRun& T, const zr_mod& M, uint32_t R, bool sums, DevArena& A, hipStream_t s) {
+  T.C.M = M;
   uint64_t prod = 1 % M.p;
   for (int j = 0; j < kNp; ++j) {
-    C.Qp[j] = prod;
+    T.C.Qp[j] = prod;
     prod = zr_mul(M, prod, kQ[j] % M.p);
   }
-  const bool sums = t >= kSumsMinT;
-  const uint32_t R1 = R + (sums ? 1 : 0);  // series; the power sums are series 0
-  // leaf polynomials by the quadratic product tree, then level by level up:
-  // the children's transforms (kept for the way down) and the parents' polynomials
-  uint64_t* leafM = A.alloc<uint64_t>(t);
-  uint64_t* tmp = A.alloc<uint64_t>(master_tmp_words(t));
-  check(master_levels(M, t, kLeaf, mono, leafM, tmp, s));
-  uint64_t* poly = A.alloc<uint64_t>(t);
-  check(copy_u64(poly, leafM, t, s));
-  std::vector<Level> lv;
-  for (uint32_t k = kLeafLog + 1; k <= logTop; ++k) {
-    Level a{};
-    a.t = t;
-    a.logN = k;
-    a.N = 1u << k;
-    a.h = a.N / 2;
-    a.nn = t / a.N + (t % a.N > a.h ? 1 : 0);
-    a.ldK = (size_t)2 * a.nn * a.N;
-    a.K = A.alloc<uint32_t>(a.ldK * kNp);
-    a.poly = poly;
-    a.pout = poly;
-    lv.push_back(a);
+  T.V = 0;
+  for (TreeSys& y : T.sys) {  // largest tops first: every offset is a multiple of its system's top
+    const uint32_t t = y.end - y.off;
+    y.off = T.V;
+    y.end = T.V + t;
+    y.logTop = tree_log_top(t);
+    T.V += 1u << y.logTop;
   }
+  T.R1 = R + (sums ? 1 : 0);
+  T.leafM = A.alloc<uint64_t>(T.V);
+  T.poly = A.alloc<uint64_t>(T.V);
+  T.sums = sums ? A.alloc<uint64_t>(T.V) : nullptr;
+  T.g = sums ? A.alloc<uint64_t>(T.V) : nullptr;
+  T.Ks = sums ? A.alloc<uint32_t>((size_t)2 * T.V * kNp) : nullptr;
   // residue workspace: groups of series small enough for the last-level cache
-  const size_t per_series = (size_t)kNp * 4 * 3 * top;
-  uint32_t group = (uint32_t)std::max<size_t>(1, std::min<size_t>(R1, (size_t)(160u << 20) / per_series));
-  group = cdiv(R1, cdiv(R1, group));
-  const size_t ldX = (size_t)std::max(2u, group) * top, ldY = (size_t)2 * group * top;
-  uint32_t* X = A.alloc<uint32_t>(ldX * kNp);
-  uint32_t* Y = A.alloc<uint32_t>(ldY * kNp);
+  const size_t per_series = (size_t)kNp * 4 * 3 * T.V;
+  T.group = (uint32_t)std::max<size_t>(1, std::min<size_t>(T.R1, (size_t)(160u << 20) / per_series));
+  T.group = cdiv(T.R1, cdiv(T.R1, T.group));
+  T.ldX = (size_t)std::max(2u, T.group) * T.V;
+  T.ldY = (size_t)2 * T.group * T.V;
+  T.X = A.alloc<uint32_t>(T.ldX * kNp);
+  T.Y = A.alloc<uint32_t>(T.ldY * kNp);
+  T.twLog = T.sys[0].logTop + (sums ? 1 : 0);
+  T.tw = T.twLog > kRowLog ? A.alloc<uint32_t>((size_t)2 * kNp << T.twLog) : nullptr;
+  const uint32_t levels = T.sys[0].logTop - kLeafLog;
+  T.K.clear();
+  for (uint32_t i = 0; i < levels; ++i) T.K.push_back(A.alloc<uint32_t>((size_t)2 * T.V * kNp));
+  T.d_sys = nullptr;
+  T.d_of = nullptr;
+  if (T.sys.size() > 1) {
+    std::vector<uint32_t> of(T.V >> kLeafLog);
+    for (uint32_t i = 0; i < T.sys.size(); ++i)
+      for (uint32_t b = T.sys[i].off >> kLeafLog; b < (T.sys[i].off + (1u << T.sys[i].logTop)) >> kLeafLog; ++b) of[b] = i;
+    Blob blob;
+    const size_t o_sys = blob.add(T.sys), o_of = blob.add(of);
+    char* d = blob.upload(A, s);
+    T.d_sys = (const TreeSys*)(d + o_sys);
+    T.d_of = (const uint32_t*)(d + o_of);
+  }
+}
+
+void tree_launch(const TreeRun& T, hipStream_t s) {
+  const uint32_t lo = kLeafLog + 1, hi = T.sys[0].logTop;
+  auto level = [&](uint32_t lg) {
+    Level a{};
+    a.logN = lg;
+    a.N = 1u << lg;
+    a.h = a.N / 2;
+    a.one = T.sys[0];
+    a.sys = T.d_sys;
+    a.sys_of = T.d_of;
+    a.sums = T.sums;
+    if (T.d_sys) {
+      uint32_t v = 0;
+      for (const TreeSys& y : T.sys)
+        if (y.logTop >= lg) v += 1u << y.logTop;
+      a.nn = v >> lg;
+    } else {
+      const uint32_t t = T.sys[0].end;
+      a.nn = t / a.N + (t % a.N > a.h ? 1 : 0);
+    }
+    a.poly = T.poly;
+    a.pout = T.poly;
+    a.X = T.X;
+    a.Y = T.Y;
+    a.ldX = T.ldX;
+    a.ldY = T.ldY;
+    a.K = lg >= lo ? T.K[lg - lo] : nullptr;
+    a.ldK = (size_t)2 * T.V;
+    a.tw = T.tw;
+    a.twLog = T.twLog;
+    return a;
+  };
+  if (T.tw)
+    hipLaunchKernelGGL(k_tree_twist, dim3(1u << (T.twLog - 8), kNp, 2), dim3(256), 0, s, T.tw, T.twLog, kNtt);
+  check(copy_u64(T.poly, T.leafM, T.V, s));
   {
     TimedLaunch tl("tree_up", s);
-    for (Level& a : lv) {
-      a.X = X;
-      a.Y = Y;
-      a.ldX = ldX;
-      a.ldY = ldY;
-      level_kernels<kChild>(a, M, 2 * a.nn, s);
-      level_product(a, C, s);
+    for (uint32_t lg = lo; lg <= hi; ++lg) {
+      const Level a = level(lg);
+      level_kernels<kChild>(a, T.C.M, 2 * a.nn, s);
+      level_product(a, T.C, s);
     }
   }
-  uint64_t* F = A.alloc<uint64_t>((size_t)R1 * t);
-  uint64_t* ps = nullptr;
-  if (sums) {
+  if (T.sums) {
     TimedLaunch tl("tree_sums", s);
-    ps = A.alloc<uint64_t>(top);
-    uint64_t* g = A.alloc<uint64_t>(top);
-    uint32_t* K = A.alloc<uint32_t>((size_t)2 * top * kNp);
-    power_sums(t, poly, ps, X, ldX, Y, ldY, K, (size_t)2 * top, g, C, s);
+    power_sums(T, level(lo), s);
   }
-  // down: the samples are the root's series
   {
     TimedLaunch tl("tree_down", s);
-    const Src in = sums ? Src{rhs - ld_rhs, ld_rhs, ps, 0} : Src{rhs, ld_rhs, nullptr, ~0u};
-    for (uint32_t j0 = 0; j0 < R1; j0 += group)
-      for (size_t i = lv.size(); i-- > 0;) {
-        Level a = lv[i];
-        a.R = std::min(group, R1 - j0);
-        a.fout = F + (size_t)j0 * t;
-        a.f = i + 1 == lv.size() ? Src{in.p + (size_t)j0 * ld_rhs, ld_rhs, in.px, j0 == 0 ? in.jx : ~0u}
-                                 : Src{F + (size_t)j0 * t, t, nullptr, ~0u};
-        level_descend(a, C, s);
+    for (uint32_t j0 = 0; j0 < T.R1; j0 += T.group)
+      for (uint32_t lg = hi; lg >= lo; --lg) {
+        Level a = level(lg);
+        a.j0 = j0;
+        a.R = std::min(T.group, T.R1 - j0);
+        level_descend(a, T.C, s);
       }
   }
   check(hipGetLastError());
-  uint64_t* work = A.alloc<uint64_t>(vsolve_leaf_words(t, R1, sums));
-  check(vsolve_leaf(M, t, R1, sums, kLeaf, mono, leafM, poly, F, out, ld_out, work, status, s));
+}
+
+void tree_solve(const zr_mod& M, uint32_t t, uint32_t R, const uint64_t* mono, const uint64_t* rhs, size_t ld_rhs,
+                uint64_t* out, size_t ld_out, int32_t* status, DevArena& A, hipStream_t s) {
+  const bool sums = t >= kSumsMinT;
+  TreeRun T;
+  TreeSys y{};
+  y.end = t;
+  y.rhs = rhs;
+  y.ld_rhs = ld_rhs;
+  y.ld = t;
+  y.f = A.alloc<uint64_t>((size_t)(R + (sums ? 1 : 0)) * t);
+  T.sys.push_back(y);
+  tree_prepare(T, M, R, sums, A, s);
+  // leaf polynomials by the quadratic product tree
+  uint64_t* tmp = A.alloc<uint64_t>(master_tmp_words(t));
+  check(master_levels(M, t, kLeaf, mono, T.leafM, tmp, s));
+  tree_launch(T, s);
+  uint64_t* work = A.alloc<uint64_t>(vsolve_leaf_words(t, T.R1, sums));
+  check(vsolve_leaf(M, t, T.R1, sums, kLeaf, mono, T.leafM, T.poly, y.f, out, ld_out, work, status, s));
 }
 
 }  // namespace zr

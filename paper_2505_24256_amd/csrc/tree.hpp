@@ -5,6 +5,7 @@
 
 #include "driver.hpp"
 #include "field.hpp"
+#include "ntt.hpp"
 
 namespace zr {
 
@@ -16,5 +17,43 @@ bool tree_applies(uint32_t t, uint32_t R);
 // launches on s.
 void tree_solve(const zr_mod& M, uint32_t t, uint32_t R, const uint64_t* mono, const uint64_t* rhs, size_t ld_rhs,
                 uint64_t* out, size_t ld_out, int32_t* status, DevArena& A, hipStream_t s);
+
+// ---- many systems through one tree ----------------------------------------------------
+
+constexpr uint32_t kTreeLeafLog = 9;  // leaf blocks of 512 rows
+constexpr uint32_t kTreeLeaf = 1u << kTreeLeafLog;
+
+// One system: rows [off, end) of the common index space (off set by
+// tree_prepare; give off = 0, end = t), right-hand side j at rhs + j ld_rhs, series j
+// of the leaf blocks at f + j ld.
+struct TreeSys {
+  uint32_t off, end, logTop, pad;
+  const uint64_t* rhs;
+  uint64_t* f;
+  size_t ld_rhs, ld;
+};
+
+// log2 of the rows of the top node of t rows
+uint32_t tree_log_top(uint32_t t);
+
+struct TreeRun {
+  CrtP C;
+  std::vector<TreeSys> sys;  // tops in descending order
+  uint32_t V, R1, group;     // rows of the index space; series (the power sums are series 0, if made)
+  uint64_t *leafM, *poly, *sums, *g;
+  uint32_t *X, *Y, *Ks, *tw;
+  uint32_t twLog;
+  size_t ldX, ldY;
+  std::vector<uint32_t*> K;  // children's transforms of each level
+  const TreeSys* d_sys;
+  const uint32_t* d_of;
+};
+
+// Workspace from A and the systems' table (uploaded on s) for R right-hand sides each.
+void tree_prepare(TreeRun& T, const zr_mod& M, uint32_t R, bool sums, DevArena& A, hipStream_t s);
+// From the leaf blocks' polynomials in T.leafM (block b of a system at off + 512 b)
+// and the right-hand sides: the whole polynomials into T.poly and every leaf
+// block's series into f.
+void tree_launch(const TreeRun& T, hipStream_t s);
 
 }  // namespace zr

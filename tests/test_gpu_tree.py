@@ -92,3 +92,37 @@ def test_tree_in_place(zr):
                                          st.data_ptr(), zr._stream(None)) == 0
     torch.cuda.synchronize()
     assert torch.equal(rhs, want)
+
+
+@pytest.mark.parametrize("graphs", [False, True])
+def test_batch_through_one_tree(zr, graphs):
+    """Large systems of a batch share one tree per right-hand-side count, small ones keep
+    their own path; a singular system does not touch the others."""
+    import torch
+    p = PRIMES[0]
+    shapes = [(20_000, 30), (16_385, 30), (9000, 30), (4097, 30), (1600, 30), (1536, 30), (1535, 30), (700, 30),
+              (65, 30), (10, 30), (1, 30), (18_000, 12), (2049, 12), (2048, 12), (5000, 30)]
+    sys_ = [_system(p, t, R, i) for i, (t, R) in enumerate(shapes)]
+    sys_[-1][0][4999] = sys_[-1][0][3]  # the last one is singular
+    so = np.concatenate([[0], np.cumsum([t for t, _ in shapes])]).astype(np.uint64)
+    ro = np.concatenate([[0], np.cumsum([t * R for t, R in shapes])]).astype(np.uint64)
+    nrhs = np.array([R for _, R in shapes], np.uint32)
+    mono = torch.cat([m for m, _ in sys_])
+    rhs = torch.cat([v.reshape(-1) for _, v in sys_])
+    out = torch.full_like(rhs, -1)
+    st = torch.full((len(shapes),), 99, dtype=torch.int32, device="cuda")
+    d_so, d_ro = (torch.from_numpy(a.view(np.int64)).cuda() for a in (so, ro))
+    zr.solve_variant()
+    zr.batch_graphs(graphs)
+    try:
+        for _ in range(2):
+            assert zr.lib().vandermonde_solve_batch(
+                len(shapes), p, d_so.data_ptr(), so.ctypes.data, mono.data_ptr(), nrhs.ctypes.data, d_ro.data_ptr(),
+                ro.ctypes.data, rhs.data_ptr(), out.data_ptr(), st.data_ptr(), zr._stream(None)) == 0
+            torch.cuda.synchronize()
+    finally:
+        zr.batch_graphs(False)
+    assert st.cpu().tolist() == [0] * (len(shapes) - 1) + [zr.ZR_ESINGULAR]
+    for i, (t, R) in enumerate(shapes[:-1]):
+        want, _ = _solve(zr, p, *sys_[i], "waves")
+        assert torch.equal(out[int(ro[i]):int(ro[i + 1])].reshape(R, t), want), (t, R)
