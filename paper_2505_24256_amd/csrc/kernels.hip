@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "../../include/zippel.h"
+#include "driver.hpp"
 #include "field.hpp"
 #include "kernels.hpp"
 #include "kernels_dev.hpp"
@@ -126,11 +127,34 @@ static bool plan_uneven(const VsolvePlan& P) {
   return u;
 }
 
+// Systems of at most this many unknowns take the staged form of the
+// producer/consumer pass, whatever R: they are paced by one workgroup's latency per
+// step, so their chunks are cut to two (three, with few values per consumer) workgroups per CU.
+// Whole solve, microseconds, scalar rows (or one wave per tile at R <= 10) against
+// staged: t = 961: R = 1 143/107, R = 30 146/115; t = 2000: R = 10 192/141, R = 30
+// 159/160, R = 60 194/203; t = 3000: R = 1 185/173, R = 30 244/233; t = 4000: R = 1 182/194,
+// R = 60 422/425.
+constexpr uint32_t kLdsMaxT = 3072;
+
 VsolvePlan vsolve_plan(uint32_t t, uint32_t R, uint32_t num_cus) {
-  VsolvePlan P;
+  VsolvePlan P{};
   P.t = t;
   P.R = R;
   const uint32_t row_blocks = std::max<uint32_t>(1, cdiv(t, 64));
+  if (dots_pc_enabled() && t <= kLdsMaxT && R > 0) {
+    P.lds = P.pc = 1;
+    P.ng = cdiv(R, kPcMaxR);
+    P.Rg = cdiv(R, P.ng);
+    P.ntile = P.Rg <= 3 ? 3 : kPcMaxTiles;
+    P.RT = cdiv(P.Rg, P.ntile);
+    P.ldv = pc_ldv(P.RT);
+    for (uint32_t k = 0; k < P.ntile; ++k) P.tw[k] = P.RT;
+    P.vt32 = (size_t)P.ntile * P.ldv * t;
+    const uint32_t S = std::max<uint32_t>(1, std::min((P.RT <= 3 ? 3 : 2) * num_cus / row_blocks, t / 64));
+    P.L = std::max<uint32_t>(1, cdiv(t, S));
+    P.S = P.Sd = std::max<uint32_t>(1, cdiv(t, P.L));
+    return P;
+  }
   // Above kPcMinR right-hand sides the chain runs once per row block in a
   // producer wave (k_vs_dots_pc) and consumer waves take tiles of at most
   // kPcRT; the unit of the launch is then a workgroup of 1 + ntile waves, a
@@ -312,6 +336,23 @@ __global__ void __launch_bounds__(64 * (1 + kPcMaxTiles)) k_vs_dots_pc(VsArgs a,
   vs_dots_pc_body<RT, HORNER, UNEVEN>(a, blockIdx.x, c0 + blockIdx.y, ntile, qbuf);
 }
 
+// the same with the consumers' rows staged through LDS (seven tiles at most, all of
+// RT), over chunks (with the Horner sum) or over the leaf blocks of a tree
+template <int RT, bool LEAF>
+__global__ void __launch_bounds__(64 * (1 + kPcMaxTiles)) k_vs_dots_pc_lds(VsArgs a, uint32_t ntile, uint32_t c0) {
+  __shared__ uint64_t qbuf[2][kQB][64];
+  __shared__ __align__(16) uint32_t rowbuf[kPcMaxTiles * 2 * kQB * pc_ldv(RT)];
+  vs_dots_pc_body<RT, !LEAF, false, true, LEAF>(a, blockIdx.x, c0 + blockIdx.y, ntile, qbuf, rowbuf);
+}
+
+// leaf blocks of a tree: four waves per SIMD (nine values would take one register too many)
+template <int RT, bool UNEVEN>
+__global__ void __launch_bounds__(64 * (1 + kPcMaxTiles), RT < 10 ? 4 : 3)
+    k_vs_dots_leaf(VsArgs a, uint32_t ntile, uint32_t c0) {
+  __shared__ uint64_t qbuf[2][kQB][64];
+  vs_dots_pc_body<RT, false, UNEVEN, false, true>(a, blockIdx.x, c0 + blockIdx.y, ntile, qbuf);
+}
+
 __global__ void __launch_bounds__(kDeltaBlock) k_vs_delta(VsArgs a, const uint64_t* __restrict__ mLv,
                                                            uint64_t* __restrict__ winv, int32_t* __restrict__ status) {
   __shared__ uint64_t sh[kDeltaBlock / 64 + 1];
@@ -356,6 +397,24 @@ static DotsPcKernel dots_pc_pick(uint32_t RT) {
 static DotsPcKernel dots_pc_kernel(uint32_t RT, bool horner = true, bool uneven = false) {
   return horner ? (uneven ? dots_pc_pick<true, true>(RT) : dots_pc_pick<true, false>(RT))
                 : (uneven ? dots_pc_pick<false, true>(RT) : dots_pc_pick<false, false>(RT));
+}
+
+// the staged pass (leaf: over the leaf blocks of a tree)
+template <bool LEAF>
+static DotsPcKernel dots_pc_lds_pick(uint32_t RT) {
+  static const DotsPcKernel table[kPcRT] = {
+      nullptr,                   k_vs_dots_pc_lds<1, LEAF>, k_vs_dots_pc_lds<2, LEAF>, k_vs_dots_pc_lds<3, LEAF>,
+      k_vs_dots_pc_lds<4, LEAF>, k_vs_dots_pc_lds<5, LEAF>, k_vs_dots_pc_lds<6, LEAF>, k_vs_dots_pc_lds<7, LEAF>,
+      k_vs_dots_pc_lds<8, LEAF>, k_vs_dots_pc_lds<9, LEAF>};
+  return RT >= 1 && RT < kPcRT ? table[RT] : nullptr;
+}
+template <bool U>
+static DotsPcKernel dots_leaf_pick(uint32_t RT) {
+  static const DotsPcKernel table[kPcRT + 1] = {
+      nullptr,              k_vs_dots_leaf<1, U>, k_vs_dots_leaf<2, U>, k_vs_dots_leaf<3, U>,
+      k_vs_dots_leaf<4, U>, k_vs_dots_leaf<5, U>, k_vs_dots_leaf<6, U>, k_vs_dots_leaf<7, U>,
+      k_vs_dots_leaf<8, U>, k_vs_dots_leaf<9, U>, k_vs_dots_leaf<10, U>};
+  return RT >= 1 && RT <= kPcRT ? table[RT] : nullptr;
 }
 
 // Workgroups of the producer/consumer pass resident per CU for ntile tiles
@@ -455,7 +514,8 @@ hipError_t vsolve(const zr_mod& M, const VsolvePlan& P, const uint64_t* mono, co
       }
     }
     if (P.pc) {
-      DotsPcKernel kp = dots_pc_kernel(P.RT, !P.dchain, plan_uneven(P));
+      DotsPcKernel kp =
+          P.lds ? dots_pc_lds_pick<false>(P.RT) : dots_pc_kernel(P.RT, !P.dchain, plan_uneven(P));
       if (!kp) return hipErrorInvalidValue;
       // chunks in launches of Sd (one partial-sum slot each), in order
       for (uint32_t c0 = 0; c0 < P.S; c0 += P.Sd) {
@@ -509,11 +569,16 @@ LeafPlan leaf_plan(uint32_t t, uint32_t R, bool sums) {
   P.Rg = cdiv(R, P.ng);
   P.pc = 1;
   P.ntile = pc_tiles_for(P.Rg);
+  // one workgroup per CU or less: rows staged, seven tiles (t = 9 997, R = 30: 86 -> 51 us)
+  P.lds = cdiv(t, 64) <= device_cus() ? 1 : 0;
+  if (P.lds) P.ntile = kPcMaxTiles;
   P.RT = cdiv(P.Rg, P.ntile);
   P.dchain = 1;
   P.S = P.Sd = 1;
   P.L = t;
   pc_widths(P.Rg, P.ntile, P.RT, true, P.tw);
+  if (P.lds)
+    for (uint32_t k = 0; k < P.ntile; ++k) P.tw[k] = P.RT;
   if (plan_uneven(P) && dots_pc_blocks_per_cu(P.RT, P.ntile, true) < dots_pc_blocks_per_cu(P.RT, P.ntile, false))
     for (uint32_t k = 0; k < P.ntile; ++k) P.tw[k] = P.RT;
   for (uint32_t k = 0; k < P.ntile; ++k) q.words += pc_ldv(P.tw[k]);
@@ -575,7 +640,9 @@ hipError_t vsolve_leaf(const zr_mod& M, uint32_t t, uint32_t R1, bool sums, uint
   a.blk = block;
   uint32_t wmax = 0;
   for (uint32_t k = 0; k < P.ntile; ++k) wmax = std::max(wmax, P.tw[k]);
-  DotsPcKernel kp = dots_pc_kernel(P.RT, false, plan_uneven(P));
+  DotsPcKernel kp = P.lds            ? dots_pc_lds_pick<true>(P.RT)
+                    : plan_uneven(P) ? dots_leaf_pick<true>(P.RT)
+                                     : dots_leaf_pick<false>(P.RT);
   if (!kp) return hipErrorInvalidValue;
   for (uint32_t g = 0, r0 = 0; g < P.ng; ++g) {
     const uint32_t Rg = R1 / P.ng + (g < R1 % P.ng ? 1 : 0);

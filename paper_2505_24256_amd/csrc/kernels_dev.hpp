@@ -38,7 +38,7 @@ struct VsArgs {
   // producer/consumer pass: right-hand sides of consumer k's tile; tile k's
   // rows (pc_ldv(tw[k]) words each) follow those of the tiles before it
   uint8_t tw[8] = {};
-  // leaf blocks of the subproduct tree (0: one system): rows [B u, B (u+1)) are
+  // leaf blocks of the subproduct tree: rows [B u, B (u+1)) are
   // a system of their own, with master polynomial and samples at those indices
   uint32_t blk = 0;
   // 1: series 0 are the power sums of the whole tree's system, so its values are the
@@ -586,13 +586,98 @@ __device__ __forceinline__ void vs_pc_consume(const VsArgs& a, uint32_t c, uint3
 }
 
 
+// The same consumer with its rows staged through LDS, for launches that leave the
+// chip mostly empty.  Scalar loads return in no order, so the consumer above can
+// have only the next step's row in flight, and with one workgroup on a CU every
+// step lasts a scalar load's way to the L2 and back (about 800 cycles, whatever RT). Here
+// each block of kQB rows is one coalesced vector load, requested while the block
+// before is multiplied, and read back from LDS (broadcast, in order, so several steps
+// ahead).  rowbuf: the wave's 2 x kQB rows.
+template <int RT>
+__device__ __forceinline__ void vs_pc_consume_lds(const VsArgs& a, uint32_t c, uint32_t lo, uint32_t hi, uint32_t nb,
+                                                  bool live, uint32_t l, uint32_t lane, uint32_t j0,
+                                                  const uint32_t* __restrict__ rows, uint64_t (*qbuf)[kQB][64],
+                                                  uint32_t* rowbuf, const zr_mod& M) {
+  constexpr uint32_t LDV = pc_ldv(RT), W = kQB * LDV, NV = (3 * RT + 3) / 4;
+  constexpr int PER = (W + 127) / 128;  // 8-byte words per lane and block
+  Acc6 acc[RT];
+#pragma unroll
+  for (int j = 0; j < RT; ++j) acc6_zero(acc[j]);
+  uint32_t since = 0;
+  uint2 st[PER];
+  // rows [top - kQB, top) of block b, top = hi - kQB b, those below lo left out
+  auto fetch = [&](uint32_t b) {
+    const uint32_t top = hi - b * kQB, first = top > lo + kQB ? top - kQB : lo;
+    const uint32_t skip = (kQB - (top - first)) * LDV;  // a short block ends at the buffer's end
+    const uint32_t* src = rows + (size_t)first * LDV;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const uint32_t w = 2 * (lane + 64 * k);
+      st[k] = w >= skip && w < W ? *(const uint2*)(src + (w - skip)) : make_uint2(0, 0);
+    }
+  };
+  auto put = [&](uint32_t b) {
+    uint32_t* dst = rowbuf + (b & 1) * W;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const uint32_t w = 2 * (lane + 64 * k);
+      if (w < W) *(uint2*)(dst + w) = st[k];
+    }
+  };
+  fetch(0);
+  for (uint32_t it = 0; it <= nb; ++it) {
+    if (it >= 1 && it < nb) fetch(it);
+    if (it >= 1) {
+      const uint32_t b = it - 1;
+      const uint32_t s_end = min(kQB, hi - lo - b * kQB);
+      const uint64_t* qb = &qbuf[b & 1][0][lane];
+      const uint32_t* rb = rowbuf + (b & 1) * W + (kQB - 1) * LDV;  // step s: row kQB - 1 - s
+#pragma unroll 4
+      for (uint32_t s = 0; s < s_end; ++s) {
+        const uint64_t q = qb[64 * s];
+        const uint32_t q0 = (uint32_t)q, q1 = (uint32_t)(q >> 32);
+        uint32_t v[4 * NV];
+#pragma unroll
+        for (uint32_t k = 0; k < 2 * NV; ++k) {
+          const uint2 x = *(const uint2*)(rb - s * LDV + 2 * k);
+          v[2 * k] = x.x;
+          v[2 * k + 1] = x.y;
+        }
+#pragma unroll
+        for (int jj = 0; jj < RT; ++jj) acc6_mac(acc[jj], q0, q1, v[3 * jj], v[3 * jj + 1], v[3 * jj + 2]);
+      }
+      since += s_end;
+      if (since + kQB > kFold) {
+#pragma unroll
+        for (int j = 0; j < RT; ++j) acc6_fold(acc[j], M);
+        since = 0;
+      }
+    }
+    if (it < nb) put(it);
+    __syncthreads();
+  }
+  if (live) {
+    const uint32_t slot = c % a.Sd;
+#pragma unroll
+    for (int j = 0; j < RT; ++j)
+      if (j0 + j < a.R) {
+        uint64_t* dst = a.spart + ((size_t)slot * a.R + j0 + j) * a.t + l;
+        const uint64_t v = acc6_reduce(M, acc[j]);
+        *dst = c >= a.Sd ? zr_add(M, v, *dst) : v;
+      }
+  }
+}
+
 // HORNER: the producer also sums h = q(m) over the chunk into hpart (the
 // batched solve); without it delta comes from the chain pass's D_c.  UNEVEN:
 // tiles may be one value narrower or wider than RT (the bodies for those
 // widths are compiled in, which costs registers; off, every tile is RT wide).
-template <int RT, bool HORNER, bool UNEVEN = false>
+// STAGED: consumers with rows in LDS (rowbuf, 2 kQB rows per tile).  LEAF: leaf blocks
+// of a tree (a.blk) in place of chunks, a constant of the kernel because the chunked one
+// at nine values has no register to spare.
+template <int RT, bool HORNER, bool UNEVEN = false, bool STAGED = false, bool LEAF = false>
 __device__ __forceinline__ void vs_dots_pc_body(const VsArgs& a, uint32_t rb, uint32_t c, uint32_t ntile,
-                                                uint64_t (*qbuf)[kQB][64]) {
+                                                uint64_t (*qbuf)[kQB][64], uint32_t* rowbuf = nullptr) {
   // the wave index is uniform within a wave: say so, so that each role's code
   // is compiled as uniform control flow (scalar loads, scalar loop counters)
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -600,7 +685,7 @@ __device__ __forceinline__ void vs_dots_pc_body(const VsArgs& a, uint32_t rb, ui
   const bool live = l0 < a.t;
   const uint32_t l = live ? l0 : a.t - 1;
   uint32_t lo, hi;
-  if (a.blk) {
+  if constexpr (LEAF) {
     lo = rb * 64 / a.blk * a.blk;  // the block of the workgroup's rows
     hi = min(a.t, lo + a.blk);
   } else {
@@ -669,6 +754,11 @@ __device__ __forceinline__ void vs_dots_pc_body(const VsArgs& a, uint32_t rb, ui
       off += pc_ldv(a.tw[k]);
     }
     if (k == tile) w = a.tw[k];
+  }
+  if constexpr (STAGED) {
+    vs_pc_consume_lds<RT>(a, c, lo, hi, nb, live, l, lane, j0, (const uint32_t*)a.VT + (size_t)off * a.t, qbuf,
+                          rowbuf + (size_t)tile * 2 * kQB * pc_ldv(RT), M);
+    return;
   }
   const_as<uint32_t> rows = (const_as<uint32_t>)((const uint32_t*)a.VT + (size_t)off * a.t);
   if constexpr (UNEVEN && RT > 1) {

@@ -21,10 +21,10 @@
 // both evaluate the same polynomial identities exactly.
 //
 // Whole solve, quadratic against tree, one MI355X: t = 9 997, R = 30: 1.07 ->
-// 0.50 ms; t = 100 003, R = 17: 49.6 -> 1.80 ms; t = 300 007, R = 40: 781 -> 10.0 ms
-// (rows 3.9 ms, bound by integer issue; columns and Chinese remainder 3.0 ms, by the
-// residues' traffic; the leaves' dot products 1.9 ms).  256 uneven systems of 10 to
-// 20 000 unknowns, R = 30, the large ones through one tree: 52.0 -> 10.5 ms.
+// 0.41 ms; t = 100 003, R = 17: 49.6 -> 1.68 ms; t = 300 007, R = 40: 781 -> 8.6 ms
+// (rows 4.1 ms, bound by integer issue; columns and Chinese remainder 2.5 ms, by the
+// residues' traffic; the leaves' dot products 1.1 ms).  256 uneven systems of 10 to
+// 20 000 unknowns, R = 30, the large ones through one tree: 52.0 -> 9.3 ms.
 //
 // A node of 2^k rows uses cyclic products of length N = 2^k: sums over i + k <= n
 // do not wrap for the coefficients wanted, the upper half of the product of the
@@ -37,6 +37,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "batch.hpp"
 #include "driver.hpp"
@@ -54,7 +55,8 @@ constexpr int kRowLog = 12;                  // longest transform of one workgro
 constexpr uint32_t kRow = 1u << kRowLog;
 constexpr uint32_t kLeafLog = kTreeLeafLog;
 constexpr uint32_t kLeaf = kTreeLeaf;
-static_assert(kLeafLog + 1 >= 10, "the shortest row transform has 2^10 points");
+constexpr int kRowMin = 9;  // shortest transform of the rows: half a wave
+static_assert(kLeafLog + 1 >= kRowMin, "");
 
 // T[i], 1/T[i], and the powers w^e of the root of order 2^22 in two digits of
 // 11 bits (P0: e = 0..2047, P1: e = 2048 i), in Montgomery form.
@@ -155,7 +157,12 @@ struct Level {
   uint32_t full;  // kInverse: all t terms (else the first h)
 };
 
-// row is the same for all lanes of a wave
+template <uint32_t NT>  // threads of a transform: at least a wave, or half of one
+__device__ __forceinline__ uint32_t wave_uniform(uint32_t x) {
+  return NT >= 64 ? __builtin_amdgcn_readfirstlane(x) : x;
+}
+// the row's system is the same for all lanes of a wave (two nodes of 512 rows that
+// share one lie in one node of 1024)
 __device__ __forceinline__ TreeSys sys_at(const Level& a, uint32_t row) {
   return a.sys ? a.sys[a.sys_of[__builtin_amdgcn_readfirstlane(row) >> kLeafLog]] : a.one;
 }
@@ -272,7 +279,7 @@ template <int LOGN, bool DIRECT, int SRC>
 __global__ void __launch_bounds__(256) k_tree_kernels(Level a, NttMods mods, uint32_t items) {
   constexpr uint32_t NT = 1u << (LOGN - 4), PER = 256 / NT;
   __shared__ __align__(16) uint32_t sh[PER * kRowWords<LOGN>];
-  const uint32_t sub = __builtin_amdgcn_readfirstlane(threadIdx.x / NT), r = threadIdx.x % NT, c = blockIdx.y;
+  const uint32_t sub = wave_uniform<NT>(threadIdx.x / NT), r = threadIdx.x % NT, c = blockIdx.y;
   const uint32_t it0 = blockIdx.x * PER + sub;
   const bool live = it0 < items;
   const uint32_t it = live ? it0 : items - 1;
@@ -306,7 +313,7 @@ template <int LOGN, bool DIRECT>
 __global__ void __launch_bounds__(256) k_tree_product(Level a, NttMods mods, uint32_t items) {
   constexpr uint32_t NT = 1u << (LOGN - 4), PER = 256 / NT;
   __shared__ __align__(16) uint32_t sh[PER * kRowWords<LOGN>];
-  const uint32_t sub = __builtin_amdgcn_readfirstlane(threadIdx.x / NT), r = threadIdx.x % NT, c = blockIdx.y;
+  const uint32_t sub = wave_uniform<NT>(threadIdx.x / NT), r = threadIdx.x % NT, c = blockIdx.y;
   const uint32_t it0 = blockIdx.x * PER + sub;
   const bool live = it0 < items;
   const uint32_t it = live ? it0 : items - 1;
@@ -337,10 +344,10 @@ __global__ void __launch_bounds__(256) k_tree_product(Level a, NttMods mods, uin
 // spills: 90 -> 42 us for 5 series of 3*10^5 rows, about 35 at full issue.  blockIdx.y =
 // prime, blockIdx.z = group of `per` series.
 template <int LOGN, bool DIRECT>
-__global__ void __launch_bounds__(256, 4) k_tree_descend(Level a, NttMods mods, uint32_t items, uint32_t per) {
+__global__ void __launch_bounds__(256, 3) k_tree_descend(Level a, NttMods mods, uint32_t items, uint32_t per) {
   constexpr uint32_t NT = 1u << (LOGN - 4), PER = 256 / NT;
   __shared__ __align__(16) uint32_t sh[PER * kRowWords<LOGN>];
-  const uint32_t sub = __builtin_amdgcn_readfirstlane(threadIdx.x / NT), r = threadIdx.x % NT, c = blockIdx.y;
+  const uint32_t sub = wave_uniform<NT>(threadIdx.x / NT), r = threadIdx.x % NT, c = blockIdx.y;
   const uint32_t it0 = blockIdx.x * PER + sub;
   const uint32_t it = std::min(it0, items - 1);
   const RowK m = row_mod(mods, c);
@@ -395,7 +402,7 @@ template <int LOGN, bool DIRECT, int SRC>
 __global__ void __launch_bounds__(256) k_tree_conv(Level a, CrtP C, NttMods mods, uint32_t items) {
   constexpr uint32_t NT = 1u << (LOGN - 4), PER = 256 / NT;
   __shared__ __align__(16) uint32_t sh[PER * kRowWords<LOGN>];
-  const uint32_t sub = __builtin_amdgcn_readfirstlane(threadIdx.x / NT), r = threadIdx.x % NT, c = blockIdx.y;
+  const uint32_t sub = wave_uniform<NT>(threadIdx.x / NT), r = threadIdx.x % NT, c = blockIdx.y;
   const uint32_t it0 = blockIdx.x * PER + sub;
   const bool live = it0 < items;
   const uint32_t it = live ? it0 : items - 1;
@@ -591,6 +598,18 @@ void col_inv(const Level& a, const CrtP& C, hipStream_t s) {
 template <int LOGN>
 constexpr uint32_t kPer = 256u >> (LOGN - 4);  // transforms per workgroup
 
+// f(length) with the transform's log2 length as a constant
+template <class F>
+void for_row_log(uint32_t logN, const F& f) {
+  switch (logN) {
+    case 9: f(std::integral_constant<int, 9>()); break;
+    case 10: f(std::integral_constant<int, 10>()); break;
+    case 11: f(std::integral_constant<int, 11>()); break;
+    case 12: f(std::integral_constant<int, 12>()); break;
+    default: throw Error(ZR_EINVAL);
+  }
+}
+
 // transforms of `items` polynomials into K
 template <int SRC>
 void level_kernels(const Level& a, const zr_mod& M, uint32_t nc, hipStream_t s) {
@@ -598,12 +617,10 @@ void level_kernels(const Level& a, const zr_mod& M, uint32_t nc, hipStream_t s) 
     ZR_COL_CASES(col_fwd, SRC, a, M, nc, 1, s)
     const uint32_t items = nc << (a.logN - kRowLog);
     hipLaunchKernelGGL((k_tree_kernels<kRowLog, false, SRC>), dim3(items, kNp), dim3(256), 0, s, a, kNtt, items);
-  } else if (a.logN == 12) {
-    hipLaunchKernelGGL((k_tree_kernels<12, true, SRC>), dim3(nc, kNp), dim3(256), 0, s, a, kNtt, nc);
-  } else if (a.logN == 11) {
-    hipLaunchKernelGGL((k_tree_kernels<11, true, SRC>), dim3(cdiv(nc, kPer<11>), kNp), dim3(256), 0, s, a, kNtt, nc);
   } else {
-    hipLaunchKernelGGL((k_tree_kernels<10, true, SRC>), dim3(cdiv(nc, kPer<10>), kNp), dim3(256), 0, s, a, kNtt, nc);
+    for_row_log(a.logN, [&](auto L) {
+      hipLaunchKernelGGL((k_tree_kernels<L, true, SRC>), dim3(cdiv(nc, kPer<L>), kNp), dim3(256), 0, s, a, kNtt, nc);
+    });
   }
 }
 
@@ -622,12 +639,10 @@ void level_product(const Level& a, const CrtP& C, hipStream_t s) {
   if (a.logN > kRowLog) {
     const uint32_t items = a.nn << (a.logN - kRowLog);
     hipLaunchKernelGGL((k_tree_product<kRowLog, false>), dim3(items, kNp), dim3(256), 0, s, a, kNtt, items);
-  } else if (a.logN == 12) {
-    hipLaunchKernelGGL((k_tree_product<12, true>), dim3(a.nn, kNp), dim3(256), 0, s, a, kNtt, a.nn);
-  } else if (a.logN == 11) {
-    hipLaunchKernelGGL((k_tree_product<11, true>), dim3(cdiv(a.nn, kPer<11>), kNp), dim3(256), 0, s, a, kNtt, a.nn);
   } else {
-    hipLaunchKernelGGL((k_tree_product<10, true>), dim3(cdiv(a.nn, kPer<10>), kNp), dim3(256), 0, s, a, kNtt, a.nn);
+    for_row_log(a.logN, [&](auto L) {
+      hipLaunchKernelGGL((k_tree_product<L, true>), dim3(cdiv(a.nn, kPer<L>), kNp), dim3(256), 0, s, a, kNtt, a.nn);
+    });
   }
   level_finish<kParent>(a, C, s);
 }
@@ -646,12 +661,10 @@ void level_descend(const Level& a, const CrtP& C, hipStream_t s) {
     hipLaunchKernelGGL((k_tree_descend<kRowLog, false>), dim3(items, kNp, cdiv(a.R, per)), dim3(256), 0, s, a, kNtt, items,
                        per);
   } else {
-    const uint32_t g = a.logN == 12 ? a.nn : a.logN == 11 ? cdiv(a.nn, kPer<11>) : cdiv(a.nn, kPer<10>);
-    const uint32_t per = descend_per(g, a.R);
-    const dim3 grid(g, kNp, cdiv(a.R, per));
-    if (a.logN == 12) hipLaunchKernelGGL((k_tree_descend<12, true>), grid, dim3(256), 0, s, a, kNtt, a.nn, per);
-    else if (a.logN == 11) hipLaunchKernelGGL((k_tree_descend<11, true>), grid, dim3(256), 0, s, a, kNtt, a.nn, per);
-    else hipLaunchKernelGGL((k_tree_descend<10, true>), grid, dim3(256), 0, s, a, kNtt, a.nn, per);
+    for_row_log(a.logN, [&](auto L) {
+      const uint32_t g = cdiv(a.nn, kPer<L>), per = descend_per(g, a.R);
+      hipLaunchKernelGGL((k_tree_descend<L, true>), dim3(g, kNp, cdiv(a.R, per)), dim3(256), 0, s, a, kNtt, a.nn, per);
+    });
   }
   level_finish<kChildren>(a, C, s);
 }
@@ -663,12 +676,10 @@ void series_product(const Level& a, const CrtP& C, hipStream_t s) {
     ZR_COL_CASES(col_fwd, SRC, a, C.M, a.nn, 1, s)
     const uint32_t items = a.nn << (a.logN - kRowLog);
     hipLaunchKernelGGL((k_tree_conv<kRowLog, false, SRC>), dim3(items, kNp), dim3(256), 0, s, a, C, kNtt, items);
-  } else if (a.logN == 12) {
-    hipLaunchKernelGGL((k_tree_conv<12, true, SRC>), dim3(a.nn, kNp), dim3(256), 0, s, a, C, kNtt, a.nn);
-  } else if (a.logN == 11) {
-    hipLaunchKernelGGL((k_tree_conv<11, true, SRC>), dim3(cdiv(a.nn, kPer<11>), kNp), dim3(256), 0, s, a, C, kNtt, a.nn);
   } else {
-    hipLaunchKernelGGL((k_tree_conv<10, true, SRC>), dim3(cdiv(a.nn, kPer<10>), kNp), dim3(256), 0, s, a, C, kNtt, a.nn);
+    for_row_log(a.logN, [&](auto L) {
+      hipLaunchKernelGGL((k_tree_conv<L, true, SRC>), dim3(cdiv(a.nn, kPer<L>), kNp), dim3(256), 0, s, a, C, kNtt, a.nn);
+    });
   }
   level_finish<DST>(a, C, s);
 }
@@ -723,15 +734,16 @@ constexpr uint32_t kSumsMinT = 32768;
 
 }  // namespace
 
-// The tree pays from about 10^4 unknowns whatever R, and below that where the
-// right-hand sides are many enough for its launches (about 40 of 4 to 10 us).
-// Quadratic against tree, microseconds: t = 4500: R = 30 397/415, R = 40 465/432; t = 5500: R = 10 383/407,
-// R = 30 497/430; t = 9000: R = 1 435/459, R = 10 665/476; t = 13 000: R = 1
-// 629/510, R = 30 1580/617.  Up to 2^21 unknowns: the power sums' last
-// transform then has 2^22 points, the primes' limit.
+// The tree pays from about 5500 unknowns whatever R, and below that where the
+// right-hand sides are many enough for its launches (about 45 of 4 to 10 us).
+// Quadratic against tree, microseconds: t = 3000: R = 30 237/228, R = 40 249/239, R = 60 312/281;
+// t = 3500: R = 5 218/218, R = 10 239/217, R = 30 272/233; t = 4500: R = 1 228/251, R = 10
+// 298/267; t = 5500: R = 1 259/262, R = 10 365/272; t = 8000: R = 1 317/275, R = 30
+// 704/339; t = 13 000: R = 1 610/360, R = 30 1568/464.  Up to 2^21 unknowns: the power
+// sums' last transform then has 2^22 points, the primes' limit.
 bool tree_applies(uint32_t t, uint32_t R) {
   if (!vsolve_uses_pc() || R == 0 || t > (1u << (kNttMaxLog - 1))) return false;
-  return t >= 10000 || (t > 4096 && (uint64_t)t * (R + 10) >= 210000);
+  return t >= 5500 || (t > 3072 && R >= 8) || (t > 2560 && R > 36);
 }
 
 uint32_t tree_log_top(uint32_t t) {
@@ -761,9 +773,11 @@ void tree_prepare(TreeRun& T, const zr_mod& M, uint32_t R, bool sums, DevArena& 
   T.sums = sums ? A.alloc<uint64_t>(T.V) : nullptr;
   T.g = sums ? A.alloc<uint64_t>(T.V) : nullptr;
   T.Ks = sums ? A.alloc<uint32_t>((size_t)2 * T.V * kNp) : nullptr;
-  // residue workspace: groups of series small enough for the last-level cache
+  // residue workspace: series in groups of at most 640 MB (t = 300 007, 41 series: 9.8 ms with
+  // 160 MB, which the last-level cache holds, 8.8 with 640, 9.0 with all at once: the
+  // launches' fill matters more)
   const size_t per_series = (size_t)kNp * 4 * 3 * T.V;
-  T.group = (uint32_t)std::max<size_t>(1, std::min<size_t>(T.R1, (size_t)(160u << 20) / per_series));
+  T.group = (uint32_t)std::max<size_t>(1, std::min<size_t>(T.R1, ((size_t)640 << 20) / per_series));
   T.group = cdiv(T.R1, cdiv(T.R1, T.group));
   T.ldX = (size_t)std::max(2u, T.group) * T.V;
   T.ldY = (size_t)2 * T.group * T.V;

@@ -20,7 +20,7 @@ void tree_solve(const zr_mod& M, uint32_t t, uint32_t R, const uint64_t* mono, c
 
 // ---- many systems through one tree ----------------------------------------------------
 
-constexpr uint32_t kTreeLeafLog = 9;  // leaf blocks of 512 rows
+constexpr uint32_t kTreeLeafLog = 8;  // leaf blocks of 256 rows
 constexpr uint32_t kTreeLeaf = 1u << kTreeLeafLog;
 
 // One system: rows [off, end) of the common index space (off set by
@@ -51,7 +51,7 @@ struct TreeRun {
 
 // Workspace from A and the systems' table (uploaded on s) for R right-hand sides each.
 void tree_prepare(TreeRun& T, const zr_mod& M, uint32_t R, bool sums, DevArena& A, hipStream_t s);
-// From the leaf blocks' polynomials in T.leafM (block b of a system at off + 512 b)
+// From the leaf blocks' polynomials in T.leafM (block b of a system at off + 256 b)
 // and the right-hand sides: the whole polynomials into T.poly and every leaf
 // block's series into f.
 void tree_launch(const TreeRun& T, hipStream_t s);

@@ -1,6 +1,6 @@
 """GPU parity of the subproduct-tree solve against the quadratic pass (one wave
 per tile), bit for bit, through zr_vandermonde_solve: sizes on both sides of the
-leaf blocks (512 rows), the levels (powers of two), the transforms of one
+leaf blocks (256 rows), the levels (powers of two), the transforms of one
 workgroup (4096 points) and of the sizes where the denominators come from power sums
 (32 768), right-hand sides from one to more than one group, primes from 65 537
 to 2^63 - 25, and singular systems.  Tolerance 0: both compute the same residues."""
@@ -49,7 +49,7 @@ def _system(p, t, R, seed):
     return mono, rhs
 
 
-@pytest.mark.parametrize("t,R", [(4097, 48), (4608, 46), (4609, 60), (8191, 20), (8192, 16), (8193, 16), (9997, 30),
+@pytest.mark.parametrize("t,R", [(2561, 37), (3073, 8), (3329, 9), (4097, 48), (4608, 46), (4609, 60), (8191, 20), (8192, 16), (8193, 16), (9997, 30),
                                  (10_000, 1), (12_289, 2), (16_384, 10), (16_385, 11), (20_001, 64), (32_767, 3),
                                  (32_768, 62), (32_769, 63), (65_537, 2), (70_000, 20), (131_073, 1)])
 def test_tree_equals_quadratic_solve(zr, t, R):
