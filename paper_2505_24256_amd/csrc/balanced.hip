@@ -147,18 +147,25 @@ __global__ void k_thiele(zr_mod M, uint32_t T, uint32_t nk, const uint64_t* __re
 // ----------------------------------------------------------------------------
 // Thiele, one wavefront per slice (nk <= 64 KPL - 1).  The same continued
 // fraction as thiele_body, computed without per-step inverses: an inverse
-// difference is carried as a fraction N/D,
-//     phi_{m+1}(x_j) = (x_j - x_m) D_j D_m / (N_j D_m - N_m D_j),
-// starting from (f_j, 1).  Every D that is used is nonzero (a zero one is the
-// vanishing denominator that ends the recursion), so replacing b_s by N_s/D_s
-// and clearing the D's scales the confirmation fraction P/Q and the
-// polynomials (A, B) by nonzero constants: no zero test and no ratio changes,
-// and the final normalisation of B removes the constant.  One inverse remains.
+// difference is carried as phi_m = c_m N/D,
+//     N'_j = (x_j - x_m) D_j,   D'_j = N_j D_m - N_m D_j,   c_{m+1} = D_m / c_m,
+// starting from (f_j, 1), c_0 = 1.  The c's never appear: with t_s = c_s P/Q the
+// continued fraction's tail from b_s on,
+//     (P, Q) <- (N_s P + (x - x_s) Q, D_s P),
+// since c_s c_{s+1} = D_s.  Every D that is used is nonzero (a zero one is the
+// vanishing denominator that ends the recursion), and a common factor of N and D, of P and
+// Q or of A and B cancels: no zero test and no ratio changes, and the final
+// normalisation of B removes what is left.  So the products may be Montgomery
+// reductions of plain residues (each leaves a factor 2^-64 on both), one
+// reduction for each sum of two products.  One inverse remains.
 //   1. all recursion steps m = 0..nk-2 at once over the lanes (lane-held
 //      index j = 64 k + lane), up to the first step with a zero denominator;
 //   2. the confirmation test of every candidate m in parallel (lane-held m),
 //      one uniform loop over s = mlast-1..0 with b_s broadcast from its lane;
 //   3. the first confirmed m -> (A, B), lane-held coefficient index r.
+// Bound by integer issue: three products and two reductions a step and part, where
+// (N, D) cleared of c took four or five full modular products (5000 slices of 42 nodes:
+// 209 -> 106 us).
 // ----------------------------------------------------------------------------
 constexpr int kThWaves = 4;      // slices (wavefronts) per workgroup
 constexpr int kThMaxKpl = 8;     // values per lane: nk <= 511
@@ -182,13 +189,22 @@ __device__ __forceinline__ uint64_t held(const uint64_t (&v)[KPL], uint32_t idx,
   return bcast(mine, idx & 63);
 }
 
+// T 2^-64 mod p for T < p 2^64 (ni = -1/p mod 2^64)
+__device__ __forceinline__ uint64_t mont_red(uint64_t p, uint64_t ni, zr_u128 T) {
+  const uint64_t lo = (uint64_t)T;
+  const uint64_t r = (uint64_t)(T >> 64) + zr_mulhi(lo * ni, p) + (lo != 0);  // the low words cancel with a carry
+  return r >= p ? r - p : r;
+}
+
 template <int KPL>
 __device__ void thiele_wave(const zr_mod& M, uint32_t T, uint32_t nk, const uint64_t* __restrict__ X,
                             const uint64_t* __restrict__ F, uint64_t* __restrict__ A, uint64_t* __restrict__ B,
                             int32_t* __restrict__ degA, int32_t* __restrict__ degB, int32_t* __restrict__ st,
                             uint32_t i) {
   const uint32_t lane = threadIdx.x & 63;
-  const uint64_t one = 1 % M.p;
+  const uint64_t one = 1 % M.p, p = M.p;
+  uint64_t ni = 1;  // -1/p modulo 2^64
+  for (int i = 0; i < 6; ++i) ni *= 2 + p * ni;
   auto fail = [&](int32_t code) {
     if (lane == 0) {
       st[i] = code;
@@ -227,8 +243,8 @@ __device__ void thiele_wave(const zr_mod& M, uint32_t T, uint32_t nk, const uint
       for (int k = g; k < KPL; ++k) {
         const uint32_t j = 64 * k + lane;
         if (j > m && j < nk) {
-          const uint64_t dn = zr_sub(M, zr_mul(M, N[k], Dm), zr_mul(M, Nm, D[k]));
-          N[k] = zr_mul(M, zr_mul(M, zr_sub(M, xv[k], xm), D[k]), Dm);
+          const uint64_t dn = mont_red(p, ni, (zr_u128)N[k] * Dm + (zr_u128)(p - Nm) * D[k]);
+          N[k] = mont_red(p, ni, (zr_u128)zr_sub(M, xv[k], xm) * D[k]);
           D[k] = dn;
           zero |= dn == 0;
         }
@@ -267,9 +283,8 @@ __device__ void thiele_wave(const zr_mod& M, uint32_t T, uint32_t nk, const uint
           if (P[k] == 0) {
             ok[k] = false;  // a zero tail: the nested fraction divides by zero
           } else {
-            const uint64_t u = zr_mul(M, zr_sub(M, xc[k], xs), Ds);
-            const uint64_t nP = zr_add(M, zr_mul(M, Ns, P[k]), zr_mul(M, u, Q[k]));
-            Q[k] = zr_mul(M, Ds, P[k]);
+            const uint64_t nP = mont_red(p, ni, (zr_u128)Ns * P[k] + (zr_u128)zr_sub(M, xc[k], xs) * Q[k]);
+            Q[k] = mont_red(p, ni, (zr_u128)Ds * P[k]);
             P[k] = nP;
           }
         }
@@ -279,14 +294,14 @@ __device__ void thiele_wave(const zr_mod& M, uint32_t T, uint32_t nk, const uint
   uint32_t c = nk;
 #pragma unroll
   for (int k = 0; k < KPL; ++k) {
-    const uint64_t hit = __ballot(ok[k] && P[k] == zr_mul(M, fc[k], Q[k]));
+    const uint64_t hit = __ballot(ok[k] && mont_red(p, ni, P[k]) == mont_red(p, ni, (zr_u128)fc[k] * Q[k]));
     if (hit && c == nk) c = 64 * k + (uint32_t)__builtin_ctzll(hit);
   }
   if (c == nk) {
     fail(zstep < nk ? -4 : -5);
     return;
   }
-  // 3. (A, B) <- (N_c, D_c); (A, B) <- (N_s A + (x - x_s) D_s B, D_s A) for
+  // 3. (A, B) <- (N_c, D_c); (A, B) <- (N_s A + (x - x_s) B, D_s A) for
   //    s = c-1..0; after c - s steps the degree is at most c - s <= c
   uint64_t Ac[KPL], Bc[KPL];
   {
@@ -304,7 +319,6 @@ __device__ void thiele_wave(const zr_mod& M, uint32_t T, uint32_t nk, const uint
     const uint32_t top = c - 64u * g < 64u ? c - 64u * g : 64u;  // s < c
     for (uint32_t l = top; l-- > 0;) {
       const uint64_t Ns = bcast(N[g], l), Ds = bcast(D[g], l), xs = bcast(xv[g], l);
-      const uint64_t u = zr_mul(M, xs, Ds);
       uint64_t Bm[KPL];  // coefficient r-1 of B
 #pragma unroll
       for (int k = 0; k < KPL; ++k) {
@@ -315,9 +329,8 @@ __device__ void thiele_wave(const zr_mod& M, uint32_t T, uint32_t nk, const uint
 #pragma unroll
       for (int k = 0; k < KPL; ++k) {
         if (64u * k > c) continue;  // coefficients above the final degree stay 0
-        const uint64_t a =
-            zr_add(M, zr_sub(M, zr_mul(M, Ns, Ac[k]), zr_mul(M, u, Bc[k])), zr_mul(M, Ds, Bm[k]));
-        Bc[k] = zr_mul(M, Ds, Ac[k]);
+        const uint64_t a = mont_red(p, ni, (zr_u128)Ns * Ac[k] + (zr_u128)(p - xs) * Bc[k] + Bm[k]);
+        Bc[k] = mont_red(p, ni, (zr_u128)Ds * Ac[k]);
         Ac[k] = a;
       }
     }
