@@ -130,11 +130,10 @@ __global__ void __launch_bounds__(64 * (1 + kPcMaxTiles))
 // in blocks of 256 = kDeltaBlock rows)
 __global__ void __launch_bounds__(kDeltaBlock) k_b_delta(uint32_t n, const uint32_t* __restrict__ prefix,
                                                          const BSolve* __restrict__ sys) {
-  __shared__ uint64_t sh[kDeltaBlock / 64 + 1];
   const uint32_t s = seg_find(prefix, n, blockIdx.x);
   const BSolve& b = sys[s];
   const uint32_t l = (blockIdx.x - prefix[s]) * kDeltaBlock + threadIdx.x;
-  vs_delta_block(b.a, l, b.mL, b.winv, b.status, sh);
+  if (l < b.a.t) vs_delta_body(b.a, l, b.mL, b.winv, b.status);
 }
 
 __global__ void k_b_scale(uint32_t n, const uint32_t* __restrict__ prefix, const BSolve* __restrict__ sys) {
@@ -207,29 +206,17 @@ struct BMaster {
   uint64_t* part;    // [nic][t]
 };
 
-__global__ void __launch_bounds__(64) k_b_master_small(zr_mod M, uint32_t n, const uint32_t* __restrict__ prefix,
-                                                       const BMaster* __restrict__ sys) {
-  __shared__ uint64_t buf[128];
+__global__ void __launch_bounds__(kMasterBase) k_b_master_small(zr_mod M, uint32_t n,
+                                                                const uint32_t* __restrict__ prefix,
+                                                                const BMaster* __restrict__ sys) {
+  __shared__ MasterLds<1> sh;
   const uint32_t s = seg_find(prefix, n, blockIdx.x);
   const BMaster& b = sys[s];
-  master_small_body(M, b.t, (blockIdx.x - prefix[s]) * 64, b.mono, b.buf[0], b.limbs[0], buf);
+  master_small_body(M, b.t, (blockIdx.x - prefix[s]) * kMasterBase, b.mono, b.buf[0], b.limbs[0], sh);
 }
 
-// level with factors of degree `half` (>= 64), chunks of IC: reads buffer r, writes r ^ 1
-__global__ void __launch_bounds__(64) k_b_master_conv(zr_mod M, uint32_t half, uint32_t IC, uint32_t r, uint32_t n,
-                                                      const uint32_t* __restrict__ prefix,
-                                                      const BMaster* __restrict__ sys) {
-  extern __shared__ uint64_t win[];  // 64 + IC + 8 words
-  const uint32_t s = seg_find(prefix, n, blockIdx.x);
-  const BMaster& b = sys[s];
-  const uint32_t nic = cdiv(half, IC);
-  const uint32_t lb = blockIdx.x - prefix[s], nrb = cdiv(b.t, 64);
-  master_conv_body(M, b.t, half, IC, nic, (lb % nrb) * 64, lb / nrb, b.buf[r], b.limbs[r], b.part, b.t, b.buf[r ^ 1],
-                   b.limbs[r ^ 1], win);
-}
-
-// the same for factors of degree half >= 128 with four waves (256
-// coefficients) sharing each window
+// level with factors of degree `half` (>= kMasterBase), chunks of IC: reads buffer r,
+// writes r ^ 1; four waves (256 coefficients) share each window
 __global__ void __launch_bounds__(256) k_b_master_conv4(zr_mod M, uint32_t half, uint32_t IC, uint32_t r, uint32_t n,
                                                         const uint32_t* __restrict__ prefix,
                                                         const BMaster* __restrict__ sys) {
@@ -818,9 +805,9 @@ void batched_solve(const zr_mod& M, const std::vector<SolveJob>& jobs_in, hipStr
   Segs small, fix;
   uint32_t halfmax = 0;
   for (uint32_t i = 0; i < n; ++i)
-    for (uint32_t h = 64; h < jobs[i].t; h *= 2) halfmax = std::max(halfmax, h);
+    for (uint32_t h = kMasterBase; h < jobs[i].t; h *= 2) halfmax = std::max(halfmax, h);
   std::vector<uint32_t> level_ic;
-  for (uint32_t h = 64; h <= halfmax; h *= 2) {
+  for (uint32_t h = kMasterBase; h <= halfmax; h *= 2) {
     uint64_t blocks = 0;
     for (uint32_t i = 0; i < n; ++i)
       if (jobs[i].t > h) blocks += cdiv(jobs[i].t, 64);
@@ -829,7 +816,7 @@ void batched_solve(const zr_mod& M, const std::vector<SolveJob>& jobs_in, hipStr
   for (uint32_t i = 0; i < n; ++i) {
     const uint32_t t = jobs[i].t;
     uint32_t big = 0;
-    for (uint32_t h = 64; h < t; h *= 2) ++big;
+    for (uint32_t h = kMasterBase; h < t; h *= 2) ++big;
     BMaster& b = bm[i];
     b.t = t;
     b.big = big;
@@ -839,9 +826,9 @@ void batched_solve(const zr_mod& M, const std::vector<SolveJob>& jobs_in, hipStr
     b.limbs[0] = A.alloc<uint4>(t + 16);
     b.limbs[1] = A.alloc<uint4>(t + 16);
     uint32_t nic_max = 1;
-    for (uint32_t h = 64, lv = 0; h < t; h *= 2, ++lv) nic_max = std::max(nic_max, cdiv(h, level_ic[lv]));
+    for (uint32_t h = kMasterBase, lv = 0; h < t; h *= 2, ++lv) nic_max = std::max(nic_max, cdiv(h, level_ic[lv]));
     b.part = nic_max > 1 ? A.alloc<uint64_t>((size_t)nic_max * t) : nullptr;
-    small.add(cdiv(t, 64));
+    small.add(cdiv(t, kMasterBase));
     fix.add(big % 2 ? cdiv(t, 256) : 0);
   }
   // ---- solve workspaces; packed rows and partial sums of all systems in two
@@ -899,12 +886,12 @@ void batched_solve(const zr_mod& M, const std::vector<SolveJob>& jobs_in, hipStr
   }
   // conv levels
   std::vector<Segs> conv, csum;
-  for (uint32_t h = 64, lv = 0; h <= halfmax; h *= 2, ++lv) {
+  for (uint32_t h = kMasterBase, lv = 0; h <= halfmax; h *= 2, ++lv) {
     Segs c, su;
     const uint32_t nic = cdiv(h, level_ic[lv]);
     for (uint32_t i = 0; i < n; ++i) {
       const uint32_t t = jobs[i].t;
-      c.add(t > h ? (size_t)cdiv(t, h >= 128 ? 256 : 64) * nic : 0);  // workgroups of 4 or 1 waves
+      c.add(t > h ? (size_t)cdiv(t, 256) * nic : 0);
       su.add(t > h && nic > 1 ? cdiv(t, 256) : 0);
     }
     conv.push_back(c);
@@ -999,16 +986,13 @@ void batched_solve(const zr_mod& M, const std::vector<SolveJob>& jobs_in, hipStr
   if (graph) check(hipStreamBeginCapture(ls, hipStreamCaptureModeThreadLocal));
   {
     TimedLaunch tl("batch_master", ls);
-    hipLaunchKernelGGL(k_b_master_small, dim3(small.total()), dim3(64), 0, ls, M, n, P32(o_small), d_bm);
+    hipLaunchKernelGGL(k_b_master_small, dim3(small.total()), dim3(kMasterBase), 0, ls, M, n, P32(o_small), d_bm);
     uint32_t r = 0;
     for (size_t lv = 0; lv < conv.size(); ++lv, r ^= 1) {
-      const uint32_t h = 64u << lv, IC = level_ic[lv];
-      if (conv[lv].total() && h >= 128)
+      const uint32_t h = kMasterBase << lv, IC = level_ic[lv];
+      if (conv[lv].total())
         hipLaunchKernelGGL(k_b_master_conv4, dim3(conv[lv].total()), dim3(256), (256 + IC + 8) * 8, ls, M, h, IC, r,
                            n, P32(o_conv[lv]), d_bm);
-      else if (conv[lv].total())
-        hipLaunchKernelGGL(k_b_master_conv, dim3(conv[lv].total()), dim3(64), (64 + IC + 8) * 8, ls, M, h, IC, r, n,
-                           P32(o_conv[lv]), d_bm);
       if (csum[lv].total())
         hipLaunchKernelGGL(k_b_master_sum, dim3(csum[lv].total()), dim3(256), 0, ls, M, h, cdiv(h, IC), r, n,
                            P32(o_csum[lv]), d_bm);

@@ -353,10 +353,10 @@ __global__ void __launch_bounds__(64 * (1 + kPcMaxTiles), RT < 10 ? 4 : 3)
   vs_dots_pc_body<RT, false, UNEVEN, false, true>(a, blockIdx.x, c0 + blockIdx.y, ntile, qbuf);
 }
 
-__global__ void __launch_bounds__(kDeltaBlock) k_vs_delta(VsArgs a, const uint64_t* __restrict__ mLv,
-                                                           uint64_t* __restrict__ winv, int32_t* __restrict__ status) {
-  __shared__ uint64_t sh[kDeltaBlock / 64 + 1];
-  vs_delta_block(a, blockIdx.x * kDeltaBlock + threadIdx.x, mLv, winv, status, sh);
+__global__ void __launch_bounds__(64) k_vs_delta(VsArgs a, const uint64_t* __restrict__ mLv, uint64_t* __restrict__ winv,
+                                                 int32_t* __restrict__ status) {
+  const uint32_t l = blockIdx.x * 64 + threadIdx.x;
+  if (l < a.t) vs_delta_body(a, l, mLv, winv, status);
 }
 
 __global__ void k_vs_scale(VsArgs a, const uint64_t* __restrict__ winv, uint64_t* __restrict__ out, size_t ld_out) {
@@ -532,7 +532,7 @@ hipError_t vsolve(const zr_mod& M, const VsolvePlan& P, const uint64_t* mono, co
     {
       TimedLaunch tl("vs_finish", s);
       if (g == 0)
-        hipLaunchKernelGGL(k_vs_delta, dim3(cdiv(t, kDeltaBlock)), dim3(kDeltaBlock), 0, s, a, mL, winv, status);
+        hipLaunchKernelGGL(k_vs_delta, dim3(cdiv(t, 64)), dim3(64), 0, s, a, mL, winv, status);
       hipLaunchKernelGGL(k_vs_scale, dim3(cdiv(t, 256), Rg), dim3(256), 0, s, a, winv, out + (size_t)r0 * ld_out,
                          ld_out);
     }
@@ -633,7 +633,7 @@ hipError_t vsolve_leaf(const zr_mod& M, uint32_t t, uint32_t R1, bool sums, uint
                        mono, mono_p, CL, M);
     if (!sums) {
       hipLaunchKernelGGL(k_vs_chain_d, dim3(cdiv(t, 256), q.S), dim3(256), 0, s, a);
-      hipLaunchKernelGGL(k_vs_delta, dim3(cdiv(t, kDeltaBlock)), dim3(kDeltaBlock), 0, s, a, (const uint64_t*)nullptr,
+      hipLaunchKernelGGL(k_vs_delta, dim3(cdiv(t, 64)), dim3(64), 0, s, a, (const uint64_t*)nullptr,
                          winv, status);
     }
   }
@@ -660,7 +660,7 @@ hipError_t vsolve_leaf(const zr_mod& M, uint32_t t, uint32_t R1, bool sums, uint
       TimedLaunch tl("vs_finish", s);
       a.sums = sums && g == 0 ? 1 : 0;  // series 0 holds the denominators
       if (a.sums)
-        hipLaunchKernelGGL(k_vs_delta, dim3(cdiv(t, kDeltaBlock)), dim3(kDeltaBlock), 0, s, a, (const uint64_t*)nullptr,
+        hipLaunchKernelGGL(k_vs_delta, dim3(cdiv(t, 64)), dim3(64), 0, s, a, (const uint64_t*)nullptr,
                            winv, status);
       const uint32_t o = r0 - (sums && g > 0 ? 1 : 0);
       if (Rg > a.sums)
@@ -678,10 +678,12 @@ hipError_t vsolve_leaf(const zr_mod& M, uint32_t t, uint32_t R1, bool sums, uint
 // of all its factors in one array of length t (factor [a, b) at [a, b)).
 // ============================================================================
 
-__global__ void __launch_bounds__(64) k_master_small(zr_mod M, uint32_t t, const uint64_t* __restrict__ mono,
-                                                     uint64_t* __restrict__ out, uint4* __restrict__ limbs) {
-  __shared__ uint64_t buf[128];
-  master_small_body(M, t, blockIdx.x * 64, mono, out, limbs, buf);
+constexpr int kMasterParts = 4;
+__global__ void __launch_bounds__(kMasterParts* kMasterBase)
+    k_master_small(zr_mod M, uint32_t t, const uint64_t* __restrict__ mono, uint64_t* __restrict__ out,
+                   uint4* __restrict__ limbs) {
+  __shared__ MasterLds<kMasterParts> sh;
+  master_small_body(M, t, blockIdx.x * kMasterBase, mono, out, limbs, sh);
 }
 
 __global__ void k_master_sum(zr_mod M, uint32_t t, uint32_t half, uint32_t nic, const uint64_t* __restrict__ cur,
@@ -695,7 +697,7 @@ size_t master_tmp_words(uint32_t t) {
   // t for the ping-pong level array, two limb arrays of t + 16 entries (two
   // words each) and the chunk partials of the largest levels
   uint32_t nic_max = 1;
-  for (uint32_t half = 64; half < t; half *= 2) nic_max = std::max(nic_max, cdiv(half, conv_ic(half, cdiv(t, 64))));
+  for (uint32_t half = kMasterBase; half < t; half *= 2) nic_max = std::max(nic_max, cdiv(half, conv_ic(half, cdiv(t, 64))));
   return (size_t)t + 1 + 4 * ((size_t)t + 16) + (nic_max > 1 ? (size_t)nic_max * t : 0) + 64;
 }
 
@@ -706,16 +708,16 @@ hipError_t master_levels(const zr_mod& M, uint32_t t, uint32_t block, const uint
   if (t == 0) return hipSuccess;
   TimedLaunch tl("master", s);
   const uint32_t top = std::min(t, block);
-  uint32_t big = 0;  // levels with half >= 64
-  for (uint32_t half = 64; half < top; half *= 2) ++big;
+  uint32_t big = 0;  // levels with half >= kMasterBase
+  for (uint32_t half = kMasterBase; half < top; half *= 2) ++big;
   const size_t t2 = ((size_t)t + 1) & ~(size_t)1;  // keep the limb arrays 16-byte aligned
   uint4* limbs[2] = {(uint4*)(tmp + t2), (uint4*)(tmp + t2 + 2 * ((size_t)t + 16))};
   uint64_t* part = tmp + t2 + 4 * ((size_t)t + 16);
   uint64_t* bufs[2] = {Mc, tmp};
   // the level written last must be Mc: the small kernel writes bufs[big % 2]
   uint32_t w = big % 2;
-  hipLaunchKernelGGL(k_master_small, dim3(cdiv(t, 64)), dim3(64), 0, s, M, t, mono, bufs[w], limbs[w]);
-  for (uint32_t half = 64; half < top; half *= 2) {
+  hipLaunchKernelGGL(k_master_small, dim3(cdiv(t, kMasterBase)), dim3(kMasterParts * kMasterBase), 0, s, M, t, mono, bufs[w], limbs[w]);
+  for (uint32_t half = kMasterBase; half < top; half *= 2) {
     const uint32_t r = w;
     w ^= 1;
     const uint32_t IC = conv_ic(half, cdiv(t, 64));

@@ -359,14 +359,14 @@ __device__ __forceinline__ void vs_chain_body(const VsArgs& a, uint32_t l, uint3
 // per r < t the limbs of M_r and of r M_r (six 32-bit words).
 constexpr uint32_t kChainW = 6;
 
-// Sum of a block's six columns mod p when every column is below 2^60 (at most
-// 64 products since the last fold): the value is below 2^137, three words
-// with the top one below 2^9.  No branch, so the products of a block and its
+// Sum of a block's six columns mod p when every column is below 2^61 (at most
+// 128 products since the last fold): the value is below 2^138, three words
+// with the top one below 2^10.  No branch, so the products of a block and its
 // reduction stay in one basic block.
 __device__ __forceinline__ uint64_t acc6_reduce_block(const zr_mod& M, const Acc6& a) {
   const zr_u128 low = (zr_u128)a.w0 + ((zr_u128)a.w22 << 22) + ((zr_u128)a.w32 << 32) + ((zr_u128)a.w44 << 44) +
-                      ((zr_u128)a.w54 << 54);  // below 2^115
-  const zr_u128 mid = (low >> 64) + ((zr_u128)a.w76 << 12);  // bits 64.. of the value, below 2^73
+                      ((zr_u128)a.w54 << 54);  // below 2^116
+  const zr_u128 mid = (low >> 64) + ((zr_u128)a.w76 << 12);  // bits 64.. of the value, below 2^74
   const uint64_t w0 = (uint64_t)low, w1 = (uint64_t)mid, w2 = (uint64_t)(mid >> 64);
   uint64_t r = zr_mod128(M, 0, w2);
   r = zr_mod128(M, r, w1);
@@ -776,62 +776,23 @@ __device__ __forceinline__ void vs_dots_pc_body(const VsArgs& a, uint32_t rb, ui
   vs_pc_consume<RT>(a, c, lo, hi, nb, live, l, lane, j0, rows, qbuf, M);
 }
 
-// Inverses of the values w of a block's kDeltaBlock threads by Montgomery's
-// simultaneous inversion: with P<_i and P>_i the products of the w of the
-// threads before and after thread i, 1/w_i = P<_i P>_i / (product of all), so
-// the block pays one inversion and a few products per thread instead of one
-// inversion per thread.  The products within a wave are shuffle scans; the
-// four wave totals meet in LDS.  Threads with use = false or w = 0 enter the
-// products as 1 and get 0.  Every thread of the block must call it.
-constexpr uint32_t kDeltaBlock = 256;
+constexpr uint32_t kDeltaBlock = 256;  // rows per workgroup of the batched and multi-prime finishes
 
-__device__ __forceinline__ uint64_t block_inverse(const zr_mod& M, uint64_t w, bool use, uint64_t* sh) {
-  constexpr uint32_t NW = kDeltaBlock / 64;
-  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint64_t one = 1 % M.p;
-  const bool part = use && w != 0;
-  uint64_t pre = part ? w : one, suf = pre;  // inclusive prefix / suffix products within the wave
-#pragma unroll
-  for (uint32_t d = 1; d < 64; d <<= 1) {
-    const uint64_t a = __shfl_up(pre, d), b = __shfl_down(suf, d);
-    if (lane >= d) pre = zr_mul(M, pre, a);
-    if (lane + d < 64) suf = zr_mul(M, suf, b);
-  }
-  uint64_t epre = __shfl_up(pre, 1), esuf = __shfl_down(suf, 1);
-  if (lane == 0) epre = one;
-  if (lane == 63) esuf = one;
-  if (lane == 63) sh[wave] = pre;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    uint64_t all = one;
-    for (uint32_t q = 0; q < NW; ++q) all = zr_mul(M, all, sh[q]);
-    sh[NW] = zr_inv(M, all);
-  }
-  __syncthreads();
-  uint64_t other = sh[NW];
-  for (uint32_t q = 0; q < NW; ++q)
-    if (q != wave) other = zr_mul(M, other, sh[q]);
-  return part ? zr_mul(M, zr_mul(M, epre, esuf), other) : 0;
-}
-
-// Combine chunks, part 1 for the rows of one block (l = row of this thread,
-// live when l < t): w = m_l delta_l = m_l M'(m_l), either as
+// Combine chunks, part 1 for row l: w = m_l delta_l = m_l M'(m_l), either as
 // t m^t + sum_c m^{lo_c} D_c from the chain pass's D_c, or as m times
 // sum_c m^{lo_c} H_c from the Horner partials H_c of the dot-product pass,
-// both by Horner over the chunks; then the inverses of the block's w (one
-// inversion per block) with their Shoup constants into winv[2t].  A zero w
-// marks the system singular.  Every thread of the block must call it (it
-// holds barriers).
-__device__ __forceinline__ void vs_delta_block(const VsArgs& a, uint32_t l, const uint64_t* __restrict__ mLv,
-                                               uint64_t* __restrict__ winv, int32_t* __restrict__ status,
-                                               uint64_t* sh) {
+// both by Horner over the chunks, or as the power sums' series; then 1/w with its
+// Shoup constant into winv[2t].  A zero w marks the system singular.  Each row inverts
+// for itself: the binary Euclid is 3 us of latency whatever the number of rows,
+// where sharing one inversion per 256 rows took some 25 dependent products more
+// (t = 50: 9.1 -> 6.0 us; t = 300 007: 38 -> 25 us).
+__device__ __forceinline__ void vs_delta_body(const VsArgs& a, uint32_t l, const uint64_t* __restrict__ mLv,
+                                              uint64_t* __restrict__ winv, int32_t* __restrict__ status) {
   const zr_mod M = a.M;
-  const bool live = l < a.t;
   uint64_t w = 0;
-  if (live && a.sums) {
+  if (a.sums) {
     for (uint32_t c = 0; c < a.Sd; ++c) w = zr_add(M, w, a.spart[(size_t)c * a.R * a.t + l]);
-    if (w == 0) atomicCAS(status, 0, -3);
-  } else if (live) {
+  } else {
     const uint64_t m = a.mono[l];
     // chunk partials from the top chunk (c = 0) down, Horner in m^L (m^len
     // for the last, shorter chunk)
@@ -854,13 +815,11 @@ __device__ __forceinline__ void vs_delta_block(const VsArgs& a, uint32_t l, cons
     }
     // with D_c the sum is m M'(m) itself; the Horner partials give M'(m)
     w = a.dpart ? acc : zr_mul(M, m, acc);
-    if (w == 0) atomicCAS(status, 0, -3);  // ZR_ESINGULAR, unless an earlier step already failed
   }
-  const uint64_t wi = block_inverse(M, w, live, sh);
-  if (live) {
-    winv[l] = wi;
-    winv[a.t + l] = wi ? zr_shoup_pre(M, wi) : 0;
-  }
+  if (w == 0) atomicCAS(status, 0, -3);  // ZR_ESINGULAR, unless an earlier step already failed
+  const uint64_t wi = zr_inv(M, w);
+  winv[l] = wi;
+  winv[a.t + l] = wi ? zr_shoup_pre(M, wi) : 0;
 }
 
 // Combine chunks, part 2 for row l and series j (right-hand side j, or j - 1 behind power sums):
@@ -879,51 +838,88 @@ __device__ __forceinline__ uint4 limbs22(uint64_t v) {
   return make_uint4((uint32_t)(v & 0x3FFFFF), (uint32_t)((v >> 22) & 0x3FFFFF), (uint32_t)(v >> 44), 0u);
 }
 
-// Bottom levels (factors of degree < 64) in LDS for leaves [b, b+64) of a
-// system of t leaves: pairwise products level by level; node boundaries
-// (multiples of 2h) coincide with those of the whole tree, including the
-// ragged end.  Writes the non-leading coefficients and their limbs.
-// buf: 2 x 64 words of LDS.
+// Bottom levels (factors of degree < kMasterBase) in LDS for leaves [b, b + kMasterBase)
+// of a system of t leaves, one output coefficient per thread; node boundaries (multiples of 2h)
+// coincide with those of the whole tree, including the ragged end.  Writes the
+// non-leading coefficients and their limbs.  The left factor's coefficients are read
+// as limbs at the same index by all lanes of a node, the right one's behind a mask, so
+// that the loop has no bounds of its own to wait for.  One workgroup of 256
+// leaves took 30 us in four launches (64 leaves a wave, then two levels through memory);
+// here 18 us with four threads a coefficient, 26 with one.
+constexpr uint32_t kMasterBase = 256;
+template <int PARTS>
+struct MasterLds {
+  uint4 lim[kMasterBase];
+  uint64_t val[kMasterBase + 1];  // the last word is zero
+  uint64_t part[PARTS > 1 ? PARTS - 1 : 1][kMasterBase];
+};
+
+// PARTS x kMasterBase threads: PARTS threads share the products of one coefficient
+// (one workgroup on a CU leaves each SIMD one wave otherwise, which waits for LDS).
+template <int PARTS>
 __device__ __forceinline__ void master_small_body(const zr_mod& M, uint32_t t, uint32_t b,
                                                   const uint64_t* __restrict__ mono, uint64_t* __restrict__ out,
-                                                  uint4* __restrict__ limbs, uint64_t* buf) {
-  const uint32_t k = threadIdx.x & 63;
-  const uint32_t n = std::min<uint32_t>(64, t - b);
-  uint64_t* cur = buf;
-  uint64_t* nxt = buf + 64;
-  if (k < n) cur[k] = zr_neg(M, mono[b + k] % M.p);
+                                                  uint4* __restrict__ limbs, MasterLds<PARTS>& sh) {
+  const uint32_t k = threadIdx.x % kMasterBase, pt = __builtin_amdgcn_readfirstlane(threadIdx.x / kMasterBase);
+  const uint32_t n = std::min<uint32_t>(kMasterBase, t - b);
+  if (threadIdx.x == 0) sh.val[kMasterBase] = 0;
+  if (pt == 0) {
+    const uint64_t v = k < n ? zr_neg(M, mono[b + k]) : 0;
+    sh.val[k] = v;
+    sh.lim[k] = limbs22(v);
+  }
   __syncthreads();
-  for (uint32_t half = 1; half < 64 && half < t; half *= 2) {
-    if (k < n) {
-      const uint32_t a = (k / (2 * half)) * (2 * half);
-      const uint32_t n1 = std::min(half, n - a);
-      const uint32_t n2 = std::min(half, n - a - n1);
-      const uint32_t kk = k - a;
-      const uint64_t* Lc = cur + a;
-      const uint64_t* Rc = cur + a + n1;
-      zr_acc192 acc;
-      zr_acc_zero(acc);
-      if (n2 > 0) {
-        const uint32_t ilo = kk + 1 > n2 ? kk + 1 - n2 : 0;
-        const uint32_t ihi = std::min(kk, n1 - 1);
-        for (uint32_t i = ilo; i <= ihi; ++i) zr_acc_mac(acc, Lc[i], Rc[kk - i]);
+  for (uint32_t half = 1; half < n; half *= 2) {
+    const uint32_t a = k & ~(2 * half - 1), kk = k - a;
+    const uint32_t n1 = a < n ? std::min(half, n - a) : 0, n2 = a + n1 < n ? std::min(half, n - a - n1) : 0;
+    // the products i that any lane of the wave needs (half >= 64: one node per wave)
+    uint32_t ilo = 0, ihi = half;
+    if (half >= 64) {
+      const uint32_t k0 = __builtin_amdgcn_readfirstlane(kk & ~63u);
+      const uint32_t m1 = __builtin_amdgcn_readfirstlane(n1), m2 = __builtin_amdgcn_readfirstlane(n2);
+      ilo = k0 + 1 > m2 ? std::min(k0 + 1 - m2, m1) : 0;
+      ihi = m2 ? std::min(k0 + 64, m1) : ilo;
+    }
+    const bool split = PARTS > 1 && half >= 32;
+    if (split) {
+      const uint32_t len = (ihi - ilo + PARTS - 1) / PARTS;
+      ilo = std::min(ihi, ilo + pt * len);
+      ihi = std::min(ihi, ilo + len);
+    }
+    uint64_t v = 0;
+    const uint64_t* R = sh.val + a + n1;
+    if (pt == 0 || split) {
+      Acc6 acc;
+      acc6_zero(acc);
+#pragma unroll 8
+      for (uint32_t i = ilo; i < ihi; ++i) {
+        const uint4 L = sh.lim[a + i];
+        const uint64_t r = *(kk - i < n2 && i < n1 ? R + (kk - i) : sh.val + kMasterBase);
+        acc6_mac(acc, (uint32_t)r, (uint32_t)(r >> 32), L.x, L.y, L.z);
       }
-      if (kk >= n1) zr_acc_mac(acc, 1, Rc[kk - n1]);
-      if (kk >= n2) zr_acc_mac(acc, 1, Lc[kk - n2]);
-      nxt[k] = zr_acc_reduce(M, acc);
+      v = acc6_reduce_block(M, acc);
+      if (pt == 0 && k < n) {
+        if (kk >= n1) v = zr_add(M, v, R[kk - n1]);
+        if (kk >= n2) v = zr_add(M, v, sh.val[a + (kk - n2)]);
+      }
+      if (pt > 0) sh.part[pt > 0 ? pt - 1 : 0][k] = v;
     }
     __syncthreads();
-    uint64_t* tswap = cur;
-    cur = nxt;
-    nxt = tswap;
+    if (pt == 0 && k < n) {
+      if (split)
+        for (int q = 0; q < PARTS - 1; ++q) v = zr_add(M, v, sh.part[q][k]);
+      sh.val[k] = v;
+      sh.lim[k] = limbs22(v);
+    }
+    __syncthreads();
   }
-  if (k < n) {
-    out[b + k] = cur[k];
-    limbs[b + k] = limbs22(cur[k]);
+  if (pt == 0 && k < n) {
+    out[b + k] = sh.val[k];
+    limbs[b + k] = sh.lim[k];
   }
 }
 
-// Large levels (factors of degree >= 64): a wave owns 64 consecutive output
+// Large levels (factors of degree >= kMasterBase): a wave owns 64 consecutive output
 // coefficients g0.. of one product and one chunk ic of the convolution index.
 // The factor L_i is wave-uniform: the level's coefficients carry their 22-bit
 // limbs (four 32-bit words per value) so that eight of them arrive with two
@@ -958,7 +954,7 @@ __device__ __forceinline__ uint64_t master_linear_terms(const zr_mod& M, uint64_
 // NW waves of one workgroup take 64 NW consecutive coefficients of one
 // product (64 NW <= 2 half) and share one LDS window, so a window of
 // 64 NW + IC words serves NW waves.
-template <int NW = 1>
+template <int NW>
 __device__ __forceinline__ void master_conv_body(const zr_mod& M, uint32_t t, uint32_t half, uint32_t IC, uint32_t nic,
                                                  uint32_t g0, uint32_t ic, const uint64_t* __restrict__ cur,
                                                  const uint4* __restrict__ limbs, uint64_t* __restrict__ part,

@@ -112,24 +112,19 @@ __device__ __forceinline__ uint64_t combine_chunks(const zr_mod& M, uint32_t t, 
   return acc;
 }
 
-// a_l = W(m_l) / (m_l M'(m_l)); the block's inverses by one inversion.
+// a_l = W(m_l) / (m_l M'(m_l)).
 __global__ void __launch_bounds__(kDeltaBlock) k_mp_finish(zr_mod M, uint32_t t, uint32_t L, uint32_t S,
                                                           const uint64_t* __restrict__ mono,
                                                           const uint64_t* __restrict__ BW,
                                                           const uint64_t* __restrict__ BD, uint64_t* __restrict__ out,
                                                           int32_t* __restrict__ status) {
-  __shared__ uint64_t sh[kDeltaBlock / 64 + 1];
   const uint32_t l = blockIdx.x * kDeltaBlock + threadIdx.x;
-  const bool live = l < t;
-  uint64_t W = 0, w = 0;
-  if (live) {
-    const uint64_t m = mono[l];
-    W = combine_chunks(M, t, L, S, m, BW, l);
-    w = zr_mul(M, m, combine_chunks(M, t, L, S, m, BD, l));
-    if (w == 0) atomicCAS(status, 0, -3);  // ZR_ESINGULAR
-  }
-  const uint64_t wi = block_inverse(M, w, live, sh);
-  if (live) out[l] = zr_mul(M, W, wi);
+  if (l >= t) return;
+  const uint64_t m = mono[l];
+  const uint64_t W = combine_chunks(M, t, L, S, m, BW, l);
+  const uint64_t w = zr_mul(M, m, combine_chunks(M, t, L, S, m, BD, l));
+  if (w == 0) atomicCAS(status, 0, -3);  // ZR_ESINGULAR
+  out[l] = zr_mul(M, W, zr_inv(M, w));
 }
 
 // ---- multiword integers (little-endian 64-bit words, kMpWords of them) ----------
