@@ -9,10 +9,9 @@
 
 #include "field.hpp"
 #include "kernels.hpp"
+#include "kernels_dev.hpp"
 
 namespace zr {
-
-__host__ __device__ static inline uint32_t cdiv(uint64_t a, uint64_t b) { return (uint32_t)((a + b - 1) / b); }
 
 // ----------------------------------------------------------------------------
 // Thiele, one lane per slice.  Samples F[j][i] at nodes X[j], j < nk.
@@ -449,56 +448,79 @@ hipError_t thiele_slices(const zr_mod& M, uint32_t T, uint32_t nk, const uint64_
 }
 
 // ----------------------------------------------------------------------------
-// Transposed Vandermonde apply out[i] = sum_l a_l m_l^(i+1): one lane per term
-// l walks its power chain over a block of i with a fixed Shoup multiplier; the
-// per-i partial sums are reduced across the wave with lane shuffles and across
-// the workgroup in LDS (the substitution kernel of §2.2 with its warp
-// reduction, on 64-lane wavefronts).
+// Transposed Vandermonde apply out[i] = sum_l a_l m_l^(i+1), as a product of two
+// small tables per workgroup: with i = i0 + 16 g + k,
+//   out[i] = sum_l m_l^k B_g[l],   B_g[l] = a_l m_l^(i0 + 1 + 16 g),
+// the 16 powers m_l^k and 8 values B_g[l] of each of 256 terms are made once by the
+// term's thread; then each thread takes one k and 16 of the terms, and sums the
+// products for all 8 g exactly (six columns), one reduction per sum; the 16
+// partial sums of an output meet in LDS.  Bound by integer issue: 6
+// multiply-adds per term and power in place of a modular product and a
+// 64-lane sum of residues by shuffles for every power (t = T = 1500: 45 -> 10 us).
 // ----------------------------------------------------------------------------
-constexpr int kApW = 4;      // waves per workgroup
 constexpr int kApB = 128;    // powers i per workgroup
+constexpr int kApL = 256;    // terms per workgroup, one per thread
+constexpr int kApK = 16, kApG = kApB / kApK;
 
-__device__ __forceinline__ uint64_t wave_sum_mod(const zr_mod& M, uint64_t v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    const uint64_t o = __shfl_xor(v, off, 64);
-    v = zr_add(M, v, o);
-  }
-  return v;
-}
+struct ApLds {
+  uint64_t pw[kApL][kApK + 1];  // m_l^k; afterwards the partial sums [16][kApB]
+  uint64_t b[kApL][kApG];
+};
 
-// block (bx, by): powers i0 = kApB bx .. + kApB, terms kApW*64 by .. (one partial row by)
+// block (bx, by): powers i0 = kApB bx .. + kApB, terms kApL by .. (one partial row by)
 __device__ __forceinline__ void vapply_body(const zr_mod& M, uint32_t t, const uint64_t* __restrict__ mono,
                                             const uint64_t* __restrict__ a, uint32_t T,
-                                            uint64_t* __restrict__ partial, uint32_t bx, uint32_t by,
-                                            uint64_t (*sh)[kApB]) {
-  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint32_t l = by * (kApW * 64) + threadIdx.x;
+                                            uint64_t* __restrict__ partial, uint32_t bx, uint32_t by, ApLds& sh) {
+  const uint32_t tid = threadIdx.x, l = by * kApL + tid;
   const uint32_t i0 = bx * kApB;
   const uint32_t nb = std::min<uint32_t>(kApB, T - i0);
-  uint64_t m = 0, mp = 0, b = 0;
-  if (l < t) {
-    m = mono[l];
-    mp = zr_shoup_pre(M, m);
-    b = zr_mul(M, a[l], zr_pow(M, m, i0 + 1));
-  }
-  for (uint32_t ii = 0; ii < nb; ++ii) {
-    const uint64_t s = wave_sum_mod(M, b);
-    if (lane == 0) sh[wave][ii] = s;
-    b = zr_shoup(M, b, m, mp);
+  {
+    const uint64_t m = l < t ? mono[l] : 0, mp = zr_shoup_pre(M, m);
+    uint64_t w = 1 % M.p;
+#pragma unroll
+    for (int k = 0; k < kApK; ++k) {
+      sh.pw[tid][k] = w;
+      w = zr_shoup(M, w, m, mp);
+    }
+    const uint64_t wp = zr_shoup_pre(M, w);  // m^16
+    uint64_t v = l < t ? zr_mul(M, a[l], zr_pow(M, m, i0 + 1)) : 0;
+#pragma unroll
+    for (int g = 0; g < kApG; ++g) {
+      sh.b[tid][g] = v;
+      v = zr_shoup(M, v, w, wp);
+    }
   }
   __syncthreads();
-  for (uint32_t ii = threadIdx.x; ii < nb; ii += blockDim.x) {
-    uint64_t s = sh[0][ii];
-    for (int w = 1; w < kApW; ++w) s = zr_add(M, s, sh[w][ii]);
-    partial[(size_t)by * T + i0 + ii] = s;
+  const uint32_t k = tid % kApK, sub = tid / kApK;  // terms 16 sub .. of the workgroup's
+  Acc6 acc[kApG];
+#pragma unroll
+  for (int g = 0; g < kApG; ++g) acc6_zero(acc[g]);
+#pragma unroll 2
+  for (uint32_t j = 0; j < kApL / kApK; ++j) {
+    const uint32_t r = sub * (kApL / kApK) + j;
+    const uint4 w = limbs22(sh.pw[r][k]);
+#pragma unroll
+    for (int g = 0; g < kApG; ++g) {
+      const uint64_t v = sh.b[r][g];
+      acc6_mac(acc[g], (uint32_t)v, (uint32_t)(v >> 32), w.x, w.y, w.z);
+    }
+  }
+  __syncthreads();  // the powers are read
+  uint64_t* red = &sh.pw[0][0];
+#pragma unroll
+  for (int g = 0; g < kApG; ++g) red[sub * kApB + g * kApK + k] = acc6_reduce_block(M, acc[g]);
+  __syncthreads();
+  if (tid < nb) {
+    uint64_t s = red[tid];
+    for (uint32_t q = 1; q < kApL / kApK; ++q) s = zr_add(M, s, red[q * kApB + tid]);
+    partial[(size_t)by * T + i0 + tid] = s;
   }
 }
 
-__global__ void __launch_bounds__(kApW * 64) k_vapply(zr_mod M, uint32_t t, const uint64_t* __restrict__ mono,
-                                                      const uint64_t* __restrict__ a, uint32_t T,
-                                                      uint64_t* __restrict__ partial) {
-  __shared__ uint64_t sh[kApW][kApB];
+__global__ void __launch_bounds__(kApL) k_vapply(zr_mod M, uint32_t t, const uint64_t* __restrict__ mono,
+                                                 const uint64_t* __restrict__ a, uint32_t T,
+                                                 uint64_t* __restrict__ partial) {
+  __shared__ ApLds sh;
   vapply_body(M, t, mono, a, T, partial, blockIdx.x, blockIdx.y, sh);
 }
 
@@ -512,27 +534,27 @@ __global__ void k_vapply_sum(zr_mod M, uint32_t T, uint32_t nparts, const uint64
 }
 
 size_t vapply_work_words(uint32_t t, uint32_t T) {
-  return (size_t)std::max<uint32_t>(1, cdiv(t, kApW * 64)) * std::max<uint32_t>(T, 1) + 64;
+  return (size_t)std::max<uint32_t>(1, cdiv(t, kApL)) * std::max<uint32_t>(T, 1) + 64;
 }
 
 hipError_t vapply(const zr_mod& M, uint32_t t, const uint64_t* mono, const uint64_t* a, uint32_t T, uint64_t* out,
                   uint64_t* work, size_t work_words, hipStream_t s) {
   if (T == 0) return hipSuccess;
   if (t == 0) return fill_u64(out, 0, T, s);
-  const uint32_t nparts = cdiv(t, kApW * 64);
+  const uint32_t nparts = cdiv(t, kApL);
   if (work_words < (size_t)nparts * T) return hipErrorInvalidValue;
   TimedLaunch tl("vapply", s);
-  hipLaunchKernelGGL(k_vapply, dim3(cdiv(T, kApB), nparts), dim3(kApW * 64), 0, s, M, t, mono, a, T, work);
+  hipLaunchKernelGGL(k_vapply, dim3(cdiv(T, kApB), nparts), dim3(kApL), 0, s, M, t, mono, a, T, work);
   hipLaunchKernelGGL(k_vapply_sum, dim3(cdiv(T, 256)), dim3(256), 0, s, M, T, nparts, work, out);
   return hipGetLastError();
 }
 
 // ---- many applies in two launches (block -> job by binary search over prefix sums)
-uint32_t vapply_batch_blocks(uint32_t t, uint32_t T) { return t ? cdiv(T, kApB) * cdiv(t, kApW * 64) : 0; }
+uint32_t vapply_batch_blocks(uint32_t t, uint32_t T) { return t ? cdiv(T, kApB) * cdiv(t, kApL) : 0; }
 
-__global__ void __launch_bounds__(kApW * 64) k_vapply_batch(zr_mod M, uint32_t n, const uint32_t* __restrict__ prefix,
+__global__ void __launch_bounds__(kApL) k_vapply_batch(zr_mod M, uint32_t n, const uint32_t* __restrict__ prefix,
                                                             const VapplyJob* __restrict__ jobs) {
-  __shared__ uint64_t sh[kApW][kApB];
+  __shared__ ApLds sh;
   const uint32_t q = thiele_job_of(n, prefix, blockIdx.x);
   const VapplyJob& j = jobs[q];
   const uint32_t lb = blockIdx.x - prefix[q], nbx = cdiv(j.T, kApB);
@@ -545,7 +567,7 @@ __global__ void k_vapply_sum_batch(zr_mod M, uint32_t n, const uint32_t* __restr
   const VapplyJob& j = jobs[q];
   const uint32_t i = (blockIdx.x - prefix[q]) * blockDim.x + threadIdx.x;
   if (i >= j.T) return;
-  const uint32_t nparts = j.t ? cdiv(j.t, kApW * 64) : 0;
+  const uint32_t nparts = j.t ? cdiv(j.t, kApL) : 0;
   uint64_t s = 0;
   for (uint32_t c = 0; c < nparts; ++c) s = zr_add(M, s, j.work[(size_t)c * j.T + i]);
   j.out[i] = s;
@@ -555,7 +577,7 @@ hipError_t vapply_batch(const zr_mod& M, uint32_t n, const uint32_t* d_prefix, u
                         const uint32_t* d_sum_prefix, uint32_t sum_total, const VapplyJob* d_jobs, hipStream_t s) {
   if (n == 0) return hipSuccess;
   TimedLaunch tl("vapply", s);
-  if (total) hipLaunchKernelGGL(k_vapply_batch, dim3(total), dim3(kApW * 64), 0, s, M, n, d_prefix, d_jobs);
+  if (total) hipLaunchKernelGGL(k_vapply_batch, dim3(total), dim3(kApL), 0, s, M, n, d_prefix, d_jobs);
   if (sum_total) hipLaunchKernelGGL(k_vapply_sum_batch, dim3(sum_total), dim3(256), 0, s, M, n, d_sum_prefix, d_jobs);
   return hipGetLastError();
 }
