@@ -19,6 +19,7 @@
 #include "field.hpp"
 #include "kernels.hpp"
 #include "multiprime.hpp"
+#include "tree.hpp"
 
 namespace zr {
 namespace {
@@ -95,6 +96,11 @@ void skeleton_solve(const zr_mod& M, uint32_t nvars, uint32_t t, const uint16_t*
   DevArena A(s);
   uint64_t* mono = A.alloc<uint64_t>(t);
   all_variable_monomials(M, nvars, t, d_exps, maxe, y, A, mono, s);
+  if (tree_applies(t, 1)) {
+    tree_solve(M, t, 1, mono, d_vals, t, d_out, t, d_status, A, s);
+    count_solve(t, 1);
+    return;
+  }
   uint64_t* Mc = A.alloc<uint64_t>(t);
   uint64_t* tmp = A.alloc<uint64_t>(master_tmp_words(t));
   check(master_poly(M, t, mono, Mc, tmp, s));
