@@ -268,6 +268,21 @@ size_t vsolve_workspace_words(const VsolvePlan& P) {
   return vsolve_rhs_words(P) + t + 2 * S * t + t + P.Sd * (size_t)P.Rg * t + S * t + 2 * t + 3 * t + 64;
 }
 
+// Shoup constant of row idx's monomial and the limbs of M_r and r M_r, r = idx
+__device__ __forceinline__ void pack_row(const zr_mod& M, size_t idx, const uint64_t* __restrict__ mono,
+                                         uint64_t* __restrict__ mono_p, const uint64_t* __restrict__ Mc,
+                                         uint32_t* __restrict__ CL) {
+  mono_p[idx] = zr_shoup_pre(M, mono[idx]);
+  const uint64_t v = Mc[idx], d = zr_mul(M, idx % M.p, v);
+  uint32_t* w = CL + idx * kChainW;
+  w[0] = (uint32_t)(v & 0x3FFFFF);
+  w[1] = (uint32_t)((v >> 22) & 0x3FFFFF);
+  w[2] = (uint32_t)(v >> 44);
+  w[3] = (uint32_t)(d & 0x3FFFFF);
+  w[4] = (uint32_t)((d >> 22) & 0x3FFFFF);
+  w[5] = (uint32_t)(d >> 44);
+}
+
 // Packed right-hand sides [ntile][t][ldv], Shoup constants of the monomials
 // and the coefficients r M_r of m M'(m).
 __global__ void k_pack(uint32_t t, uint32_t R, uint32_t RT, uint32_t ntile, uint32_t ldv,
@@ -277,21 +292,13 @@ __global__ void k_pack(uint32_t t, uint32_t R, uint32_t RT, uint32_t ntile, uint
   const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   const size_t total = (size_t)ntile * t * ldv;
   if (idx < total) VT[idx] = pack_word(idx, t, R, RT, ldv, rhs, ld_rhs, Mc);
-  if (idx < t) {
-    mono_p[idx] = zr_shoup_pre(M, mono[idx]);
-    const uint64_t v = Mc[idx], d = zr_mul(M, idx % M.p, v);
-    uint32_t* w = CL + idx * kChainW;
-    w[0] = (uint32_t)(v & 0x3FFFFF);
-    w[1] = (uint32_t)((v >> 22) & 0x3FFFFF);
-    w[2] = (uint32_t)(v >> 44);
-    w[3] = (uint32_t)(d & 0x3FFFFF);
-    w[4] = (uint32_t)((d >> 22) & 0x3FFFFF);
-    w[5] = (uint32_t)(d >> 44);
-  }
+  if (idx < t) pack_row(M, idx, mono, mono_p, Mc, CL);
 }
 
-// Packed rows of the producer/consumer tiles (blockIdx.y = tile), widths tw.
-__global__ void k_pack_pc(VsArgs a, const uint64_t* __restrict__ rhs, size_t ld_rhs, uint32_t* __restrict__ VT) {
+// Packed rows of the producer/consumer tiles (blockIdx.y = tile), widths tw; mono_p
+// (null: made already) and CL on the way.
+__global__ void k_pack_pc(VsArgs a, const uint64_t* __restrict__ rhs, size_t ld_rhs, uint32_t* __restrict__ VT,
+                          uint64_t* __restrict__ mono_p, const uint64_t* __restrict__ Mc, uint32_t* __restrict__ CL) {
   const uint32_t tile = blockIdx.y;
   uint32_t j0 = 0, off = 0, w = 0;
 #pragma unroll
@@ -304,6 +311,7 @@ __global__ void k_pack_pc(VsArgs a, const uint64_t* __restrict__ rhs, size_t ld_
   }
   const uint32_t ldv = pc_ldv(w);
   const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (mono_p && tile == 0 && idx < a.t) pack_row(a.M, idx, a.mono, mono_p, Mc, CL);
   if (idx < (size_t)a.t * ldv)
     VT[(size_t)off * a.t + idx] =
         pack_word_pc((uint32_t)(idx / ldv), (uint32_t)(idx % ldv), a.R, w, j0, rhs, ld_rhs);
@@ -491,12 +499,13 @@ hipError_t vsolve(const zr_mod& M, const VsolvePlan& P, const uint64_t* mono, co
         uint32_t wmax = 0;
         for (uint32_t k = 0; k < P.ntile; ++k) wmax = std::max(wmax, P.tw[k]);
         hipLaunchKernelGGL(k_pack_pc, dim3(cdiv((size_t)t * pc_ldv(wmax), 256), P.ntile), dim3(256), 0, s, a,
-                           rhs + (size_t)r0 * ld_rhs, ld_rhs, (uint32_t*)VT);
+                           rhs + (size_t)r0 * ld_rhs, ld_rhs, (uint32_t*)VT, g == 0 ? mono_p : nullptr, Mc, CL);
+      } else {
+        // the one-wave-per-tile rows (ldv words with M_r), Shoup constants and chain limbs
+        const size_t total = P.ntile * t * P.ldv;  // 32-bit words
+        hipLaunchKernelGGL(k_pack, dim3(cdiv(total, 256)), dim3(256), 0, s, P.t, Rg, P.RT, P.ntile, P.ldv,
+                           rhs + (size_t)r0 * ld_rhs, ld_rhs, Mc, (uint32_t*)VT, mono, mono_p, CL, M);
       }
-      // the one-wave-per-tile rows (ldv words with M_r), Shoup constants and chain limbs
-      const size_t total = std::max<size_t>(P.pc ? 0 : P.ntile * t * P.ldv, t);  // 32-bit words
-      hipLaunchKernelGGL(k_pack, dim3(cdiv(total, 256)), dim3(256), 0, s, P.t, Rg, P.RT, P.pc ? 0 : P.ntile, P.ldv,
-                         rhs + (size_t)r0 * ld_rhs, ld_rhs, Mc, (uint32_t*)VT, mono, mono_p, CL, M);
     }
     if (g == 0) {
       {
@@ -650,7 +659,7 @@ hipError_t vsolve_leaf(const zr_mod& M, uint32_t t, uint32_t R1, bool sums, uint
     {
       TimedLaunch tl("vs_pack", s);
       hipLaunchKernelGGL(k_pack_pc, dim3(cdiv((size_t)t * pc_ldv(wmax), 256), P.ntile), dim3(256), 0, s, a,
-                         F + (size_t)r0 * t, (size_t)t, (uint32_t*)VT);
+                         F + (size_t)r0 * t, (size_t)t, (uint32_t*)VT, (uint64_t*)nullptr, leafM, CL);
     }
     {
       TimedLaunch tl("vs_dots", s);
@@ -835,10 +844,57 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_apply(uint32_t n, const u
   }
 }
 
+// the whole scan in one workgroup, kScanOnePer consecutive counts per thread and turn
+constexpr int kScanOne = 1024, kScanOnePer = 8;
+constexpr uint32_t kScanOneMax = 2 * kScanOne * kScanOnePer;
+__global__ void __launch_bounds__(kScanOne) k_scan_one(uint32_t n, const uint32_t* __restrict__ cnt,
+                                                       uint32_t* __restrict__ off) {
+  __shared__ uint32_t wsum[kScanOne / 64];
+  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t carry = 0;
+  for (uint32_t b0 = 0; b0 < n; b0 += kScanOne * kScanOnePer) {
+    const uint32_t base = b0 + threadIdx.x * kScanOnePer;
+    uint32_t loc[kScanOnePer], v = 0;
+#pragma unroll
+    for (int e = 0; e < kScanOnePer; ++e) {
+      loc[e] = base + e < n ? cnt[base + e] : 0;
+      v += loc[e];
+    }
+    uint32_t incl = v;
+#pragma unroll
+    for (uint32_t d = 1; d < 64; d <<= 1) {
+      const uint32_t u = __shfl_up(incl, d);
+      if (lane >= d) incl += u;
+    }
+    if (lane == 63) wsum[wave] = incl;
+    __syncthreads();
+    uint32_t ex = carry + incl - v, total = 0;
+    for (uint32_t w = 0; w < kScanOne / 64; ++w) {
+      if (w < wave) ex += wsum[w];
+      total += wsum[w];
+    }
+    carry += total;
+#pragma unroll
+    for (int e = 0; e < kScanOnePer; ++e) {
+      if (base + e < n) off[base + e] = ex;
+      ex += loc[e];
+    }
+    __syncthreads();  // wsum is read before the next turn writes it
+  }
+  if (threadIdx.x == 0) off[n] = carry;
+}
+
 size_t scan_tmp_words(uint32_t n) { return cdiv(std::max<uint32_t>(n, 1), kScanBlock) + 1; }
 
 hipError_t exclusive_scan(uint32_t n, const uint32_t* cnt, uint32_t* off, uint32_t* tmp, hipStream_t s) {
   TimedLaunch tl("scan", s);
+  // Up to two turns of one workgroup beat the three launches, besides the two launches
+  // saved (kernel time at 3 000 counts 10.5 -> 3.6 us, 10^4 10.0 -> 7.2, 16 000
+  // 10.7 -> 8.7); at four turns they do not (32 000: 10.5 -> 14.6).
+  if (n <= kScanOneMax) {
+    hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(kScanOne), 0, s, n, cnt, off);
+    return hipGetLastError();
+  }
   const uint32_t nb = cdiv(std::max<uint32_t>(n, 1), kScanBlock);
   hipLaunchKernelGGL(k_scan_sums, dim3(nb), dim3(kScanThreads), 0, s, n, cnt, tmp);
   hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kScanThreads), 0, s, nb, tmp, off + n);
