@@ -9,11 +9,13 @@ terms with uniform distinct exponents, coefficients uniform mod a seeded
 63-bit prime (hidden-polynomial seed 3, schedule seed 1003).  One step =
 stage 8 from the stage-7 result f(x_1..x_7, c_8): one transposed Vandermonde
 system of 5*10^5 unknowns with 40 right-hand sides (master polynomial,
-synthetic-division dot products, inverse and scaling), the Newton lift of
-every term over 41 nodes, the expansion into the final skeleton, and the two
-probe checks.  The black box's samples are computed once on the device,
-recorded and replayed (a device-to-device copy per call) inside the timed
-region.
+dot products, inverse and scaling), the Newton lift of every term over 41
+nodes, the expansion into the final skeleton, and the two probe checks.  The
+solve runs through a subproduct tree; the rate is quoted over the quadratic
+algorithm's products all the same, so that it stays comparable
+(``mulmods_counted``), and ``roofline`` counts what is performed.  The black
+box's samples are computed once on the device, recorded and replayed (a
+device-to-device copy per call) inside the timed region.
 
 Further legs, reported under their own keys: the n = 6, t = 10^4 whole
 reconstruction; 4096 batched reconstructions against one at a time; served
@@ -47,11 +49,9 @@ CU, SIMD, LANES, CLOCK_GHZ = 256, 4, 16, 2.4
 MUL32_PEAK_TOPS = CU * SIMD * LANES * CLOCK_GHZ * 1e9 / 1e12
 MUL32_PER_MULMOD = 4
 
-# HBM bytes per launch of the dominant solve kernel on the headline workload,
-# from rocprofv3 FETCH_SIZE / WRITE_SIZE scaled by the copy-probe calibration
-# (profiles/k_vs_dots_pc_n8_d40_t5e5_hbm_counters.md).  Valid only for the
-# kernel sources the counters were taken on (None: not measured for them).
-DOTS_TRAFFIC = {"sources_sha16": "e1ba96d12974ac06", "bytes_per_launch": 7713177498}
+# The subproduct tree's transforms: five primes, and three 32x32-bit multiplies per
+# Montgomery product.  Systems it takes (csrc/tree.hpp) and rows of its leaves.
+TREE_PRIMES, MUL32_PER_MONT, TREE_LEAF_LOG, TREE_SUMS_MIN_T = 5, 3, 8, 32768
 
 HEADLINE_STAGE = 8  # the last variable of the n = 8 workload
 
@@ -64,20 +64,31 @@ def _system_sizes(w):
     return [int(len(np.unique(e[:, :k], axis=0))) for k in range(1, e.shape[1])]
 
 
-def _dots_work(c) -> int:
-    """Algorithmic modular products of the solves' dot-product passes: the R t^2
-    products and the t(t-1) chain steps per system (the denominators m_l M'(m_l)
-    come from the chain pass, not from this one)."""
-    return c["dot_products"] + c["chain_steps"]
+def _tree_applies(t, R):
+    """Whether a system of t unknowns and R right-hand sides goes through the tree
+    (the rule of csrc/tree.hpp, for the producer/consumer variant)."""
+    return t >= 5500 or (t > 3072 and R >= 8) or (t > 2560 and R > 36)
 
 
-def _dots_sources_sha16() -> str:
-    import hashlib
-    h = hashlib.sha256()
-    for f in ("field.hpp", "kernels_dev.hpp", "kernels.hip"):
-        with open(os.path.join(ROOT, "paper_2505_24256_amd", "csrc", f), "rb") as fh:
-            h.update(fh.read())
-    return h.hexdigest()[:16]
+def _dots_done(t, R, tree):
+    """Modular products that the dot-product pass of one system performs: R t^2 and
+    the t(t-1) chain steps, or those of the tree's leaf blocks of 256 rows (with
+    the power sums as one more series from 32 768 unknowns on)."""
+    if not tree:
+        return R * t * t + t * (t - 1)
+    leaf = 1 << TREE_LEAF_LOG
+    return (R + (1 if t >= TREE_SUMS_MIN_T else 0) + 1) * leaf * t
+
+
+def _tree_down_mul32(t, R):
+    """32x32-bit multiplies of the descent: per level of nodes of N = 2^k rows and per
+    series, one forward and two inverse transforms (k/2 Montgomery products a point
+    each) and two pointwise products, modulo five primes.  Padding, the Chinese
+    remainder and the reductions are not counted."""
+    series = R + (1 if t >= TREE_SUMS_MIN_T else 0)
+    top = max(1, t - 1).bit_length()
+    per_point = sum(1.5 * k + 2 for k in range(TREE_LEAF_LOG + 1, top + 1))
+    return t * series * TREE_PRIMES * per_point * MUL32_PER_MONT
 
 
 class CachingBox:
@@ -179,17 +190,11 @@ def batched_vs_plain(zr, synth, args, stream):
     zr.timing(False)
     breakdown = {}
     for name in ("batch_master", "batch_pack", "batch_chain", "batch_dots", "batch_finish", "batch_newton",
-                 "batch_expand", "master", "vs_pack", "vs_chain", "vs_scan", "vs_dots", "vs_finish"):
+                 "batch_expand", "master", "vs_pack", "vs_chain", "vs_scan", "vs_dots", "vs_finish",
+                 "tree_up", "tree_sums", "tree_down"):
         k, ms = zr.timing_get(name)
         if k:
             breakdown[name] = {"launches": k, "ms_total": round(ms, 2)}
-    # the persistent dot-product passes of the timed run against their work
-    # (dot products and chains of q of every system, 4 32-bit multiplies each)
-    solve_kernel = None
-    if "batch_dots" in breakdown and breakdown["batch_dots"]["ms_total"] > 0:
-        tops = 4.0 * _dots_work(cnt) / (breakdown["batch_dots"]["ms_total"] * 1e-3) / 1e12
-        solve_kernel = {"kernel": "k_b_dots_pc", "achieved_TOPs": round(tops, 3),
-                        "frac_of_derived_peak": round(tops / MUL32_PEAK_TOPS, 4)}
     _progress(f"batched {times}, with graphs {tg:.3f}; plain one at a time")
     # plain, one at a time, same recordings
     for r in recs:
@@ -219,7 +224,6 @@ def batched_vs_plain(zr, synth, args, stream):
         "speedup": round(tp / tb, 3), "mulmods": cnt["mulmods"], "bit_exact": bool(exact),
         "band_choices": tuned, "setup_seconds": {"generate": round(t_gen, 1), "record": round(t_rec, 1)},
         "timed_run": {"seconds": round(t_timed, 3), "per_kernel": breakdown},
-        "solve_kernel": solve_kernel,
     }
 
 
@@ -365,8 +369,8 @@ def headline(zr, synth, args, stream):
     torch.cuda.synchronize()
     zr.timing(False)
     kernels = {}
-    for name in ("mono", "master", "vs_pack", "vs_chain", "vs_scan", "vs_dots", "vs_finish", "newton", "scan",
-                 "expand"):
+    for name in ("mono", "master", "vs_pack", "vs_chain", "vs_scan", "vs_dots", "vs_finish", "tree_up", "tree_sums",
+                 "tree_down", "newton", "scan", "expand"):
         n, ms = zr.timing_get(name)
         if n:
             kernels[name] = {"launches": n, "ms_total": round(ms, 3)}
@@ -419,14 +423,17 @@ def config2_leg(zr, synth, args, stream):
     exact = exact and bool(np.array_equal(e, w.hidden.exps) and np.array_equal(c, w.hidden.coefs))
     n_dots, ms_dots = zr.timing_get("vs_dots")
     steps = args.config2_steps
-    alu = _dots_work(cnt) * steps * MUL32_PER_MULMOD / (ms_dots / 1e3) / 1e12 if ms_dots else 0.0
+    R = int(w.deg[0])
+    pc = args.solve_variant == "producer_consumer"
+    done = sum(_dots_done(t, R, pc and _tree_applies(t, R)) for t in _system_sizes(w))
+    alu = done * steps * MUL32_PER_MULMOD / (ms_dots / 1e3) / 1e12 if ms_dots else 0.0
     return {"workload": "plain polynomial Zippel, whole reconstruction, n=6, per-variable degree<=30, t=10^4",
             "system_sizes": _system_sizes(w), "right_hand_sides": int(w.deg[0]),
             "mulmod_per_s": round(cnt["mulmods"] * steps / el, 1), "ms_per_reconstruction": round(el / steps * 1e3, 3),
             "reconstructions_per_s": round(steps / el, 3),
             "latency_ms": {"p50": round(statistics.median(lat) * 1e3, 3),
                            "p99": round(float(np.percentile(lat, 99)) * 1e3, 3)},
-            "solve_kernel": {"kernel": "k_vs_dots_pc", "achieved_TOPs": round(alu, 3),
+            "solve_kernel": {"kernel": "dot-product passes, over the products they perform", "achieved_TOPs": round(alu, 3),
                              "frac_of_derived_peak": round(alu / MUL32_PEAK_TOPS, 4),
                              "avg_launch_ms": round(ms_dots / n_dots, 4) if n_dots else None},
             "mulmods_per_reconstruction": cnt["mulmods"], "steps": steps, "bit_exact": exact}
@@ -486,9 +493,8 @@ def multi_expression_leg(zr, synth, args, stream):
     cm = zr.last_counters()
     exact = exact and all(np.array_equal(r[0], h.exps) and np.array_equal(r[1], h.coefs) for r, h in zip(res, polys))
     steps = max(1, args.multi_steps)
-    alu_m = _dots_work(cm) * steps * MUL32_PER_MULMOD / (ms_dots / 1e3) / 1e12 if ms_dots else 0.0
     # the same expressions one at a time
-    sep_s, sep_mul, sep_solve, sep_ms = 0.0, 0, 0, 0.0
+    sep_s, sep_mul, sep_ms = 0.0, 0, 0.0
     for h, d in zip(polys, dg):
         r1 = zr.Recorder(synth.DeviceBlackBox(h, nthreads=args.cpu_threads))
         e1, c1 = zr.reconstruct(p, d, r1, sched=sched, stream=stream)
@@ -502,17 +508,15 @@ def multi_expression_leg(zr, synth, args, stream):
         c = zr.last_counters()
         sep_s += t1
         sep_mul += c["mulmods"]
-        sep_solve += _dots_work(c)
         r1.close()
-    alu_s = sep_solve * MUL32_PER_MULMOD / (sep_ms / 1e3) / 1e12 if sep_ms else 0.0
     rec.close()
     return {"workload": "8 expressions sampled together, n=6, degree bounds 8 in x_1..x_5 and 8/8/7/7/6/6/5/5 in x_6, "
                         f"each 99% of a common {t}-term set within its bounds plus 0.5% own terms",
             "terms": [int(h.nterms) for h in polys],
             "together": {"seconds": round(tm, 4), "mulmods": cm["mulmods"], "max_system": cm["max_t"],
-                         "solve_kernel_TOPs": round(alu_m, 3), "frac_of_derived_peak": round(alu_m / MUL32_PEAK_TOPS, 4)},
-            "separately": {"seconds": round(sep_s, 4), "mulmods": sep_mul, "solve_kernel_TOPs": round(alu_s, 3),
-                           "frac_of_derived_peak": round(alu_s / MUL32_PEAK_TOPS, 4)},
+                         "dot_product_pass_ms": round(ms_dots / steps, 3)},
+            "separately": {"seconds": round(sep_s, 4), "mulmods": sep_mul,
+                           "dot_product_pass_ms": round(sep_ms, 3)},
             "speedup": round(sep_s / tm, 3) if tm else None, "bit_exact": bool(exact)}
 
 
@@ -541,7 +545,8 @@ def multiprime_leg(zr, synth, args, stream):
     zr.timing_reset()
     _replayed(zr, rec, run, 1)
     zr.timing(False)
-    per = {k: round(zr.timing_get(k)[1], 3) for k in ("mp_corr", "mp_eval", "mp_crt_rr", "vs_dots", "master")}
+    per = {k: round(zr.timing_get(k)[1], 3) for k in ("mp_corr", "mp_eval", "mp_crt_rr", "vs_dots", "master", "tree_up", "tree_sums",
+                                                          "tree_down")}
     exact = exact and bool(np.array_equal(e, q.exps) and fr == list(zip(q.num, q.den)))
     # the first prime alone
     r0 = zr.Recorder(synth.DeviceBlackBox(q.mod(primes[0]), nthreads=args.cpu_threads))
@@ -594,8 +599,8 @@ def cpu_baseline(zr, synth, args, stream, W_step):
     division and dot products, inverse and scaling; unsigned __int128 products
     reduced with %) on a bounded sample of the headline's operation mix: one
     system of t = 2*10^4 random distinct monomial values with 40 right-hand
-    sides.  Its cost grows as t^2 like the headline's, so its mulmod/s is
-    the comparable rate; the full step's oracle time is extrapolated from it."""
+    sides.  The oracle's cost grows as t^2 and it performs every product counted;
+    its time for the full step is extrapolated from this rate."""
     import oracle
     nthr = max(1, min(args.cpu_threads, os.cpu_count() or 1))
     t, R = args.cpu_sample_t, 40
@@ -613,7 +618,7 @@ def cpu_baseline(zr, synth, args, stream, W_step):
     return {"value": round(rate, 1), "unit": "mulmod/s", "cores": nthr, "kind": "oracle",
             "sample": f"the oracle's transposed Vandermonde solve of one t={t}, R={R} system with random distinct "
                       "monomial values (the headline step's operation mix at a size the oracle finishes in seconds; "
-                      "cost grows as t^2 in both); unsigned __int128 products reduced with %, OpenMP over rows",
+                      "its cost grows as t^2); unsigned __int128 products reduced with %, OpenMP over rows",
             "seconds": round(tcpu, 2), "matches_gpu": bool(st == 0 and np.array_equal(got, want)),
             "extrapolated_step_seconds": round(W_step / rate, 1)}
 
@@ -671,25 +676,35 @@ def main():
     mulmods = cnt["mulmods"] * steps
     value = mulmods / elapsed
     n_dots, ms_dots = H["n_dots"], H["ms_dots"]
-    solve_alg = _dots_work(cnt) * steps               # R t^2 + t (t-1): what the dot-product pass computes
-    achieved_mulmod_s = solve_alg / (ms_dots / 1e3) if ms_dots else 0.0
-    alu = achieved_mulmod_s * MUL32_PER_MULMOD / 1e12
-    traffic = (DOTS_TRAFFIC["bytes_per_launch"]
-               if DOTS_TRAFFIC["sources_sha16"] == _dots_sources_sha16() and args.solve_variant == "producer_consumer"
-               else None)
+    tree = args.solve_variant == "producer_consumer" and _tree_applies(t_sys, R)
+    dots_tops = (MUL32_PER_MULMOD * _dots_done(t_sys, R, tree) * steps / (ms_dots / 1e3) / 1e12) if ms_dots else 0.0
+    down = H["kernels"].get("tree_down") if tree else None
+    # the kernels that take most of the step: the tree's descent (events of the warm-up
+    # steps), or the dot-product pass (events of the timed steps)
+    if down:
+        alu = _tree_down_mul32(t_sys, R) * args.warmup / (down["ms_total"] / 1e3) / 1e12
+    else:
+        alu = dots_tops
     # measured ceiling of the 32x32->64-bit multiply: the v_mad_u64_u32 probe
     # (independent streams at full occupancy), run here on the same GPU
     mad_ms, mad_ops = zr.microbench("mad_u64_u32", blocks=2048, iters=131072)
     mad_peak = mad_ops / mad_ms / 1e9 if mad_ms > 0 else None
     roofline = {"bound": "alu", "achieved": round(alu, 3), "peak": round(MUL32_PEAK_TOPS, 3),
-                "unit": "TOP/s (32x32-bit multiplies; one 64x64-bit modular product or multiply-accumulate = 4)",
-                "frac": round(alu / MUL32_PEAK_TOPS, 4), "traffic": traffic,
-                "traffic_unit": "bytes per launch (HBM, rocprofv3 counters, calibrated)",
-                "kernel": "k_vs_dots_pc" if args.solve_variant == "producer_consumer" else "k_vs_dots",
-                "launches_per_step": n_dots // steps if steps else 0,
-                "avg_launch_ms": round(ms_dots / n_dots, 3) if n_dots else None,
-                "work_per_step": "4 (R t^2 + t (t-1)) 32x32-bit multiplies (the dot products and the chain of "
-                                 "q), t = %d, R = %d, over the step's launches (chunk groups of equal size)" % (t_sys, R),
+                "unit": "TOP/s (32x32-bit multiplies performed; a Montgomery product mod a 30-bit prime = 3, a 64x64-bit "
+                        "product of the dot products = 4)",
+                "frac": round(alu / MUL32_PEAK_TOPS, 4), "traffic": None,
+                "kernel": "descent of the subproduct tree (k_tree_col_fwd, k_tree_descend, k_tree_col_inv, k_tree_crt)"
+                          if down else "dot-product pass",
+                "ms_per_step": (round(down["ms_total"] / args.warmup, 3) if down
+                                else round(ms_dots / steps, 3) if steps else None),
+                "work_per_step": "3 multiplies for each Montgomery product of one forward and two inverse transforms "
+                                 "and two pointwise products per level, series and prime, t = %d, R = %d; padding, "
+                                 "Chinese remainder and reductions left out" % (t_sys, R) if down else
+                                 "4 (R t^2 + t (t-1)) 32x32-bit multiplies, t = %d, R = %d" % (t_sys, R),
+                "dot_product_pass": {"achieved": round(dots_tops, 3),
+                                     "frac": round(dots_tops / MUL32_PEAK_TOPS, 4),
+                                     "launches_per_step": n_dots // steps if steps else 0,
+                                     "avg_launch_ms": round(ms_dots / n_dots, 3) if n_dots else None},
                 "measured_mul32_peak": {
                     "value": round(mad_peak, 3) if mad_peak else None, "unit": "TOP/s",
                     "probe": "v_mad_u64_u32, 8 independent chains per lane, 2048 x 256 threads, 131072 iterations "
@@ -738,6 +753,10 @@ def main():
                        "p99": round(float(np.percentile(H["lat"], 99)) * 1e3, 3)},
         "bit_exact": H["exact"],
         "mulmods_per_step": cnt["mulmods"],
+        "mulmods_counted": "products of the quadratic algorithm for this workload, a fixed number: R t^2 + 2t(t-1) + "
+                           "t(t-1)/2 + t(R+3) for the solve and t D (D+1) for the lift.  The subproduct tree gets the "
+                           "same values with far fewer products, so value compares builds on this workload and is no "
+                           "rate of the hardware (it may exceed the multipliers' peak); roofline counts what is performed",
         "roofline": roofline,
         "cpu_baseline": cpu,
         "kernels_warmup": {"steps": args.warmup, "per_kernel": H["kernels"]},
