@@ -592,8 +592,13 @@ LeafPlan leaf_plan(uint32_t t, uint32_t R, bool sums) {
     for (uint32_t k = 0; k < P.ntile; ++k) P.tw[k] = P.RT;
   for (uint32_t k = 0; k < P.ntile; ++k) q.words += pc_ldv(P.tw[k]);
   P.vt32 = (size_t)q.words * t;
-  // chunks of the denominators' sums: about 1024 workgroups, at least 128 steps each
-  q.S = std::max<uint32_t>(1, std::min<uint32_t>(t / 128, cdiv(1024, cdiv(t, 256))));
+  // Chunks of the denominators' sums: at least 128 steps each, and as many as fill whole
+  // rounds of the three workgroups (148 VGPRs) that a CU holds, one round below 16 384 rows and
+  // two above.  About 1024 workgroups left a second round nearly empty (with the finish,
+  // which reads a partial sum per chunk: t = 9 997 79 -> 68 us, 75 with two rounds;
+  // t = 20 011 220 -> 181 us, 190 with one; t = 32 000 468 -> 402 us, 416 with one).
+  const uint32_t wgs = 3 * device_cus() * (t < 16384 ? 1 : 2);
+  q.S = std::max<uint32_t>(1, std::min<uint32_t>(t / 128, wgs / cdiv(t, 256)));
   q.L = cdiv(t, q.S);
   q.S = sums ? 0 : cdiv(t, q.L);
   return q;
