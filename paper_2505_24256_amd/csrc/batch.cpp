@@ -79,7 +79,7 @@ static void reconstruct_batch(uint32_t n, const zr_params* params, zr_blackbox_f
   uint64_t p = 0;
   for (uint32_t i = 0; i < n; ++i) {
     try {
-      P[i].reset(new Params(&params[i], false));
+      P[i].reset(new Params(&params[i], false, p));  // one prime for all: tested once
       if (P[i]->first > 1) throw Error(ZR_EINVAL);  // resumption is a one-reconstruction feature
       st[i] = ZR_OK;
     } catch (const Error& e) {

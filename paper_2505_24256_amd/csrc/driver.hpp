@@ -55,7 +55,8 @@ struct Params {
   std::vector<uint32_t> deg, deg_den, need, nnodes;
   std::vector<uint64_t> y, anchor, nodes, probes;
   std::vector<size_t> node_off;
-  Params(const zr_params* P, bool balanced);
+  // known_prime: a p that this call (or the server it belongs to) has tested already, else 0
+  Params(const zr_params* P, bool balanced, uint64_t known_prime = 0);
   // anchor of variable v followed by its first count-1 nodes
   std::vector<uint64_t> node_list(uint32_t v, uint32_t count) const;
 };

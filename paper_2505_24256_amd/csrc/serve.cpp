@@ -759,7 +759,7 @@ zr_status zr_server_submit(zr_server* srv, const zr_params* params, int balanced
   Server& S = srv->impl;
   try {
     std::unique_ptr<Request> r(new Request());
-    r->P.reset(new Params(params, balanced != 0));
+    r->P.reset(new Params(params, balanced != 0, S.p));  // tested when the server was made
     if (r->P->p != S.p || r->P->first > 1) return ZR_EINVAL;
     r->balanced = balanced != 0;
     r->bb = bb;
