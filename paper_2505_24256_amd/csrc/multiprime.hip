@@ -2,7 +2,8 @@
 // ends with the recovery of rational numbers; §2.2: the multi-prime Zippel
 // routine).  With the term set fixed by the first prime, each further prime
 // needs the coefficients of t known monomials: one transposed Vandermonde
-// system with a single right-hand side, solved here in its correlation form,
+// system with a single right-hand side, below 5 500 terms (beyond, and up to 2^21,
+// the subproduct tree takes it) solved here in its correlation form,
 //   a_l = W(m_l) / (m_l M'(m_l)),   W(z) = sum_d w_d z^d,
 //   w_d = sum_{r=0}^{t-1-d} M_{r+d+1} v_{r+1}   (M_t = 1),
 // which is sum_r q_{l,r} v_{r+1} regrouped by powers of m_l (q_l = M/(z - m_l)).
