@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "batch.hpp"
+#include "capture.hpp"
 #include "driver.hpp"
 #include "field.hpp"
 #include "kernels.hpp"
@@ -998,7 +999,8 @@ void batched_solve(const zr_mod& M, const std::vector<SolveJob>& jobs_in, hipStr
   // which cannot be captured; the graph is then launched on the caller's)
   const bool graph = graphs_enabled();
   const hipStream_t ls = graph ? capture_stream() : s;
-  if (graph) check(hipStreamBeginCapture(ls, hipStreamCaptureModeThreadLocal));
+  StreamCapture capture;
+  if (graph) check(capture.begin(ls));
   {
     TimedLaunch tl("batch_master", ls);
     hipLaunchKernelGGL(k_b_master_small, dim3(small.total()), dim3(kMasterBase), 0, ls, M, n, P32(o_small), d_bm);
@@ -1049,7 +1051,7 @@ void batched_solve(const zr_mod& M, const std::vector<SolveJob>& jobs_in, hipStr
   }
   if (graph) {
     hipGraph_t g = nullptr;
-    const hipError_t e = hipStreamEndCapture(ls, &g);
+    const hipError_t e = capture.end(&g);
     if (e != hipSuccess || !g) throw Error(ZR_EDEVICE);
     hipGraphExec_t ge = nullptr;
     if (hipGraphInstantiate(&ge, g, nullptr, nullptr, 0) != hipSuccess) {
