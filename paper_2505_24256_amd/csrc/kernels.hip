@@ -707,11 +707,12 @@ __global__ void k_master_sum(zr_mod M, uint32_t t, uint32_t half, uint32_t nic, 
   if (g < t) master_sum_body(M, t, half, nic, g, cur, part, t, nxt, limbs_nxt);
 }
 
-size_t master_tmp_words(uint32_t t) {
+size_t master_tmp_words(uint32_t t, uint32_t block) {
   // t for the ping-pong level array, two limb arrays of t + 16 entries (two
-  // words each) and the chunk partials of the largest levels
+  // words each) and the chunk partials of the largest of the levels up to `block`
   uint32_t nic_max = 1;
-  for (uint32_t half = kMasterBase; half < t; half *= 2) nic_max = std::max(nic_max, cdiv(half, conv_ic(half, cdiv(t, 64))));
+  for (uint32_t half = kMasterBase; half < std::min(t, block); half *= 2)
+    nic_max = std::max(nic_max, cdiv(half, conv_ic(half, cdiv(t, 64))));
   return (size_t)t + 1 + 4 * ((size_t)t + 16) + (nic_max > 1 ? (size_t)nic_max * t : 0) + 64;
 }
 

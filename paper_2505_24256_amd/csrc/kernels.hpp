@@ -44,11 +44,12 @@ hipError_t vsolve(const zr_mod& M, const VsolvePlan& P, const uint64_t* mono, co
 
 // Master polynomial M(z) = prod_l (z - m_l): lower coefficients into Mc[t];
 // tmp is a scratch array of master_tmp_words(t).  Product tree, ceil(log2 t) levels.
-size_t master_tmp_words(uint32_t t);
+size_t master_tmp_words(uint32_t t, uint32_t block = ~0u);
 hipError_t master_poly(const zr_mod& M, uint32_t t, const uint64_t* mono, uint64_t* Mc, uint64_t* tmp,
                        hipStream_t s);
 
-// The tree's levels up to factors of degree `block` only (blocks of that many rows).
+// The tree's levels up to factors of degree `block` only (blocks of that many rows); tmp
+// holds master_tmp_words(t, block).
 hipError_t master_levels(const zr_mod& M, uint32_t t, uint32_t block, const uint64_t* mono, uint64_t* Mc, uint64_t* tmp,
                          hipStream_t s);
 

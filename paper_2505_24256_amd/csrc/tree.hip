@@ -875,7 +875,7 @@ void tree_solve(const zr_mod& M, uint32_t t, uint32_t R, const uint64_t* mono, c
   T.sys.push_back(y);
   tree_prepare(T, M, R, sums, A, s);
   // leaf polynomials by the quadratic product tree
-  uint64_t* tmp = A.alloc<uint64_t>(master_tmp_words(t));
+  uint64_t* tmp = A.alloc<uint64_t>(master_tmp_words(t, kLeaf));
   check(master_levels(M, t, kLeaf, mono, T.leafM, tmp, s));
   tree_launch(T, s);
   uint64_t* work = A.alloc<uint64_t>(vsolve_leaf_words(t, T.R1, sums));
