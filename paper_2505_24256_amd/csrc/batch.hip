@@ -42,8 +42,8 @@ struct BSolve {
   uint64_t* qstart;
   uint64_t* mL;
   uint64_t* winv;
-  const uint64_t* rhs;  // [R][ld]
-  uint64_t* out;        // [R - a.sums][ld]
+  uint64_t* rhs;         // [R - a.sums][ld], the unknowns in place
+  const uint64_t* head;  // series 0 where a.sums
   size_t ld;
   int32_t* status;
   uint32_t RT, ntile;
@@ -59,7 +59,7 @@ __global__ void k_b_pack(uint32_t n, const uint32_t* __restrict__ prefix, const 
   const size_t idx = (size_t)(blockIdx.x - prefix[s]) * blockDim.x + threadIdx.x;
   const uint32_t t = b.a.t;
   if (idx < (size_t)b.ntile * t * b.a.ldv)
-    ((uint32_t*)b.a.VT)[idx] = pack_word(idx, t, b.a.R, b.RT, b.a.ldv, b.rhs, b.ld, b.a.Mc);
+    ((uint32_t*)b.a.VT)[idx] = pack_word(idx, t, b.a.R, b.RT, b.a.ldv, b.rhs, b.ld, b.a.Mc, b.a.sums, b.head);
   if (idx < t) ((uint64_t*)b.a.mono_p)[idx] = zr_shoup_pre(b.a.M, b.a.mono[idx]);
 }
 
@@ -142,7 +142,7 @@ __global__ void k_b_scale(uint32_t n, const uint32_t* __restrict__ prefix, const
   const BSolve& b = sys[s];
   const uint32_t lb = blockIdx.x - prefix[s], nrb = cdiv(b.a.t, 256);
   const uint32_t l = (lb % nrb) * 256 + threadIdx.x;
-  if (l < b.a.t) vs_scale_body(b.a, l, b.a.sums + lb / nrb, b.winv, b.out, b.ld);
+  if (l < b.a.t) vs_scale_body(b.a, l, b.a.sums + lb / nrb, b.winv, b.rhs, b.ld);
 }
 
 // Small systems packed into shared wavefronts: lane i of item w handles row
@@ -760,24 +760,19 @@ static void split_large(const zr_mod& M, std::vector<SolveJob>& jobs, std::vecto
   for (size_t i0 = 0, i1; i0 < cand.size(); i0 = i1) {
     const uint32_t R = jobs[cand[i0]].R;
     double saved = 0;
-    size_t words = 0;
     for (i1 = i0; i1 < cand.size() && jobs[cand[i1]].R == R; ++i1) {
       const double t = jobs[cand[i1]].t;
       saved += t * R * (t - kTreeLeaf - kTreeLevelSteps * (tree_log_top(jobs[cand[i1]].t) - kTreeLeafLog));
-      words += (size_t)(R + 1) * jobs[cand[i1]].t;
     }
     if (saved < kBatchTreeMinWork) continue;
     trees.emplace_back();
     TreeRun& T = trees.back();
-    uint64_t* f = A.alloc<uint64_t>(words);
     for (size_t i = i0; i < i1; ++i) {
       const SolveJob& j = jobs[cand[i]];
       TreeSys y{};
       y.end = j.t;
-      y.rhs = j.rhs;
+      y.rhs = y.f = j.rhs;
       y.ld_rhs = y.ld = j.t;
-      y.f = f;
-      f += (size_t)(R + 1) * j.t;
       T.sys.push_back(y);
     }
     tree_prepare(T, M, R, true, A, s);
@@ -785,8 +780,8 @@ static void split_large(const zr_mod& M, std::vector<SolveJob>& jobs, std::vecto
       SolveJob& j = jobs[cand[i]];
       const TreeSys& y = T.sys[i - i0];
       for (uint32_t b = 0; b < j.t; b += kTreeLeaf)
-        leaves.push_back(SolveJob{std::min(kTreeLeaf, j.t - b), R + 1, j.mono + b, y.f + b, j.status, j.rhs + b, j.t,
-                                  T.leafM + y.off + b});
+        leaves.push_back(SolveJob{std::min(kTreeLeaf, j.t - b), R + 1, j.mono + b, j.rhs + b, j.status,
+                                  T.sums + y.off + b, j.t, T.leafM + y.off + b});
       j.t = 0;  // replaced
     }
   }
@@ -888,9 +883,9 @@ void batched_solve(const zr_mod& M, const std::vector<SolveJob>& jobs_in, hipStr
     b.a.hpart = part_base + b.hp_off;
     b.winv = A.alloc<uint64_t>(2 * t);
     b.rhs = jobs[i].rhs;
-    b.out = jobs[i].out ? jobs[i].out : jobs[i].rhs;
-    b.ld = jobs[i].out ? jobs[i].ld : t;
-    b.a.sums = jobs[i].out ? 1 : 0;
+    b.head = jobs[i].sums;
+    b.ld = jobs[i].sums ? jobs[i].ld : t;
+    b.a.sums = jobs[i].sums ? 1 : 0;
     b.status = jobs[i].status;
     b.RT = P.RT;
     b.ntile = P.ntile;

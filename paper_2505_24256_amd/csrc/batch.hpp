@@ -54,10 +54,10 @@ struct SolveJob {
   const uint64_t* mono;
   uint64_t* rhs;
   int32_t* status;
-  // leaf block of a larger system (tree.hpp), null in a caller's job: series rhs[R]
-  // at stride ld, the power sums first; unknowns of series 1.. into out at stride ld;
-  // master polynomial into Mc
-  uint64_t* out = nullptr;
+  // leaf block of a larger system (tree.hpp), null in a caller's job: series 0 of R is
+  // the power sums' sums[t], series 1.. stand in rhs at stride ld and become the
+  // unknowns there; master polynomial into Mc
+  const uint64_t* sums = nullptr;
   size_t ld = 0;
   uint64_t* Mc = nullptr;
 };

@@ -295,10 +295,11 @@ __global__ void k_pack(uint32_t t, uint32_t R, uint32_t RT, uint32_t ntile, uint
   if (idx < t) pack_row(M, idx, mono, mono_p, Mc, CL);
 }
 
-// Packed rows of the producer/consumer tiles (blockIdx.y = tile), widths tw; mono_p
-// (null: made already) and CL on the way.
-__global__ void k_pack_pc(VsArgs a, const uint64_t* __restrict__ rhs, size_t ld_rhs, uint32_t* __restrict__ VT,
-                          uint64_t* __restrict__ mono_p, const uint64_t* __restrict__ Mc, uint32_t* __restrict__ CL) {
+// Packed rows of the producer/consumer tiles (blockIdx.y = tile), widths tw (head: series 0
+// where a.sums); mono_p (null: made already) and CL on the way.
+__global__ void k_pack_pc(VsArgs a, const uint64_t* __restrict__ rhs, size_t ld_rhs, const uint64_t* __restrict__ head,
+                          uint32_t* __restrict__ VT, uint64_t* __restrict__ mono_p, const uint64_t* __restrict__ Mc,
+                          uint32_t* __restrict__ CL) {
   const uint32_t tile = blockIdx.y;
   uint32_t j0 = 0, off = 0, w = 0;
 #pragma unroll
@@ -314,7 +315,7 @@ __global__ void k_pack_pc(VsArgs a, const uint64_t* __restrict__ rhs, size_t ld_
   if (mono_p && tile == 0 && idx < a.t) pack_row(a.M, idx, a.mono, mono_p, Mc, CL);
   if (idx < (size_t)a.t * ldv)
     VT[(size_t)off * a.t + idx] =
-        pack_word_pc((uint32_t)(idx / ldv), (uint32_t)(idx % ldv), a.R, w, j0, rhs, ld_rhs);
+        pack_word_pc((uint32_t)(idx / ldv), (uint32_t)(idx % ldv), a.R, w, j0, rhs, ld_rhs, a.sums, head);
 }
 
 // Chain values B_c (WB, the chunks c < S-1) and partials D_c of m M'(m) (WD):
@@ -499,7 +500,8 @@ hipError_t vsolve(const zr_mod& M, const VsolvePlan& P, const uint64_t* mono, co
         uint32_t wmax = 0;
         for (uint32_t k = 0; k < P.ntile; ++k) wmax = std::max(wmax, P.tw[k]);
         hipLaunchKernelGGL(k_pack_pc, dim3(cdiv((size_t)t * pc_ldv(wmax), 256), P.ntile), dim3(256), 0, s, a,
-                           rhs + (size_t)r0 * ld_rhs, ld_rhs, (uint32_t*)VT, g == 0 ? mono_p : nullptr, Mc, CL);
+                           rhs + (size_t)r0 * ld_rhs, ld_rhs, (const uint64_t*)nullptr, (uint32_t*)VT,
+                           g == 0 ? mono_p : nullptr, Mc, CL);
       } else {
         // the one-wave-per-tile rows (ldv words with M_r), Shoup constants and chain limbs
         const size_t total = P.ntile * t * P.ldv;  // 32-bit words
@@ -553,7 +555,7 @@ hipError_t vsolve(const zr_mod& M, const VsolvePlan& P, const uint64_t* mono, co
 // ============================================================================
 // Leaf blocks of the subproduct tree: every block of `block` rows is a system
 // of its own, whose samples and master polynomial stand at the block's indices
-// of F and leafM, so the producer/consumer pass runs over them as it runs over
+// of out and leafM, so the producer/consumer pass runs over them as it runs over
 // one system, each workgroup over the steps of its own block.
 // ============================================================================
 
@@ -611,10 +613,10 @@ size_t vsolve_leaf_words(uint32_t t, uint32_t R1, bool sums) {
   return vsolve_rhs_words(q.P) + (size_t)t * (1 + q.P.Rg + q.S + 2 + 3) + 64;
 }
 
-hipError_t vsolve_leaf(const zr_mod& M, uint32_t t, uint32_t R1, bool sums, uint32_t block, const uint64_t* mono,
-                       const uint64_t* leafM, const uint64_t* rootM, const uint64_t* F, uint64_t* out, size_t ld_out,
+hipError_t vsolve_leaf(const zr_mod& M, uint32_t t, uint32_t R1, const uint64_t* sums, uint32_t block,
+                       const uint64_t* mono, const uint64_t* leafM, const uint64_t* rootM, uint64_t* out, size_t ld_out,
                        uint64_t* work, int32_t* status, hipStream_t s) {
-  const LeafPlan q = leaf_plan(t, R1, sums);
+  const LeafPlan q = leaf_plan(t, R1, sums != nullptr);
   const VsolvePlan& P = q.P;
   uint64_t* VT = work;
   uint64_t* mono_p = VT + vsolve_rhs_words(P);
@@ -643,8 +645,8 @@ hipError_t vsolve_leaf(const zr_mod& M, uint32_t t, uint32_t R1, bool sums, uint
   a.dpart = dpart;
   {
     TimedLaunch tl("vs_chain", s);
-    hipLaunchKernelGGL(k_pack, dim3(cdiv(t, 256)), dim3(256), 0, s, t, R1, 1u, 0u, 2u, F, (size_t)t, rootM, (uint32_t*)VT,
-                       mono, mono_p, CL, M);
+    hipLaunchKernelGGL(k_pack, dim3(cdiv(t, 256)), dim3(256), 0, s, t, R1, 1u, 0u, 2u, (const uint64_t*)out, ld_out, rootM,
+                       (uint32_t*)VT, mono, mono_p, CL, M);
     if (!sums) {
       hipLaunchKernelGGL(k_vs_chain_d, dim3(cdiv(t, 256), q.S), dim3(256), 0, s, a);
       hipLaunchKernelGGL(k_vs_delta, dim3(cdiv(t, 64)), dim3(64), 0, s, a, (const uint64_t*)nullptr,
@@ -661,10 +663,12 @@ hipError_t vsolve_leaf(const zr_mod& M, uint32_t t, uint32_t R1, bool sums, uint
   for (uint32_t g = 0, r0 = 0; g < P.ng; ++g) {
     const uint32_t Rg = R1 / P.ng + (g < R1 % P.ng ? 1 : 0);
     a.R = Rg;
+    a.sums = sums && g == 0 ? 1 : 0;  // series 0 holds the denominators
+    uint64_t* og = out + (size_t)(r0 - (sums && g > 0 ? 1 : 0)) * ld_out;
     {
       TimedLaunch tl("vs_pack", s);
       hipLaunchKernelGGL(k_pack_pc, dim3(cdiv((size_t)t * pc_ldv(wmax), 256), P.ntile), dim3(256), 0, s, a,
-                         F + (size_t)r0 * t, (size_t)t, (uint32_t*)VT, (uint64_t*)nullptr, leafM, CL);
+                         (const uint64_t*)og, ld_out, sums, (uint32_t*)VT, (uint64_t*)nullptr, leafM, CL);
     }
     {
       TimedLaunch tl("vs_dots", s);
@@ -672,14 +676,11 @@ hipError_t vsolve_leaf(const zr_mod& M, uint32_t t, uint32_t R1, bool sums, uint
     }
     {
       TimedLaunch tl("vs_finish", s);
-      a.sums = sums && g == 0 ? 1 : 0;  // series 0 holds the denominators
       if (a.sums)
         hipLaunchKernelGGL(k_vs_delta, dim3(cdiv(t, 64)), dim3(64), 0, s, a, (const uint64_t*)nullptr,
                            winv, status);
-      const uint32_t o = r0 - (sums && g > 0 ? 1 : 0);
       if (Rg > a.sums)
-        hipLaunchKernelGGL(k_vs_scale, dim3(cdiv(t, 256), Rg - a.sums), dim3(256), 0, s, a, winv, out + (size_t)o * ld_out,
-                           ld_out);
+        hipLaunchKernelGGL(k_vs_scale, dim3(cdiv(t, 256), Rg - a.sums), dim3(256), 0, s, a, winv, og, ld_out);
     }
     r0 += Rg;
   }

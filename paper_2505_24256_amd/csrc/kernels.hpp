@@ -54,14 +54,14 @@ hipError_t master_levels(const zr_mod& M, uint32_t t, uint32_t block, const uint
                          hipStream_t s);
 
 // Leaf step of the tree solve: block u of `block` rows (a multiple of 64) is a
-// system with samples F[j][block u ..] (R1 series of t words) and master
-// polynomial leafM[block u ..].  Dot products per block, the denominators m M'(m)
-// of the whole system (rootM its polynomial), and the scaling into out.  sums:
-// series 0 holds the power sums, so its values are the denominators and the
-// right-hand sides are series 1..R1-1; else the chain pass makes them.
+// system with samples out[j][block u ..] and master polynomial leafM[block u ..].  Dot
+// products per block, the denominators m M'(m) of the whole system (rootM its
+// polynomial), and the unknowns into out, in place of the samples.  sums [t], if
+// given: the blocks' power sums, one more series (R1 counts it) whose values are the
+// denominators; else the chain pass makes them.
 size_t vsolve_leaf_words(uint32_t t, uint32_t R1, bool sums);
-hipError_t vsolve_leaf(const zr_mod& M, uint32_t t, uint32_t R1, bool sums, uint32_t block, const uint64_t* mono,
-                       const uint64_t* leafM, const uint64_t* rootM, const uint64_t* F, uint64_t* out, size_t ld_out,
+hipError_t vsolve_leaf(const zr_mod& M, uint32_t t, uint32_t R1, const uint64_t* sums, uint32_t block,
+                       const uint64_t* mono, const uint64_t* leafM, const uint64_t* rootM, uint64_t* out, size_t ld_out,
                        uint64_t* work, int32_t* status, hipStream_t s);
 
 // ---- Newton lift (eq. 1) and skeleton expansion ------------------------------

@@ -41,8 +41,9 @@ struct VsArgs {
   // leaf blocks of the subproduct tree: rows [B u, B (u+1)) are
   // a system of their own, with master polynomial and samples at those indices
   uint32_t blk = 0;
-  // 1: series 0 are the power sums of the whole tree's system, so its values are the
-  // denominators m M'(m), and the right-hand sides are series 1..R-1
+  // 1: series 0 are the power sums of the whole tree's system (an array of its own,
+  // `head` where rows are packed), so its values are the denominators m M'(m), and the
+  // right-hand sides are series 1..R-1
   uint32_t sums = 0;
 };
 
@@ -54,10 +55,15 @@ __device__ __forceinline__ void chunk_range(uint32_t t, uint32_t L, uint32_t c, 
 // Packed right-hand sides, word idx of [ntile][t][ldv] (32-bit words): for
 // jj < RT the value v = v^(tile*RT + jj)_{r+1} as three limbs v & (2^22-1),
 // (v >> 22) & (2^22-1), v >> 44 at words 3jj..3jj+2; M_r at words 3RT, 3RT+1;
-// zero padding.
+// zero padding.  nh = 1: series 0 is head[t], series j right-hand side j - 1.
+__device__ __forceinline__ uint64_t series_value(uint32_t j, uint32_t r, const uint64_t* __restrict__ rhs, size_t ld_rhs,
+                                                 uint32_t nh, const uint64_t* __restrict__ head) {
+  return j < nh ? head[r] : rhs[(size_t)(j - nh) * ld_rhs + r];
+}
 __device__ __forceinline__ uint32_t pack_word(size_t idx, uint32_t t, uint32_t R, uint32_t RT, uint32_t ldv,
                                               const uint64_t* __restrict__ rhs, size_t ld_rhs,
-                                              const uint64_t* __restrict__ Mc) {
+                                              const uint64_t* __restrict__ Mc, uint32_t nh = 0,
+                                              const uint64_t* __restrict__ head = nullptr) {
   const uint32_t w = (uint32_t)(idx % ldv);
   const size_t rest = idx / ldv;
   const uint32_t r = (uint32_t)(rest % t), tile = (uint32_t)(rest / t);
@@ -65,7 +71,7 @@ __device__ __forceinline__ uint32_t pack_word(size_t idx, uint32_t t, uint32_t R
   if (w < 3 * RT) {
     const uint32_t jj = w / 3, limb = w % 3;
     const uint32_t j = tile * RT + jj;
-    const uint64_t v = j < R ? rhs[(size_t)j * ld_rhs + r] : 0;
+    const uint64_t v = j < R ? series_value(j, r, rhs, ld_rhs, nh, head) : 0;
     out = (uint32_t)((v >> (22 * limb)) & (limb < 2 ? 0x3FFFFFu : 0xFFFFFFFFu));
   } else if (w == 3 * RT) {
     out = (uint32_t)Mc[r];
@@ -79,10 +85,11 @@ __device__ __forceinline__ uint32_t pack_word(size_t idx, uint32_t t, uint32_t R
 // right-hand side is j0: the three 22-bit limbs of v^(j0+jj)_{r+1} at words
 // 3jj..3jj+2, zero beyond (and for right-hand sides past R).
 __device__ __forceinline__ uint32_t pack_word_pc(uint32_t r, uint32_t w, uint32_t R, uint32_t tw, uint32_t j0,
-                                                 const uint64_t* __restrict__ rhs, size_t ld_rhs) {
+                                                 const uint64_t* __restrict__ rhs, size_t ld_rhs, uint32_t nh,
+                                                 const uint64_t* __restrict__ head) {
   if (w >= 3 * tw) return 0;
   const uint32_t j = j0 + w / 3, limb = w % 3;
-  const uint64_t v = j < R ? rhs[(size_t)j * ld_rhs + r] : 0;
+  const uint64_t v = j < R ? series_value(j, r, rhs, ld_rhs, nh, head) : 0;
   return (uint32_t)((v >> (22 * limb)) & (limb < 2 ? 0x3FFFFFu : 0xFFFFFFFFu));
 }
 

@@ -141,7 +141,7 @@ struct Level {
   TreeSys one;         // the only system (sys null), or
   const TreeSys* sys;  // the systems, and the system of each leaf block
   const uint32_t* sys_of;
-  const uint64_t* sums;  // power sums, series 0 (null: none)
+  uint64_t* sums;        // power sums, series 0 at every level (null: none)
   const uint64_t* poly;  // children's polynomials
   uint64_t* pout;      // parents' polynomials
   uint32_t* X;         // column-transformed residues [prime][series or child][node N + s]
@@ -188,10 +188,8 @@ __device__ __forceinline__ uint64_t source_point(const Level& a, const TreeSys& 
   if constexpr (SRC == kSeries) {
     const uint32_t row = item * a.N + (a.N - 1 - s);
     const uint32_t jj = a.j0 + j;
-    const uint64_t* f;
-    if (a.logN != y.logTop) f = y.f + (size_t)jj * y.ld;
-    else if (a.sums) f = jj == 0 ? a.sums + y.off : y.rhs + (size_t)(jj - 1) * y.ld_rhs;
-    else f = y.rhs + (size_t)jj * y.ld_rhs;
+    const uint64_t* f = a.logN == y.logTop ? y.rhs + (size_t)jj * y.ld_rhs : y.f + (size_t)jj * y.ld;
+    if (a.sums && jj == 0) f = a.sums + y.off;
     return row < y.end ? f[row - y.off] : 0;
   } else if constexpr (SRC == kChild) {
     const uint32_t row = item * a.h, n = row < y.end ? std::min(a.h, y.end - row) : 0;
@@ -223,7 +221,9 @@ __device__ __forceinline__ void store_point(const Level& a, const TreeSys& y, co
                                             uint32_t node, uint32_t s, uint64_t v) {
   if constexpr (DST == kChildren) {
     const uint32_t row = node * a.N + side * a.h + (a.N - 1 - s);
-    if (row < y.end) y.f[(size_t)(a.j0 + j) * y.ld + (row - y.off)] = v;
+    const uint32_t jj = a.j0 + j;
+    uint64_t* f = a.sums && jj == 0 ? a.sums + y.off : y.f + (size_t)jj * y.ld;
+    if (row < y.end) f[row - y.off] = v;
   } else if constexpr (DST == kParent) {
     const uint32_t row = node * a.N + s;
     if (row >= y.end) return;
@@ -766,6 +766,10 @@ void tree_prepare(TreeRun& T, const zr_mod& M, uint32_t R, bool sums, DevArena& 
     y.end = T.V + t;
     y.logTop = tree_log_top(t);
     T.V += 1u << y.logTop;
+    if (sums) {  // series j is right-hand side j - 1
+      y.rhs -= y.ld_rhs;
+      y.f -= y.ld;
+    }
   }
   T.R1 = R + (sums ? 1 : 0);
   T.leafM = A.alloc<uint64_t>(T.V);
@@ -870,8 +874,8 @@ void tree_solve(const zr_mod& M, uint32_t t, uint32_t R, const uint64_t* mono, c
   y.end = t;
   y.rhs = rhs;
   y.ld_rhs = ld_rhs;
-  y.ld = t;
-  y.f = A.alloc<uint64_t>((size_t)(R + (sums ? 1 : 0)) * t);
+  y.f = out;  // read and packed before the unknowns are written
+  y.ld = ld_out;
   T.sys.push_back(y);
   tree_prepare(T, M, R, sums, A, s);
   // leaf polynomials by the quadratic product tree
@@ -879,7 +883,7 @@ void tree_solve(const zr_mod& M, uint32_t t, uint32_t R, const uint64_t* mono, c
   check(master_levels(M, t, kLeaf, mono, T.leafM, tmp, s));
   tree_launch(T, s);
   uint64_t* work = A.alloc<uint64_t>(vsolve_leaf_words(t, T.R1, sums));
-  check(vsolve_leaf(M, t, T.R1, sums, kLeaf, mono, T.leafM, T.poly, y.f, out, ld_out, work, status, s));
+  check(vsolve_leaf(M, t, T.R1, T.sums, kLeaf, mono, T.leafM, T.poly, out, ld_out, work, status, s));
 }
 
 }  // namespace zr

@@ -24,8 +24,8 @@ constexpr uint32_t kTreeLeafLog = 8;  // leaf blocks of 256 rows
 constexpr uint32_t kTreeLeaf = 1u << kTreeLeafLog;
 
 // One system: rows [off, end) of the common index space (off set by
-// tree_prepare; give off = 0, end = t), right-hand side j at rhs + j ld_rhs, series j
-// of the leaf blocks at f + j ld.
+// tree_prepare; give off = 0, end = t), right-hand side j at rhs + j ld_rhs, its series
+// at f + j ld from the top's children down to the leaf blocks (f may be rhs).
 struct TreeSys {
   uint32_t off, end, logTop, pad;
   const uint64_t* rhs;
@@ -53,7 +53,7 @@ struct TreeRun {
 void tree_prepare(TreeRun& T, const zr_mod& M, uint32_t R, bool sums, DevArena& A, hipStream_t s);
 // From the leaf blocks' polynomials in T.leafM (block b of a system at off + 256 b)
 // and the right-hand sides: the whole polynomials into T.poly and every leaf
-// block's series into f.
+// block's series into f (and, with power sums, into T.sums).
 void tree_launch(const TreeRun& T, hipStream_t s);
 
 }  // namespace zr

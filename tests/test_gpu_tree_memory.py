@@ -71,3 +71,31 @@ def test_one_system_leaves_out_the_quadratic_product_tree(zr):
     print(f"[gpu-test] one system: {got / 2**20:.0f} MiB taken, {need / 2**20:.0f} MiB needed", flush=True)
     assert int(st.item()) == 0
     assert got <= 2 * need
+
+
+def test_one_system_keeps_its_series_in_the_output(zr):
+    """Many right-hand sides: the workspace is the residues' 640 MB, the transforms and a
+    leaf pass of at most 63 right-hand sides, whatever their number."""
+    import torch
+    t, R = 4_100, 40_000
+    mono, rhs = _random(t, R, 2)
+    out = torch.empty_like(rhs)
+    st = torch.zeros(1, dtype=torch.int32, device="cuda")
+
+    def call(s):
+        assert zr.lib().zr_vandermonde_solve(P, t, R, mono.data_ptr(), rhs.data_ptr(), out.data_ptr(), st.data_ptr(),
+                                             s) == 0
+    got = _growth(call)
+    leaves = 8 * t * (10 * 8 + 63 + 32)  # packed rows (ten tiles' worth of 16 words), sums, denominators' chunks
+    need = (640 << 20) + _transforms(t) + leaves
+    print(f"[gpu-test] {R} right-hand sides: {got / 2**20:.0f} MiB taken, {need / 2**20:.0f} MiB needed, "
+          f"right-hand sides {8 * t * R / 2**20:.0f} MiB", flush=True)
+    assert int(st.item()) == 0
+    assert got <= 2 * need
+    # first, middle and last against the same columns alone
+    for j in (0, R // 2, R - 1):
+        one = torch.empty(t, dtype=torch.int64, device="cuda")
+        assert zr.lib().zr_vandermonde_solve(P, t, 1, mono.data_ptr(), rhs[j * t:(j + 1) * t].data_ptr(),
+                                             one.data_ptr(), st.data_ptr(), zr._stream(None)) == 0
+        torch.cuda.synchronize()
+        assert torch.equal(one, out[j * t:(j + 1) * t])
