@@ -744,8 +744,9 @@ constexpr double kBatchTreeMinWork = 3e9;
 // products of the quadratic pass.
 constexpr double kTreeLevelSteps = 190;
 
-// Large systems of a batch through one tree per right-hand-side count: the
-// system's job is replaced by one job per leaf block.
+// Large systems of a batch through one tree per right-hand-side count (several beyond
+// kTreeMaxRows rows), all in one workspace: the system's job is replaced by one job per
+// leaf block.
 static void split_large(const zr_mod& M, std::vector<SolveJob>& jobs, std::vector<TreeRun>& trees, DevArena& A,
                         hipStream_t s) {
   if (!vsolve_uses_pc()) return;
@@ -757,6 +758,7 @@ static void split_large(const zr_mod& M, std::vector<SolveJob>& jobs, std::vecto
     return tree_log_top(jobs[x].t) > tree_log_top(jobs[y].t);
   });
   std::vector<SolveJob> leaves;
+  std::vector<uint32_t> of;  // job of each system, in the trees' order
   for (size_t i0 = 0, i1; i0 < cand.size(); i0 = i1) {
     const uint32_t R = jobs[cand[i0]].R;
     double saved = 0;
@@ -765,26 +767,34 @@ static void split_large(const zr_mod& M, std::vector<SolveJob>& jobs, std::vecto
       saved += t * R * (t - kTreeLeaf - kTreeLevelSteps * (tree_log_top(jobs[cand[i1]].t) - kTreeLeafLog));
     }
     if (saved < kBatchTreeMinWork) continue;
-    trees.emplace_back();
-    TreeRun& T = trees.back();
+    size_t rows = 0;  // of the tree being filled
     for (size_t i = i0; i < i1; ++i) {
       const SolveJob& j = jobs[cand[i]];
+      const size_t v = (size_t)1 << tree_log_top(j.t);
+      if (i == i0 || rows + v > kTreeMaxRows) {
+        trees.emplace_back();
+        trees.back().R = R;
+        rows = 0;
+      }
+      rows += v;
       TreeSys y{};
       y.end = j.t;
       y.rhs = y.f = j.rhs;
       y.ld_rhs = y.ld = j.t;
-      T.sys.push_back(y);
+      trees.back().sys.push_back(y);
+      of.push_back(cand[i]);
     }
-    tree_prepare(T, M, R, true, A, s);
-    for (size_t i = i0; i < i1; ++i) {
-      SolveJob& j = jobs[cand[i]];
-      const TreeSys& y = T.sys[i - i0];
+  }
+  tree_prepare(trees, M, true, A, s);
+  size_t i = 0;
+  for (const TreeRun& T : trees)
+    for (const TreeSys& y : T.sys) {
+      SolveJob& j = jobs[of[i++]];
       for (uint32_t b = 0; b < j.t; b += kTreeLeaf)
-        leaves.push_back(SolveJob{std::min(kTreeLeaf, j.t - b), R + 1, j.mono + b, j.rhs + b, j.status,
+        leaves.push_back(SolveJob{std::min(kTreeLeaf, j.t - b), j.R + 1, j.mono + b, j.rhs + b, j.status,
                                   T.sums + y.off + b, j.t, T.leafM + y.off + b});
       j.t = 0;  // replaced
     }
-  }
   jobs.erase(std::remove_if(jobs.begin(), jobs.end(), [](const SolveJob& j) { return !j.t; }), jobs.end());
   jobs.insert(jobs.end(), leaves.begin(), leaves.end());
 }

@@ -752,57 +752,91 @@ uint32_t tree_log_top(uint32_t t) {
   return lg;
 }
 
-void tree_prepare(TreeRun& T, const zr_mod& M, uint32_t R, bool sums, DevArena& A, hipStream_t s) {
-  T.C.M = M;
-  uint64_t prod = 1 % M.p;
-  for (int j = 0; j < kNp; ++j) {
-    T.C.Qp[j] = prod;
-    prod = zr_mul(M, prod, kQ[j] % M.p);
+// Series of one group of R1, of nearly equal groups within kTreeResidueBytes: one
+// series' residues and its two products, five primes.
+static uint32_t group_size(size_t V, uint32_t R1) {
+  const uint32_t most =
+      (uint32_t)std::max<size_t>(1, std::min<size_t>(R1, kTreeResidueBytes / ((size_t)kNp * 4 * 3 * V)));
+  return cdiv(R1, cdiv(R1, most));
+}
+
+void TreeSpace::add(size_t V, uint32_t logTop, uint32_t R1, bool sums) {
+  const uint32_t group = group_size(V, R1);
+  poly = std::max(poly, 2 * V);
+  X = std::max(X, (size_t)std::max(2u, group) * V * kNp);
+  Y = std::max(Y, (size_t)2 * group * V * kNp);
+  K = std::max(K, (size_t)(logTop - kLeafLog) * 2 * V * kNp);
+  if (sums) {
+    g = std::max(g, 2 * V);
+    Ks = std::max(Ks, (size_t)2 * V * kNp);
   }
-  T.V = 0;
-  for (TreeSys& y : T.sys) {  // largest tops first: every offset is a multiple of its system's top
-    const uint32_t t = y.end - y.off;
-    y.off = T.V;
-    y.end = T.V + t;
-    y.logTop = tree_log_top(t);
-    T.V += 1u << y.logTop;
-    if (sums) {  // series j is right-hand side j - 1
-      y.rhs -= y.ld_rhs;
-      y.f -= y.ld;
+  const uint32_t lg = logTop + (sums ? 1 : 0);
+  if (lg > kRowLog) twLog = std::max(twLog, lg);
+}
+
+size_t TreeSpace::bytes() const { return 4 * (poly + g + X + Y + K + Ks + (twLog ? (size_t)2 * kNp << twLog : 0)); }
+
+void tree_prepare(std::vector<TreeRun>& trees, const zr_mod& M, bool sums, DevArena& A, hipStream_t s) {
+  if (trees.empty()) return;
+  TreeSpace S;
+  for (TreeRun& T : trees) {
+    T.V = 0;
+    for (TreeSys& y : T.sys) {  // largest tops first: every offset is a multiple of its system's top
+      const uint32_t t = y.end - y.off;
+      y.off = T.V;
+      y.end = T.V + t;
+      y.logTop = tree_log_top(t);
+      T.V += 1u << y.logTop;
+      if (sums) {  // series j is right-hand side j - 1
+        y.rhs -= y.ld_rhs;
+        y.f -= y.ld;
+      }
     }
+    T.R1 = T.R + (sums ? 1 : 0);
+    T.group = group_size(T.V, T.R1);
+    S.add(T.V, T.sys[0].logTop, T.R1, sums);
   }
-  T.R1 = R + (sums ? 1 : 0);
-  T.leafM = A.alloc<uint64_t>(T.V);
-  T.poly = A.alloc<uint64_t>(T.V);
-  T.sums = sums ? A.alloc<uint64_t>(T.V) : nullptr;
-  T.g = sums ? A.alloc<uint64_t>(T.V) : nullptr;
-  T.Ks = sums ? A.alloc<uint32_t>((size_t)2 * T.V * kNp) : nullptr;
-  // residue workspace: series in groups of at most 640 MB (t = 300 007, 41 series: 9.8 ms with
-  // 160 MB, which the last-level cache holds, 8.8 with 640, 9.0 with all at once: the
-  // launches' fill matters more)
-  const size_t per_series = (size_t)kNp * 4 * 3 * T.V;
-  T.group = (uint32_t)std::max<size_t>(1, std::min<size_t>(T.R1, ((size_t)640 << 20) / per_series));
-  T.group = cdiv(T.R1, cdiv(T.R1, T.group));
-  T.ldX = (size_t)std::max(2u, T.group) * T.V;
-  T.ldY = (size_t)2 * T.group * T.V;
-  T.X = A.alloc<uint32_t>(T.ldX * kNp);
-  T.Y = A.alloc<uint32_t>(T.ldY * kNp);
-  T.twLog = T.sys[0].logTop + (sums ? 1 : 0);
-  T.tw = T.twLog > kRowLog ? A.alloc<uint32_t>((size_t)2 * kNp << T.twLog) : nullptr;
-  const uint32_t levels = T.sys[0].logTop - kLeafLog;
-  T.K.clear();
-  for (uint32_t i = 0; i < levels; ++i) T.K.push_back(A.alloc<uint32_t>((size_t)2 * T.V * kNp));
-  T.d_sys = nullptr;
-  T.d_of = nullptr;
-  if (T.sys.size() > 1) {
-    std::vector<uint32_t> of(T.V >> kLeafLog);
-    for (uint32_t i = 0; i < T.sys.size(); ++i)
-      for (uint32_t b = T.sys[i].off >> kLeafLog; b < (T.sys[i].off + (1u << T.sys[i].logTop)) >> kLeafLog; ++b) of[b] = i;
-    Blob blob;
-    const size_t o_sys = blob.add(T.sys), o_of = blob.add(of);
-    char* d = blob.upload(A, s);
-    T.d_sys = (const TreeSys*)(d + o_sys);
-    T.d_of = (const uint32_t*)(d + o_of);
+  uint64_t* poly = A.alloc<uint64_t>(S.poly / 2);
+  uint64_t* g = sums ? A.alloc<uint64_t>(S.g / 2) : nullptr;
+  uint32_t* Ks = sums ? A.alloc<uint32_t>(S.Ks) : nullptr;
+  uint32_t* X = A.alloc<uint32_t>(S.X);
+  uint32_t* Y = A.alloc<uint32_t>(S.Y);
+  uint32_t* K = A.alloc<uint32_t>(S.K);
+  uint32_t* tw = S.twLog ? A.alloc<uint32_t>((size_t)2 * kNp << S.twLog) : nullptr;
+  for (TreeRun& T : trees) {
+    T.C.M = M;
+    uint64_t prod = 1 % M.p;
+    for (int j = 0; j < kNp; ++j) {
+      T.C.Qp[j] = prod;
+      prod = zr_mul(M, prod, kQ[j] % M.p);
+    }
+    T.leafM = A.alloc<uint64_t>(T.V);
+    T.sums = sums ? A.alloc<uint64_t>(T.V) : nullptr;
+    T.poly = poly;
+    T.g = g;
+    T.Ks = Ks;
+    T.X = X;
+    T.Y = Y;
+    T.ldX = (size_t)std::max(2u, T.group) * T.V;
+    T.ldY = (size_t)2 * T.group * T.V;
+    T.tw = tw;
+    T.twLog = S.twLog;
+    T.make_tw = tw && &T == &trees[0];
+    T.K.clear();
+    for (uint32_t i = 0; i < T.sys[0].logTop - kLeafLog; ++i) T.K.push_back(K + (size_t)i * 2 * T.V * kNp);
+    T.d_sys = nullptr;
+    T.d_of = nullptr;
+    if (T.sys.size() > 1) {
+      std::vector<uint32_t> of(T.V >> kLeafLog);
+      for (uint32_t i = 0; i < T.sys.size(); ++i)
+        for (uint32_t b = T.sys[i].off >> kLeafLog; b < (T.sys[i].off + (1u << T.sys[i].logTop)) >> kLeafLog; ++b)
+          of[b] = i;
+      Blob blob;
+      const size_t o_sys = blob.add(T.sys), o_of = blob.add(of);
+      char* d = blob.upload(A, s);
+      T.d_sys = (const TreeSys*)(d + o_sys);
+      T.d_of = (const uint32_t*)(d + o_of);
+    }
   }
 }
 
@@ -838,7 +872,7 @@ void tree_launch(const TreeRun& T, hipStream_t s) {
     a.twLog = T.twLog;
     return a;
   };
-  if (T.tw)
+  if (T.make_tw)
     hipLaunchKernelGGL(k_tree_twist, dim3(1u << (T.twLog - 8), kNp, 2), dim3(256), 0, s, T.tw, T.twLog, kNtt);
   check(copy_u64(T.poly, T.leafM, T.V, s));
   {
@@ -869,7 +903,9 @@ void tree_launch(const TreeRun& T, hipStream_t s) {
 void tree_solve(const zr_mod& M, uint32_t t, uint32_t R, const uint64_t* mono, const uint64_t* rhs, size_t ld_rhs,
                 uint64_t* out, size_t ld_out, int32_t* status, DevArena& A, hipStream_t s) {
   const bool sums = t >= kSumsMinT;
-  TreeRun T;
+  std::vector<TreeRun> one(1);
+  TreeRun& T = one[0];
+  T.R = R;
   TreeSys y{};
   y.end = t;
   y.rhs = rhs;
@@ -877,7 +913,7 @@ void tree_solve(const zr_mod& M, uint32_t t, uint32_t R, const uint64_t* mono, c
   y.f = out;  // read and packed before the unknowns are written
   y.ld = ld_out;
   T.sys.push_back(y);
-  tree_prepare(T, M, R, sums, A, s);
+  tree_prepare(one, M, sums, A, s);
   // leaf polynomials by the quadratic product tree
   uint64_t* tmp = A.alloc<uint64_t>(master_tmp_words(t, kLeaf));
   check(master_levels(M, t, kLeaf, mono, T.leafM, tmp, s));

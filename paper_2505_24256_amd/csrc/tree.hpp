@@ -36,21 +36,43 @@ struct TreeSys {
 // log2 of the rows of the top node of t rows
 uint32_t tree_log_top(uint32_t t);
 
+// Rows of one tree, at most (a batch's systems beyond it go into further trees, which
+// use the same workspace): two series' residues then stay below kTreeResidueBytes.
+constexpr uint32_t kTreeMaxRows = 1u << 22;
+// Residues of a group of series, at most (bytes).  t = 300 007, 41 series: 9.8 ms with
+// 160 MB, which the last-level cache holds, 8.8 with 640, 9.0 with all at once: the
+// launches' fill matters more.
+constexpr size_t kTreeResidueBytes = (size_t)640 << 20;
+
+// Workspace that trees run one after the other on a stream share, in 32-bit words: the
+// largest of each part over the trees added.
+struct TreeSpace {
+  size_t poly = 0, g = 0;           // whole polynomials; 1/Q of the power sums
+  size_t X = 0, Y = 0, K = 0, Ks = 0;  // residues of a group, their products; transforms of all levels; of g
+  uint32_t twLog = 0;               // log2 of the longest transform
+  // a tree of V rows (at most kTreeMaxRows) whose largest node has 2^logTop, with R1 series
+  void add(size_t V, uint32_t logTop, uint32_t R1, bool sums);
+  size_t bytes() const;
+};
+
 struct TreeRun {
   CrtP C;
   std::vector<TreeSys> sys;  // tops in descending order
+  uint32_t R;                // right-hand sides of each
   uint32_t V, R1, group;     // rows of the index space; series (the power sums are series 0, if made)
   uint64_t *leafM, *poly, *sums, *g;
   uint32_t *X, *Y, *Ks, *tw;
   uint32_t twLog;
+  bool make_tw;  // the first of the trees that share a table of twist factors
   size_t ldX, ldY;
   std::vector<uint32_t*> K;  // children's transforms of each level
   const TreeSys* d_sys;
   const uint32_t* d_of;
 };
 
-// Workspace from A and the systems' table (uploaded on s) for R right-hand sides each.
-void tree_prepare(TreeRun& T, const zr_mod& M, uint32_t R, bool sums, DevArena& A, hipStream_t s);
+// Workspace from A, shared by the trees (launched in this order on one stream), and the
+// systems' tables (uploaded on s).
+void tree_prepare(std::vector<TreeRun>& trees, const zr_mod& M, bool sums, DevArena& A, hipStream_t s);
 // From the leaf blocks' polynomials in T.leafM (block b of a system at off + 256 b)
 // and the right-hand sides: the whole polynomials into T.poly and every leaf
 // block's series into f (and, with power sums, into T.sums).

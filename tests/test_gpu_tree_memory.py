@@ -1,6 +1,7 @@
 """Device memory that solves through the subproduct tree take from the allocator, on a
 stream of their own (whose cache of blocks starts empty), against what the tree
 needs.  Blocks are rounded up to powers of two, so twice the sum bounds them."""
+import numpy as np
 import pytest
 
 import synth
@@ -99,3 +100,65 @@ def test_one_system_keeps_its_series_in_the_output(zr):
                                              one.data_ptr(), st.data_ptr(), zr._stream(None)) == 0
         torch.cuda.synchronize()
         assert torch.equal(one, out[j * t:(j + 1) * t])
+
+
+def _batch(zr, shapes, seed):
+    """A batch of systems (t, R): (call(stream), systems, solution of each)."""
+    import torch
+    sys_ = [_random(t, R, seed + i) for i, (t, R) in enumerate(shapes)]
+    so = np.concatenate([[0], np.cumsum([t for t, _ in shapes])]).astype(np.uint64)
+    ro = np.concatenate([[0], np.cumsum([t * R for t, R in shapes])]).astype(np.uint64)
+    nrhs = np.array([R for _, R in shapes], np.uint32)
+    mono, rhs = torch.cat([m for m, _ in sys_]), torch.cat([v for _, v in sys_])
+    out = torch.full_like(rhs, -1)
+    st = torch.full((len(shapes),), 99, dtype=torch.int32, device="cuda")
+    d_so, d_ro = (torch.from_numpy(a.view(np.int64)).cuda() for a in (so, ro))
+
+    def call(s):
+        assert zr.lib().vandermonde_solve_batch(
+            len(shapes), P, d_so.data_ptr(), so.ctypes.data, mono.data_ptr(), nrhs.ctypes.data, d_ro.data_ptr(),
+            ro.ctypes.data, rhs.data_ptr(), out.data_ptr(), st.data_ptr(), s) == 0
+        torch.cuda.synchronize()
+        assert not bool(st.any())
+    return call, sys_, lambda i: out[int(ro[i]):int(ro[i + 1])]
+
+
+def _alone(zr, t, R, mono, rhs):
+    import torch
+    out = torch.empty_like(rhs)
+    st = torch.zeros(1, dtype=torch.int32, device="cuda")
+    assert zr.lib().zr_vandermonde_solve(P, t, R, mono.data_ptr(), rhs.data_ptr(), out.data_ptr(), st.data_ptr(),
+                                         zr._stream(None)) == 0
+    torch.cuda.synchronize()
+    return out
+
+
+def test_trees_of_a_batch_share_their_workspace(zr):
+    """Six right-hand-side counts are six trees, one after the other: residues and
+    transforms of the largest, leaf blocks of all."""
+    import torch
+    t = 100_003
+    shapes = [(t, R) for R in range(26, 32)]
+    call, sys_, got_of = _batch(zr, shapes, 50)
+    got = _growth(call)
+    V = _rows(t)
+    residues = 60 * V * 32
+    twist = 80 * V
+    leaves = sum(t * (4 * 3 * 32 + 8 * (R + 2) + 8 * 11) for t, R in shapes)  # packed rows, sums, polynomials and limbs
+    words = 8 * V * (4 + 2 * 5)
+    need = residues + _transforms(t) + twist + leaves + words
+    print(f"[gpu-test] six trees: {got / 2**20:.0f} MiB taken, {need / 2**20:.0f} MiB needed", flush=True)
+    for i in (0, 5):
+        assert torch.equal(got_of(i), _alone(zr, t, shapes[i][1], *sys_[i]))
+    assert got <= 2 * need
+
+
+def test_batch_of_several_trees_of_one_count(zr):
+    """More rows of one right-hand-side count than one tree holds (2^22): 33 systems whose
+    nodes take 2^17 rows each fill one and a part of the next, the small ones follow."""
+    import torch
+    shapes = [(65_537, 2)] * 33 + [(65_536, 2), (9_000, 2), (3_000, 2)]
+    call, sys_, got_of = _batch(zr, shapes, 90)
+    call(zr._stream(None))
+    for i in (0, 31, 32, 33, 34, 35):
+        assert torch.equal(got_of(i), _alone(zr, *shapes[i], *sys_[i])), i
