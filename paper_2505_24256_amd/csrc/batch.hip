@@ -744,15 +744,38 @@ constexpr double kBatchTreeMinWork = 3e9;
 // products of the quadratic pass.
 constexpr double kTreeLevelSteps = 190;
 
+static bool batch_tree_takes(uint64_t t) {
+  return vsolve_uses_pc() && t >= kBatchTreeMinT && t <= (1u << (kNttMaxLog - 1));
+}
+// modular products that the tree leaves out of a system's quadratic pass
+static double batch_tree_saved(double t, double R, uint32_t log_top) {
+  return t * R * (t - kTreeLeaf - kTreeLevelSteps * (log_top - kTreeLeafLog));
+}
+
+void TreeEstimate::add(uint64_t t, uint64_t R) {
+  if (!batch_tree_takes(t) || !R) return;
+  const uint32_t lg = tree_log_top((uint32_t)t);
+  rows_ += (uint64_t)1 << lg;
+  R_ = std::max(R_, R);
+  log_top_ = std::max(log_top_, lg);
+  saved_ += batch_tree_saved((double)t, (double)R, lg);
+}
+// leaf polynomials and power sums
+uint64_t TreeEstimate::own(uint64_t t) {
+  return batch_tree_takes(t) ? (uint64_t)16 << tree_log_top((uint32_t)t) : 0;
+}
+uint64_t TreeEstimate::shared() const {
+  return saved_ < kBatchTreeMinWork ? 0 : TreeSpace::bound(rows_, log_top_, (uint32_t)R_ + 1);
+}
+
 // Large systems of a batch through one tree per right-hand-side count (several beyond
 // kTreeMaxRows rows), all in one workspace: the system's job is replaced by one job per
 // leaf block.
 static void split_large(const zr_mod& M, std::vector<SolveJob>& jobs, std::vector<TreeRun>& trees, DevArena& A,
                         hipStream_t s) {
-  if (!vsolve_uses_pc()) return;
   std::vector<uint32_t> cand;
   for (uint32_t i = 0; i < jobs.size(); ++i)
-    if (jobs[i].t >= kBatchTreeMinT && jobs[i].t <= (1u << (kNttMaxLog - 1))) cand.push_back(i);
+    if (batch_tree_takes(jobs[i].t)) cand.push_back(i);
   std::stable_sort(cand.begin(), cand.end(), [&](uint32_t x, uint32_t y) {
     if (jobs[x].R != jobs[y].R) return jobs[x].R < jobs[y].R;
     return tree_log_top(jobs[x].t) > tree_log_top(jobs[y].t);
@@ -762,10 +785,8 @@ static void split_large(const zr_mod& M, std::vector<SolveJob>& jobs, std::vecto
   for (size_t i0 = 0, i1; i0 < cand.size(); i0 = i1) {
     const uint32_t R = jobs[cand[i0]].R;
     double saved = 0;
-    for (i1 = i0; i1 < cand.size() && jobs[cand[i1]].R == R; ++i1) {
-      const double t = jobs[cand[i1]].t;
-      saved += t * R * (t - kTreeLeaf - kTreeLevelSteps * (tree_log_top(jobs[cand[i1]].t) - kTreeLeafLog));
-    }
+    for (i1 = i0; i1 < cand.size() && jobs[cand[i1]].R == R; ++i1)
+      saved += batch_tree_saved(jobs[cand[i1]].t, R, tree_log_top(jobs[cand[i1]].t));
     if (saved < kBatchTreeMinWork) continue;
     size_t rows = 0;  // of the tree being filled
     for (size_t i = i0; i < i1; ++i) {

@@ -66,6 +66,21 @@ struct SolveJob {
 // all systems through the persistent work-queue pass.
 void batched_solve(const zr_mod& M, const std::vector<SolveJob>& jobs, hipStream_t s);
 
+// Device memory that batched_solve takes for subproduct trees besides the leaf blocks'
+// own solves, at most, for systems known by size only: own() for each system, shared()
+// once for all systems added (the trees of a call run one after the other).
+class TreeEstimate {
+ public:
+  void add(uint64_t t, uint64_t R);
+  static uint64_t own(uint64_t t);
+  uint64_t shared() const;
+
+ private:
+  uint64_t rows_ = 0, R_ = 0;
+  uint32_t log_top_ = 0;
+  double saved_ = 0;
+};
+
 // Newton matrices and powers of y_k for many (nodes, y_k) sets at once:
 // for job j, Wl (D1*D1*3 + 24 words, limbs [i][d][3] of the inverse
 // Vandermonde matrix of the D1 nodes) and ypow (2*D1 words: y_k^d and their

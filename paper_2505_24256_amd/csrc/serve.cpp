@@ -57,7 +57,9 @@ struct Request {
 // terms, capped by `cap` (the caller's expected final size, or the degree
 // bounds' monomial count), at four words a term.  The balanced path has a
 // numerator and a denominator and adds the per-slice Thiele tables (samples and
-// two coefficient tables of nk + 1 rows for T = max(tN, tD) slices).
+// two coefficient tables of nk + 1 rows for T = max(tN, tD) slices).  A system that
+// may go through a subproduct tree adds its part of the tree; the workspace that all
+// trees of a step share is counted once, over the active requests (shared_footprint).
 uint64_t monomial_count(const Params& P) {
   uint64_t c = 1;
   for (uint32_t v = 0; v < P.nvars; ++v) {
@@ -72,11 +74,21 @@ uint64_t stage_footprint(const Params& P, bool balanced, uint32_t k, uint64_t tN
   const uint64_t D1 = (uint64_t)P.need[k] + 1;
   auto words = [&](uint64_t t) {
     t = std::max<uint64_t>(t, 1);
-    return t * (4 * D1 + 12) + std::min(t * D1, cap) * 4;
+    return t * (4 * D1 + 12) + std::min(t * D1, cap) * 4 + (k ? TreeEstimate::own(t) / 8 : 0);
   };
   if (!balanced) return 8 * words(tN);
   const uint64_t T = std::max<uint64_t>(std::max(tN, tD), 1);
   return 8 * (words(tN) + words(tD) + 3 * (D1 + 1) * T);
+}
+
+uint64_t shared_footprint(const std::vector<Request*>& active) {
+  TreeEstimate e;
+  for (const Request* r : active) {
+    if (r->k == 0 || r->k >= r->P->last) continue;  // the first stage solves no system
+    e.add(r->SN.t, r->P->deg[r->k]);
+    if (r->balanced) e.add(r->SD.t, r->P->deg_den[r->k]);
+  }
+  return e.shared();
 }
 
 }  // namespace
@@ -86,6 +98,7 @@ struct Server {
   uint64_t p;
   zr_mod M;
   uint64_t budget, used = 0;
+  uint64_t shared = 0;  // workspace common to the active requests' next stages
   uint32_t max_active;
   uint64_t next_id = 1, steps = 0;
   std::unique_ptr<DevArena> status_arena;
@@ -795,14 +808,14 @@ zr_status zr_server_step(zr_server* srv, uint32_t* n_active, uint32_t* n_pending
     // (a request larger than the budget still runs when nothing else does)
     while (!S.pending.empty() && S.active.size() < S.max_active) {
       Request* r = S.pending.front();
-      if (!S.active.empty() && S.used + r->footprint > S.budget) break;
+      if (!S.active.empty() && S.used + S.shared + r->footprint > S.budget) break;
       S.pending.pop_front();
       S.used += r->footprint;
       r->admitted_step = S.steps;
       S.active.push_back(r);
       S.stats.admitted += 1;
     }
-    S.stats.peak_footprint = std::max(S.stats.peak_footprint, S.used);
+    S.stats.peak_footprint = std::max(S.stats.peak_footprint, S.used + S.shared);
     S.stats.peak_active = std::max<uint64_t>(S.stats.peak_active, S.active.size());
     if (!S.active.empty()) {
       advance(S);
@@ -836,7 +849,8 @@ zr_status zr_server_step(zr_server* srv, uint32_t* n_active, uint32_t* n_pending
         }
       }
       S.active.swap(keep);
-      S.stats.peak_footprint = std::max(S.stats.peak_footprint, S.used);
+      S.shared = shared_footprint(S.active);
+      S.stats.peak_footprint = std::max(S.stats.peak_footprint, S.used + S.shared);
     }
   } catch (const Error& e) {
     return (zr_status)e.code;
@@ -880,7 +894,7 @@ uint32_t zr_server_finished(zr_server* srv, uint64_t* ids, uint32_t cap) {
 zr_status zr_server_get_stats(zr_server* srv, zr_server_stats* out) {
   if (!srv || !out) return ZR_EINVAL;
   *out = srv->impl.stats;
-  out->footprint = srv->impl.used;
+  out->footprint = srv->impl.used + srv->impl.shared;
   out->active = srv->impl.active.size();
   out->pending = srv->impl.pending.size();
   return ZR_OK;

@@ -776,6 +776,13 @@ void TreeSpace::add(size_t V, uint32_t logTop, uint32_t R1, bool sums) {
 
 size_t TreeSpace::bytes() const { return 4 * (poly + g + X + Y + K + Ks + (twLog ? (size_t)2 * kNp << twLog : 0)); }
 
+size_t TreeSpace::bound(size_t rows, uint32_t logTop, uint32_t R1) {
+  const size_t V = std::min<size_t>(rows, kTreeMaxRows), row = 4 * kNp;
+  const size_t residues = std::max(4 * row * V, std::min(3 * row * V * R1, kTreeResidueBytes));
+  const size_t transforms = 2 * row * V * (logTop - kLeafLog + 1);  // Ks is one level more
+  return residues + transforms + 2 * 8 * V + (2 * row << (logTop + 1));
+}
+
 void tree_prepare(std::vector<TreeRun>& trees, const zr_mod& M, bool sums, DevArena& A, hipStream_t s) {
   if (trees.empty()) return;
   TreeSpace S;
