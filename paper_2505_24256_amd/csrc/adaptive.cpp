@@ -145,7 +145,9 @@ void reconstruct_adaptive(const zr_params* params, uint32_t confirm, zr_blackbox
       check(fill_i32((int32_t*)d_nz, 0, maxm + 1, s));
       if (k == 1) call_bb(bb, ctx, P, 1, 1, P.y.data(), X.data(), 1, vals, s);
       else check(copy_u64(vals, cur.coef, t, s));
-      // one master polynomial for all of the stage's quadratic solves
+      // one tree, or one master polynomial, for all of the stage's solves: the path of the
+      // first batch, which is the widest or as wide as the later ones
+      std::unique_ptr<TreeSolver> tree;
       uint64_t* Mc = nullptr;
       if (k >= 2 && t) C.mulmods += (uint64_t)t * (t - 1) / 2;
       uint32_t m = 0, run = 0, stop = 0;
@@ -163,8 +165,10 @@ void reconstruct_adaptive(const zr_params* params, uint32_t confirm, zr_blackbox
         if (k >= 2 && t) {
           // rows m+1..m+B in place
           DevArena W(s);
-          if (tree_applies(t, B)) {
-            tree_solve(P.M, t, B, cur.mono, rows, t, rows, t, d_status, W, s);
+          if (!tree && !Mc && tree_applies(t, B))
+            tree.reset(new TreeSolver(P.M, t, std::max(B, kBatchMax), cur.mono, A, s));
+          if (tree) {
+            tree->solve(B, rows, t, rows, t, d_status, W);
           } else {
             if (!Mc) {
               Mc = A.alloc<uint64_t>(t);

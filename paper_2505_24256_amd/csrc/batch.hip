@@ -800,7 +800,7 @@ static void split_large(const zr_mod& M, std::vector<SolveJob>& jobs, std::vecto
       rows += v;
       TreeSys y{};
       y.end = j.t;
-      y.rhs = y.f = j.rhs;
+      y.rhs = y.f = j.rhs - j.t;
       y.ld_rhs = y.ld = j.t;
       trees.back().sys.push_back(y);
       of.push_back(cand[i]);
@@ -1042,7 +1042,10 @@ void batched_solve(const zr_mod& M, const std::vector<SolveJob>& jobs_in, hipStr
     }
     if (fix.total()) hipLaunchKernelGGL(k_b_master_fix, dim3(fix.total()), dim3(256), 0, ls, n, P32(o_fix), d_bm);
   }
-  for (const TreeRun& t : trees) tree_launch(t, ls);
+  for (const TreeRun& t : trees) {
+    tree_build(t, ls);
+    tree_descend(t, ls);
+  }
   {
     TimedLaunch tl("batch_pack", ls);
     hipLaunchKernelGGL(k_b_pack, dim3(pack.total()), dim3(256), 0, ls, n, P32(o_pack), d_bs);

@@ -571,7 +571,7 @@ struct LeafPlan {
   uint32_t L, S;    // chunks of the denominators
   uint32_t words;   // packed words per step
 };
-LeafPlan leaf_plan(uint32_t t, uint32_t R, bool sums) {
+LeafPlan leaf_plan(uint32_t t, uint32_t R, bool chain) {
   LeafPlan q{};
   VsolvePlan& P = q.P;
   P.t = t;
@@ -602,28 +602,32 @@ LeafPlan leaf_plan(uint32_t t, uint32_t R, bool sums) {
   const uint32_t wgs = 3 * device_cus() * (t < 16384 ? 1 : 2);
   q.S = std::max<uint32_t>(1, std::min<uint32_t>(t / 128, wgs / cdiv(t, 256)));
   q.L = cdiv(t, q.S);
-  q.S = sums ? 0 : cdiv(t, q.L);
+  q.S = chain ? cdiv(t, q.L) : 0;
   return q;
 }
 }  // namespace
 
-size_t vsolve_leaf_words(uint32_t t, uint32_t R1, bool sums) {
-  const LeafPlan q = leaf_plan(t, R1, sums);
-  // VT | mono_p | spart [Rg][t] | D_c [S][t] | winv [2t] | CL [t][6] (32-bit)
-  return vsolve_rhs_words(q.P) + (size_t)t * (1 + q.P.Rg + q.S + 2 + 3) + 64;
+// mono_p [t] | winv [2t]
+size_t vsolve_leaf_fixed_words(uint32_t t) { return 3 * (size_t)t; }
+
+size_t vsolve_leaf_words(uint32_t t, uint32_t R1, bool chain) {
+  const LeafPlan q = leaf_plan(t, R1, chain);
+  // VT | spart [Rg][t] | D_c [S][t] | CL [t][6] (32-bit)
+  return vsolve_rhs_words(q.P) + (size_t)t * (q.P.Rg + q.S + 3) + 64;
 }
 
 hipError_t vsolve_leaf(const zr_mod& M, uint32_t t, uint32_t R1, const uint64_t* sums, uint32_t block,
                        const uint64_t* mono, const uint64_t* leafM, const uint64_t* rootM, uint64_t* out, size_t ld_out,
-                       uint64_t* work, int32_t* status, hipStream_t s) {
-  const LeafPlan q = leaf_plan(t, R1, sums != nullptr);
+                       uint64_t* fixed, bool first, uint64_t* work, int32_t* status, hipStream_t s) {
+  const bool chain = first && !sums;
+  const LeafPlan q = leaf_plan(t, R1, chain);
   const VsolvePlan& P = q.P;
+  uint64_t* mono_p = fixed;
+  uint64_t* winv = mono_p + t;
   uint64_t* VT = work;
-  uint64_t* mono_p = VT + vsolve_rhs_words(P);
-  uint64_t* spart = mono_p + t;
+  uint64_t* spart = VT + vsolve_rhs_words(P);
   uint64_t* dpart = spart + (size_t)P.Rg * t;
-  uint64_t* winv = dpart + (size_t)q.S * t;
-  uint32_t* CL = (uint32_t*)(winv + 2 * (size_t)t);
+  uint32_t* CL = (uint32_t*)(dpart + (size_t)q.S * t);
   VsArgs a;
   a.M = M;
   a.t = t;
@@ -643,11 +647,11 @@ hipError_t vsolve_leaf(const zr_mod& M, uint32_t t, uint32_t R1, const uint64_t*
   a.hpart = nullptr;
   a.CL = CL;
   a.dpart = dpart;
-  {
+  if (first) {
     TimedLaunch tl("vs_chain", s);
     hipLaunchKernelGGL(k_pack, dim3(cdiv(t, 256)), dim3(256), 0, s, t, R1, 1u, 0u, 2u, (const uint64_t*)out, ld_out, rootM,
                        (uint32_t*)VT, mono, mono_p, CL, M);
-    if (!sums) {
+    if (chain) {
       hipLaunchKernelGGL(k_vs_chain_d, dim3(cdiv(t, 256), q.S), dim3(256), 0, s, a);
       hipLaunchKernelGGL(k_vs_delta, dim3(cdiv(t, 64)), dim3(64), 0, s, a, (const uint64_t*)nullptr,
                          winv, status);

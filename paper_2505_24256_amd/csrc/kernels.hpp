@@ -58,11 +58,14 @@ hipError_t master_levels(const zr_mod& M, uint32_t t, uint32_t block, const uint
 // products per block, the denominators m M'(m) of the whole system (rootM its
 // polynomial), and the unknowns into out, in place of the samples.  sums [t], if
 // given: the blocks' power sums, one more series (R1 counts it) whose values are the
-// denominators; else the chain pass makes them.
-size_t vsolve_leaf_words(uint32_t t, uint32_t R1, bool sums);
+// denominators; else the chain pass makes them.  Denominators and Shoup constants stand
+// in `fixed` (vsolve_leaf_fixed_words): made by the call with first, found by later
+// ones, which take no sums.  work: vsolve_leaf_words, chain where the chain pass runs.
+size_t vsolve_leaf_fixed_words(uint32_t t);
+size_t vsolve_leaf_words(uint32_t t, uint32_t R1, bool chain);
 hipError_t vsolve_leaf(const zr_mod& M, uint32_t t, uint32_t R1, const uint64_t* sums, uint32_t block,
                        const uint64_t* mono, const uint64_t* leafM, const uint64_t* rootM, uint64_t* out, size_t ld_out,
-                       uint64_t* work, int32_t* status, hipStream_t s);
+                       uint64_t* fixed, bool first, uint64_t* work, int32_t* status, hipStream_t s);
 
 // ---- Newton lift (eq. 1) and skeleton expansion ------------------------------
 // g[d][l] = sum_i W[d][i] vals[i][l] with W the inverse Vandermonde matrix of

@@ -794,10 +794,6 @@ void tree_prepare(std::vector<TreeRun>& trees, const zr_mod& M, bool sums, DevAr
       y.end = T.V + t;
       y.logTop = tree_log_top(t);
       T.V += 1u << y.logTop;
-      if (sums) {  // series j is right-hand side j - 1
-        y.rhs -= y.ld_rhs;
-        y.f -= y.ld;
-      }
     }
     T.R1 = T.R + (sums ? 1 : 0);
     T.group = group_size(T.V, T.R1);
@@ -847,58 +843,62 @@ void tree_prepare(std::vector<TreeRun>& trees, const zr_mod& M, bool sums, DevAr
   }
 }
 
-void tree_launch(const TreeRun& T, hipStream_t s) {
-  const uint32_t lo = kLeafLog + 1, hi = T.sys[0].logTop;
-  auto level = [&](uint32_t lg) {
-    Level a{};
-    a.logN = lg;
-    a.N = 1u << lg;
-    a.h = a.N / 2;
-    a.one = T.sys[0];
-    a.sys = T.d_sys;
-    a.sys_of = T.d_of;
-    a.sums = T.sums;
-    if (T.d_sys) {
-      uint32_t v = 0;
-      for (const TreeSys& y : T.sys)
-        if (y.logTop >= lg) v += 1u << y.logTop;
-      a.nn = v >> lg;
-    } else {
-      const uint32_t t = T.sys[0].end;
-      a.nn = t / a.N + (t % a.N > a.h ? 1 : 0);
-    }
-    a.poly = T.poly;
-    a.pout = T.poly;
-    a.X = T.X;
-    a.Y = T.Y;
-    a.ldX = T.ldX;
-    a.ldY = T.ldY;
-    a.K = lg >= lo ? T.K[lg - lo] : nullptr;
-    a.ldK = (size_t)2 * T.V;
-    a.tw = T.tw;
-    a.twLog = T.twLog;
-    return a;
-  };
+static Level tree_level(const TreeRun& T, uint32_t lg) {
+  Level a{};
+  a.logN = lg;
+  a.N = 1u << lg;
+  a.h = a.N / 2;
+  a.one = T.sys[0];
+  a.sys = T.d_sys;
+  a.sys_of = T.d_of;
+  a.sums = T.sums;
+  if (T.d_sys) {
+    uint32_t v = 0;
+    for (const TreeSys& y : T.sys)
+      if (y.logTop >= lg) v += 1u << y.logTop;
+    a.nn = v >> lg;
+  } else {
+    const uint32_t t = T.sys[0].end;
+    a.nn = t / a.N + (t % a.N > a.h ? 1 : 0);
+  }
+  a.poly = T.poly;
+  a.pout = T.poly;
+  a.X = T.X;
+  a.Y = T.Y;
+  a.ldX = T.ldX;
+  a.ldY = T.ldY;
+  a.K = lg > kLeafLog ? T.K[lg - kLeafLog - 1] : nullptr;
+  a.ldK = (size_t)2 * T.V;
+  a.tw = T.tw;
+  a.twLog = T.twLog;
+  return a;
+}
+
+void tree_build(const TreeRun& T, hipStream_t s) {
   if (T.make_tw)
     hipLaunchKernelGGL(k_tree_twist, dim3(1u << (T.twLog - 8), kNp, 2), dim3(256), 0, s, T.tw, T.twLog, kNtt);
   check(copy_u64(T.poly, T.leafM, T.V, s));
   {
     TimedLaunch tl("tree_up", s);
-    for (uint32_t lg = lo; lg <= hi; ++lg) {
-      const Level a = level(lg);
+    for (uint32_t lg = kLeafLog + 1; lg <= T.sys[0].logTop; ++lg) {
+      const Level a = tree_level(T, lg);
       level_kernels<kChild>(a, T.C.M, 2 * a.nn, s);
       level_product(a, T.C, s);
     }
   }
   if (T.sums) {
     TimedLaunch tl("tree_sums", s);
-    power_sums(T, level(lo), s);
+    power_sums(T, tree_level(T, kLeafLog + 1), s);
   }
+  check(hipGetLastError());
+}
+
+void tree_descend(const TreeRun& T, hipStream_t s) {
   {
     TimedLaunch tl("tree_down", s);
     for (uint32_t j0 = 0; j0 < T.R1; j0 += T.group)
-      for (uint32_t lg = hi; lg >= lo; --lg) {
-        Level a = level(lg);
+      for (uint32_t lg = T.sys[0].logTop; lg > kLeafLog; --lg) {
+        Level a = tree_level(T, lg);
         a.j0 = j0;
         a.R = std::min(T.group, T.R1 - j0);
         level_descend(a, T.C, s);
@@ -907,26 +907,47 @@ void tree_launch(const TreeRun& T, hipStream_t s) {
   check(hipGetLastError());
 }
 
-void tree_solve(const zr_mod& M, uint32_t t, uint32_t R, const uint64_t* mono, const uint64_t* rhs, size_t ld_rhs,
-                uint64_t* out, size_t ld_out, int32_t* status, DevArena& A, hipStream_t s) {
-  const bool sums = t >= kSumsMinT;
-  std::vector<TreeRun> one(1);
-  TreeRun& T = one[0];
-  T.R = R;
+TreeSolver::TreeSolver(const zr_mod& M, uint32_t t, uint32_t Rmax, const uint64_t* mono, DevArena& A, hipStream_t s)
+    : t_(t), mono_(mono), s_(s), one_(1) {
+  TreeRun& T = one_[0];
+  T.R = Rmax;
   TreeSys y{};
   y.end = t;
-  y.rhs = rhs;
-  y.ld_rhs = ld_rhs;
-  y.f = out;  // read and packed before the unknowns are written
-  y.ld = ld_out;
   T.sys.push_back(y);
-  tree_prepare(one, M, sums, A, s);
-  // leaf polynomials by the quadratic product tree
-  uint64_t* tmp = A.alloc<uint64_t>(master_tmp_words(t, kLeaf));
-  check(master_levels(M, t, kLeaf, mono, T.leafM, tmp, s));
-  tree_launch(T, s);
-  uint64_t* work = A.alloc<uint64_t>(vsolve_leaf_words(t, T.R1, sums));
-  check(vsolve_leaf(M, t, T.R1, T.sums, kLeaf, mono, T.leafM, T.poly, out, ld_out, work, status, s));
+  tree_prepare(one_, M, t >= kSumsMinT, A, s);
+  cap_ = T.group;
+  tmp_ = A.alloc<uint64_t>(master_tmp_words(t, kLeaf));
+  fixed_ = A.alloc<uint64_t>(vsolve_leaf_fixed_words(t));
+}
+
+void TreeSolver::solve(uint32_t R, const uint64_t* rhs, size_t ld_rhs, uint64_t* out, size_t ld_out, int32_t* status,
+                       DevArena& W) {
+  TreeRun T = one_[0];
+  const bool first = !built_;
+  if (!first) T.sums = nullptr;  // the denominators are made
+  T.R = R;
+  T.R1 = R + (T.sums ? 1 : 0);
+  T.group = cdiv(T.R1, cdiv(T.R1, cap_));
+  TreeSys& y = T.sys[0];
+  y.ld_rhs = ld_rhs;
+  y.ld = ld_out;
+  y.rhs = rhs - (T.sums ? ld_rhs : 0);
+  y.f = out - (T.sums ? ld_out : 0);  // read and packed before the unknowns are written
+  if (first) {
+    // leaf polynomials by the quadratic product tree
+    check(master_levels(T.C.M, t_, kLeaf, mono_, T.leafM, tmp_, s_));
+    tree_build(T, s_);
+    built_ = true;
+  }
+  tree_descend(T, s_);
+  uint64_t* work = W.alloc<uint64_t>(vsolve_leaf_words(t_, T.R1, first && !T.sums));
+  check(vsolve_leaf(T.C.M, t_, T.R1, T.sums, kLeaf, mono_, T.leafM, T.poly, out, ld_out, fixed_, first, work, status,
+                    s_));
+}
+
+void tree_solve(const zr_mod& M, uint32_t t, uint32_t R, const uint64_t* mono, const uint64_t* rhs, size_t ld_rhs,
+                uint64_t* out, size_t ld_out, int32_t* status, DevArena& A, hipStream_t s) {
+  TreeSolver(M, t, R, mono, A, s).solve(R, rhs, ld_rhs, out, ld_out, status, A);
 }
 
 }  // namespace zr

@@ -24,8 +24,10 @@ constexpr uint32_t kTreeLeafLog = 8;  // leaf blocks of 256 rows
 constexpr uint32_t kTreeLeaf = 1u << kTreeLeafLog;
 
 // One system: rows [off, end) of the common index space (off set by
-// tree_prepare; give off = 0, end = t), right-hand side j at rhs + j ld_rhs, its series
-// at f + j ld from the top's children down to the leaf blocks (f may be rhs).
+// tree_prepare; give off = 0, end = t), the samples of series j at rhs + j ld_rhs, the
+// series at f + j ld from the top's children down to the leaf blocks (f may be rhs).
+// With power sums, which are series 0, rhs and f stand one series before the first
+// right-hand side.
 struct TreeSys {
   uint32_t off, end, logTop, pad;
   const uint64_t* rhs;
@@ -76,9 +78,28 @@ struct TreeRun {
 // Workspace from A, shared by the trees (launched in this order on one stream), and the
 // systems' tables (uploaded on s).
 void tree_prepare(std::vector<TreeRun>& trees, const zr_mod& M, bool sums, DevArena& A, hipStream_t s);
-// From the leaf blocks' polynomials in T.leafM (block b of a system at off + 256 b)
-// and the right-hand sides: the whole polynomials into T.poly and every leaf
-// block's series into f (and, with power sums, into T.sums).
-void tree_launch(const TreeRun& T, hipStream_t s);
+// From the leaf blocks' polynomials in T.leafM (block b of a system at off + 256 b): the
+// whole polynomials into T.poly, the children's transforms, and the power sums.
+void tree_build(const TreeRun& T, hipStream_t s);
+// From the right-hand sides: every leaf block's series into f (and, with power sums,
+// into T.sums).
+void tree_descend(const TreeRun& T, hipStream_t s);
+
+// One system whose right-hand sides come in several sets: the tree and the denominators
+// are made with the first set.  Workspace from A (which outlives it) for about Rmax
+// right-hand sides at a time, and from W during a call.
+class TreeSolver {
+ public:
+  TreeSolver(const zr_mod& M, uint32_t t, uint32_t Rmax, const uint64_t* mono, DevArena& A, hipStream_t s);
+  void solve(uint32_t R, const uint64_t* rhs, size_t ld_rhs, uint64_t* out, size_t ld_out, int32_t* status, DevArena& W);
+
+ private:
+  uint32_t t_, cap_;  // cap_: series that the residues hold
+  const uint64_t* mono_;
+  hipStream_t s_;
+  std::vector<TreeRun> one_;
+  uint64_t *tmp_, *fixed_;
+  bool built_ = false;
+};
 
 }  // namespace zr
