@@ -32,7 +32,7 @@ namespace zr {
 // ============================================================================
 
 static uint32_t dots_waves_per_cu(uint32_t RT);
-static uint32_t dots_pc_blocks_per_cu(uint32_t RT, uint32_t ntile, bool uneven);
+static uint32_t dots_pc_blocks_per_cu(uint32_t RT, uint32_t ntile, bool uneven, bool leaf = false);
 
 // Variant of the dot-product pass: one wave per tile (0) or the
 // producer/consumer form (1, the default; systems of at most kPcMinR
@@ -427,15 +427,18 @@ static DotsPcKernel dots_leaf_pick(uint32_t RT) {
 }
 
 // Workgroups of the producer/consumer pass resident per CU for ntile tiles
-// (uneven: the kernel with the bodies of the neighbouring widths).
-static uint32_t dots_pc_blocks_per_cu(uint32_t RT, uint32_t ntile, bool uneven) {
-  static int cache[2][kPcRT + 1][kPcMaxTiles + 1] = {{{0}}};
+// (uneven: the kernel with the bodies of the neighbouring widths; leaf: the pass over a
+// tree's leaf blocks).
+static uint32_t dots_pc_blocks_per_cu(uint32_t RT, uint32_t ntile, bool uneven, bool leaf) {
+  static int cache[4][kPcRT + 1][kPcMaxTiles + 1] = {{{0}}};
   if (RT < 1 || RT > kPcRT || ntile < 1 || ntile > kPcMaxTiles) return 2;
-  int& c = cache[uneven ? 1 : 0][RT][ntile];
+  int& c = cache[2 * leaf + uneven][RT][ntile];
   if (!c) {
     int nb = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, dots_pc_kernel(RT, true, uneven), 64 * (1 + ntile), 0) !=
-            hipSuccess ||
+    const DotsPcKernel k = !leaf    ? dots_pc_kernel(RT, true, uneven)
+                           : uneven ? dots_leaf_pick<true>(RT)
+                                    : dots_leaf_pick<false>(RT);
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k, 64 * (1 + ntile), 0) != hipSuccess ||
         nb <= 0)
       nb = 2;
     c = nb;
@@ -590,7 +593,8 @@ LeafPlan leaf_plan(uint32_t t, uint32_t R, bool chain) {
   pc_widths(P.Rg, P.ntile, P.RT, true, P.tw);
   if (P.lds)
     for (uint32_t k = 0; k < P.ntile; ++k) P.tw[k] = P.RT;
-  if (plan_uneven(P) && dots_pc_blocks_per_cu(P.RT, P.ntile, true) < dots_pc_blocks_per_cu(P.RT, P.ntile, false))
+  if (plan_uneven(P) &&
+      dots_pc_blocks_per_cu(P.RT, P.ntile, true, true) < dots_pc_blocks_per_cu(P.RT, P.ntile, false, true))
     for (uint32_t k = 0; k < P.ntile; ++k) P.tw[k] = P.RT;
   for (uint32_t k = 0; k < P.ntile; ++k) q.words += pc_ldv(P.tw[k]);
   P.vt32 = (size_t)q.words * t;
