@@ -35,8 +35,8 @@ static uint32_t dots_waves_per_cu(uint32_t RT);
 static uint32_t dots_pc_blocks_per_cu(uint32_t RT, uint32_t ntile, bool uneven, bool leaf = false);
 
 // Variant of the dot-product pass: one wave per tile (0) or the
-// producer/consumer form (1, the default; systems of at most kPcMinR
-// right-hand sides still take one wave per tile); see zr_solve_variant.
+// producer/consumer form (1, the default; beyond kLdsMaxT unknowns, systems of at most
+// kPcMinR right-hand sides still take one wave per tile); see zr_solve_variant.
 constexpr int kDefaultDotsVariant = 1;
 static std::atomic<int> g_dots_variant{kDefaultDotsVariant};
 static bool dots_pc_enabled() { return g_dots_variant.load() == 1; }
@@ -127,26 +127,38 @@ static bool plan_uneven(const VsolvePlan& P) {
   return u;
 }
 
-// Systems of at most this many unknowns take the staged form of the
-// producer/consumer pass, whatever R: they are paced by one workgroup's latency per
-// step, so their chunks are cut to two (three, with few values per consumer) workgroups per CU.
-// Whole solve, microseconds, scalar rows (or one wave per tile at R <= 10) against
-// staged: t = 961: R = 1 143/107, R = 30 146/115; t = 2000: R = 10 192/141, R = 30
-// 159/160, R = 60 194/203; t = 3000: R = 1 185/173, R = 30 244/233; t = 4000: R = 1 182/194,
-// R = 60 422/425.
+// Systems of at most kLdsMaxT unknowns take the staged form of the producer/consumer
+// pass: they are paced by one workgroup's latency per step, so their chunks are cut to
+// two (three, with few values per consumer) workgroups per CU.  Whole solve,
+// microseconds, scalar rows (or one wave per tile at R <= 10) against staged: t = 961:
+// R = 1 143/107, R = 30 146/115; t = 2000: R = 10 192/141, R = 30 159/160; t = 3000: R = 1
+// 185/173, R = 30 244/233; t = 4000: R = 1 182/194, R = 60 422/425.
+// With eight and nine values per consumer (and seven, where several groups share the chain
+// pass) a step is long enough for a scalar row's way to the L2, and reading it from LDS
+// costs more than it saves; the staged form is then ahead only while its chunks are the
+// shorter ones.  Those of the scalar form hold at least 128 steps and so fill less of
+// the chip up to about 1 900 unknowns; beyond 2 048 they no longer fit one round of
+// the 512 resident workgroups.  Between, scalar/staged: R = 63: t = 1792 175/171, 1888
+// 178/178, 1920 172/180, 2048 180/183, 2112 225/212, 2240 228/219; R = 50: 1888 168/168, 1920
+// 164/168, 2048 163/168; R = 127 (three groups of 43): 1888 314/312, 1984 315/326, 2048
+// 313/328, 2200 447/395; R = 300: 1888 542/538, 1984 543/568.  From there to 3 072 unknowns the two differ by -4 to +6%.
 constexpr uint32_t kLdsMaxT = 3072;
+static bool plan_staged(uint32_t t, uint32_t ng, uint32_t RT) {
+  const bool wide = RT >= 8 || (RT == 7 && ng > 1);
+  return t <= kLdsMaxT && !(wide && t > 1888 && t <= 2048);
+}
 
 VsolvePlan vsolve_plan(uint32_t t, uint32_t R, uint32_t num_cus) {
   VsolvePlan P{};
   P.t = t;
   P.R = R;
   const uint32_t row_blocks = std::max<uint32_t>(1, cdiv(t, 64));
-  if (dots_pc_enabled() && t <= kLdsMaxT && R > 0) {
+  P.ng = std::max<uint32_t>(1, cdiv(R, kPcMaxR));
+  P.Rg = cdiv(R, P.ng);
+  P.ntile = P.Rg <= 3 ? 3 : kPcMaxTiles;
+  P.RT = cdiv(P.Rg, P.ntile);
+  if (dots_pc_enabled() && R > 0 && plan_staged(t, P.ng, P.RT)) {
     P.lds = P.pc = 1;
-    P.ng = cdiv(R, kPcMaxR);
-    P.Rg = cdiv(R, P.ng);
-    P.ntile = P.Rg <= 3 ? 3 : kPcMaxTiles;
-    P.RT = cdiv(P.Rg, P.ntile);
     P.ldv = pc_ldv(P.RT);
     for (uint32_t k = 0; k < P.ntile; ++k) P.tw[k] = P.RT;
     P.vt32 = (size_t)P.ntile * P.ldv * t;
