@@ -340,8 +340,8 @@ zr_status zippel_reconstruct_batch(uint32_t n, const zr_params* params, zr_black
  * multiply-accumulates; 1 (default) a producer wave runs the chain once per
  * row block and publishes it through LDS to one consumer wave per tile
  * (beyond 3 072 unknowns, systems with at most 10 right-hand sides run as 0), and
- * large systems (from 5 500 unknowns, from 3 073 with eight right-hand sides and
- * from 2 561 with 37, up to 2^21) are first cut into independent blocks of rows by a
+ * large systems (from 5 500 unknowns, from 2 241 the sooner the more right-hand
+ * sides there are, up to 2^21) are first cut into independent blocks of rows by a
  * subproduct tree with exact number-theoretic transforms, so that the quadratic
  * pass covers only the blocks.  Same results for both.  Any other value returns ZR_EINVAL and leaves the choice unchanged. */
 zr_status zr_solve_variant(int variant);

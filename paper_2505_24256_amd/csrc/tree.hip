@@ -736,14 +736,24 @@ constexpr uint32_t kSumsMinT = 32768;
 
 // The tree pays from about 5500 unknowns whatever R, and below that where the
 // right-hand sides are many enough for its launches (about 45 of 4 to 10 us).
-// Quadratic against tree, microseconds: t = 3000: R = 30 237/228, R = 40 249/239, R = 60 312/281;
-// t = 3500: R = 5 218/218, R = 10 239/217, R = 30 272/233; t = 4500: R = 1 228/251, R = 10
-// 298/267; t = 5500: R = 1 259/262, R = 10 365/272; t = 8000: R = 1 317/275, R = 30
-// 704/339; t = 13 000: R = 1 610/360, R = 30 1568/464.  Up to 2^21 unknowns: the power
-// sums' last transform then has 2^22 points, the primes' limit.
+// Quadratic against tree, whole solve, microseconds, on both sides of each line:
+// t = 2177: R = 200 511/522, R = 400 904/868; t = 2250: R = 127 395/407, R = 200 521/520, R = 400
+// 928/869; t = 2400: R = 80 294/304, R = 100 338/331, R = 200 576/526; t = 2561: R = 37 211/217, R = 43
+// 228/229, R = 50 243/234; t = 2700: R = 28 202/202, R = 32 214/209, R = 40 229/222; t = 2945: R = 20
+// 199/200, R = 24 214/205; t = 3072: R = 20 195/202, R = 24 217/205, R = 32 230/216; t = 3073: R = 8
+// 215/199, R = 12 195/201, R = 16 205/203; t = 3400: R = 8 218/200, R = 15 214/204; t = 4500: R = 1
+// 228/251, R = 10 298/267; t = 5500: R = 1 259/262, R = 10 365/272; t = 13 000: R = 1 610/360, R = 30
+// 1568/464.  Up to 2^21 unknowns: the power sums' last transform then has 2^22 points,
+// the primes' limit.
 bool tree_applies(uint32_t t, uint32_t R) {
   if (!vsolve_uses_pc() || R == 0 || t > (1u << (kNttMaxLog - 1))) return false;
-  return t >= 5500 || (t > 3072 && R >= 8) || (t > 2560 && R > 36);
+  if (t >= 5500) return true;
+  if (t > 3072) return R >= 8;
+  if (t > 2944) return R >= 24;
+  if (t > 2688) return R >= 32;
+  if (t > 2560) return R >= 43;
+  if (t > 2304) return R >= 100;
+  return t > 2240 && R >= 200;
 }
 
 uint32_t tree_log_top(uint32_t t) {

@@ -44,3 +44,10 @@ def _check(zr, t, R):
 @pytest.mark.parametrize("R", [43, 49, 50, 57, 63, 99, 127])
 def test_staged_and_scalar_rows(zr, t, R):
     _check(zr, t, R)
+
+
+@pytest.mark.parametrize("t,R", [(2240, 200), (2241, 199), (2241, 200), (2304, 120), (2305, 99), (2305, 100), (2560, 43),
+                                 (2561, 42), (2561, 43), (2688, 32), (2689, 31), (2689, 32), (2944, 24), (2945, 23),
+                                 (2945, 24), (3072, 63), (3073, 7), (3073, 8), (5499, 7), (5500, 1)])
+def test_quadratic_and_tree(zr, t, R):
+    _check(zr, t, R)
