@@ -736,12 +736,21 @@ static BPlan bplan(uint32_t t, uint32_t R, double cap, const Tuning& T) {
   return P;
 }
 
-// Systems from which a batch's tree is built, and the work it has to save (modular
-// products) for its some 60 launches of 5 us.
-constexpr uint32_t kBatchTreeMinT = 1536;
-constexpr double kBatchTreeMinWork = 3e9;
+// Unknowns from which a system of a batch goes into its tree, and the work a tree has to
+// save (modular products, by batch_tree_saved) for its some 60 launches of 5 us.
+// Whole batches of n equal systems, quadratic queue against tree, microseconds, by the work
+// saved: t = 12 000, R = 30, n = 1 (3.8e9) 1495/681; t = 8000, R = 30, n = 1 (1.6e9) 798/553;
+// t = 2500, R = 8, n = 64 (1.9e9) 2041/1086; t = 2049, R = 30, n = 16 (1e9) 856/748; t = 4097,
+// R = 30, n = 4 (1.4e9) 867/695, n = 2 (7e8) 587/612, n = 1 (3.6e8) 411/523; t = 6000, R = 30,
+// n = 1 (9e8) 544/538; t = 1536, R = 30, n = 16 (5e8) 541/518, n = 8 (2.6e8) 402/439; t = 1025,
+// R = 30, n = 256 (1.6e9) 2732/2724, n = 64 (4e8) 889/896; t = 1024, R = 30, n = 256 (3.1e9)
+// 2521/1750; t = 700, R = 30, n = 700 (9e8) 3781/3613, R = 8 (2.5e8) 1816/1820; t = 640, R = 30,
+// n = 700 (5e7) 3164/3352.
+constexpr uint32_t kBatchTreeMinT = 700;
+constexpr double kBatchTreeMinWork = 1e9;
 // A level's transforms cost about as much per row and right-hand side as this many
-// products of the quadratic pass.
+// products of the quadratic pass: the cost is even where 256 + 190 levels reach t (640 at
+// two levels), as measured.
 constexpr double kTreeLevelSteps = 190;
 
 static bool batch_tree_takes(uint64_t t) {
