@@ -50,8 +50,9 @@ MUL32_PEAK_TOPS = CU * SIMD * LANES * CLOCK_GHZ * 1e9 / 1e12
 MUL32_PER_MULMOD = 4
 
 # The subproduct tree's transforms: five primes, and three 32x32-bit multiplies per
-# Montgomery product.  Systems it takes (csrc/tree.hpp) and rows of its leaves.
-TREE_PRIMES, MUL32_PER_MONT, TREE_LEAF_LOG, TREE_SUMS_MIN_T = 5, 3, 8, 32768
+# Montgomery product.  Its leaf blocks have 2^TREE_LEAF_LOG rows (kTreeLeafLog in
+# csrc/tree.hpp).  Which systems go through it is read from the launches that ran.
+TREE_PRIMES, MUL32_PER_MONT, TREE_LEAF_LOG = 5, 3, 8
 
 HEADLINE_STAGE = 8  # the last variable of the n = 8 workload
 
@@ -64,28 +65,28 @@ def _system_sizes(w):
     return [int(len(np.unique(e[:, :k], axis=0))) for k in range(1, e.shape[1])]
 
 
-def _tree_applies(t, R):
-    """Whether a system of t unknowns and R right-hand sides goes through the tree
-    (the rule of csrc/tree.hpp, for the producer/consumer variant)."""
-    return t >= 5500 or (t > 3072 and R >= 8) or (t > 2560 and R > 36)
+def _tree_launches(zr):
+    """Since the timing was reset: systems that went through the tree, and those of them
+    whose power sums were one more series (one timed launch each)."""
+    return zr.timing_get("tree_down")[0], zr.timing_get("tree_sums")[0]
 
 
-def _dots_done(t, R, tree):
-    """Modular products that the dot-product pass of one system performs: R t^2 and
-    the t(t-1) chain steps, or those of the tree's leaf blocks of 256 rows (with
-    the power sums as one more series from 32 768 unknowns on)."""
-    if not tree:
-        return R * t * t + t * (t - 1)
-    leaf = 1 << TREE_LEAF_LOG
-    return (R + (1 if t >= TREE_SUMS_MIN_T else 0) + 1) * leaf * t
+def _dots_done(sizes, R, trees, sums):
+    """Modular products that the dot-product passes of systems of these sizes with R
+    right-hand sides each perform: R t^2 and the t(t-1) chain steps, or, for the
+    `trees` largest, those of the tree's leaf blocks (the `sums` largest with the power
+    sums as one more series)."""
+    leaf, done = 1 << TREE_LEAF_LOG, 0
+    for i, t in enumerate(sorted(sizes, reverse=True)):
+        done += (R + (1 if i < sums else 0) + 1) * leaf * t if i < trees else R * t * t + t * (t - 1)
+    return done
 
 
-def _tree_down_mul32(t, R):
+def _tree_down_mul32(t, series):
     """32x32-bit multiplies of the descent: per level of nodes of N = 2^k rows and per
     series, one forward and two inverse transforms (k/2 Montgomery products a point
     each) and two pointwise products, modulo five primes.  Padding, the Chinese
     remainder and the reductions are not counted."""
-    series = R + (1 if t >= TREE_SUMS_MIN_T else 0)
     top = max(1, t - 1).bit_length()
     per_point = sum(1.5 * k + 2 for k in range(TREE_LEAF_LOG + 1, top + 1))
     return t * series * TREE_PRIMES * per_point * MUL32_PER_MONT
@@ -351,9 +352,13 @@ def headline(zr, synth, args, stream):
         zr.lib().zr_recorder_rewind(rec.handle)
         return zr.reconstruct(w.p, w.deg, rec, sched=w.schedule, stream=stream, first_stage=k, start=start)
 
-    # recording run (device black box): also checks the result
+    # recording run (device black box): also checks the result, and tells which path the solve takes
     t0 = time.perf_counter()
+    zr.timing(True)
+    zr.timing_reset()
     e, c = zr.reconstruct(w.p, w.deg, rec, sched=w.schedule, stream=stream, first_stage=k, start=start)
+    zr.timing(False)
+    trees, sums = _tree_launches(zr)
     exact = bool(np.array_equal(e, w.hidden.exps) and np.array_equal(c, w.hidden.coefs))
     _progress(f"recorded in {time.perf_counter() - t0:.1f} s; bit exact {exact}")
     if not exact:
@@ -390,7 +395,7 @@ def headline(zr, synth, args, stream):
     exact = exact and bool(np.array_equal(e, w.hidden.exps) and np.array_equal(c, w.hidden.coefs))
     n_dots, ms_dots = zr.timing_get("vs_dots")
     return {"w": w, "start": start, "cnt": cnt, "elapsed": elapsed, "lat": lat, "exact": exact,
-            "n_dots": n_dots, "ms_dots": ms_dots, "kernels": kernels}
+            "n_dots": n_dots, "ms_dots": ms_dots, "kernels": kernels, "trees": trees, "sums": sums}
 
 
 def config2_leg(zr, synth, args, stream):
@@ -400,7 +405,11 @@ def config2_leg(zr, synth, args, stream):
     import torch
     w = synth.config_workload(2)
     rec = zr.Recorder(synth.DeviceBlackBox(w.hidden, nthreads=args.cpu_threads))
+    zr.timing(True)
+    zr.timing_reset()
     e, c = zr.reconstruct(w.p, w.deg, rec, sched=w.schedule, stream=stream)
+    zr.timing(False)
+    trees, sums = _tree_launches(zr)
     exact = bool(np.array_equal(e, w.hidden.exps) and np.array_equal(c, w.hidden.coefs))
     rec.replay(True)
     for _ in range(2):
@@ -424,8 +433,7 @@ def config2_leg(zr, synth, args, stream):
     n_dots, ms_dots = zr.timing_get("vs_dots")
     steps = args.config2_steps
     R = int(w.deg[0])
-    pc = args.solve_variant == "producer_consumer"
-    done = sum(_dots_done(t, R, pc and _tree_applies(t, R)) for t in _system_sizes(w))
+    done = _dots_done(_system_sizes(w), R, trees, sums)
     alu = done * steps * MUL32_PER_MULMOD / (ms_dots / 1e3) / 1e12 if ms_dots else 0.0
     return {"workload": "plain polynomial Zippel, whole reconstruction, n=6, per-variable degree<=30, t=10^4",
             "system_sizes": _system_sizes(w), "right_hand_sides": int(w.deg[0]),
@@ -676,13 +684,13 @@ def main():
     mulmods = cnt["mulmods"] * steps
     value = mulmods / elapsed
     n_dots, ms_dots = H["n_dots"], H["ms_dots"]
-    tree = args.solve_variant == "producer_consumer" and _tree_applies(t_sys, R)
-    dots_tops = (MUL32_PER_MULMOD * _dots_done(t_sys, R, tree) * steps / (ms_dots / 1e3) / 1e12) if ms_dots else 0.0
-    down = H["kernels"].get("tree_down") if tree else None
+    done = _dots_done([t_sys], R, H["trees"], H["sums"])
+    dots_tops = (MUL32_PER_MULMOD * done * steps / (ms_dots / 1e3) / 1e12) if ms_dots else 0.0
+    down = H["kernels"].get("tree_down")
     # the kernels that take most of the step: the tree's descent (events of the warm-up
     # steps), or the dot-product pass (events of the timed steps)
     if down:
-        alu = _tree_down_mul32(t_sys, R) * args.warmup / (down["ms_total"] / 1e3) / 1e12
+        alu = _tree_down_mul32(t_sys, R + H["sums"]) * args.warmup / (down["ms_total"] / 1e3) / 1e12
     else:
         alu = dots_tops
     # measured ceiling of the 32x32->64-bit multiply: the v_mad_u64_u32 probe
