@@ -943,6 +943,8 @@ void TreeSolver::solve(uint32_t R, const uint64_t* rhs, size_t ld_rhs, uint64_t*
   y.ld = ld_out;
   y.rhs = rhs - (T.sums ? ld_rhs : 0);
   y.f = out - (T.sums ? ld_out : 0);  // read and packed before the unknowns are written
+  // before the first launch: a call that fails for memory has written nothing
+  uint64_t* work = W.alloc<uint64_t>(vsolve_leaf_words(t_, T.R1, first && !T.sums));
   if (first) {
     // leaf polynomials by the quadratic product tree
     check(master_levels(T.C.M, t_, kLeaf, mono_, T.leafM, tmp_, s_));
@@ -950,7 +952,6 @@ void TreeSolver::solve(uint32_t R, const uint64_t* rhs, size_t ld_rhs, uint64_t*
     built_ = true;
   }
   tree_descend(T, s_);
-  uint64_t* work = W.alloc<uint64_t>(vsolve_leaf_words(t_, T.R1, first && !T.sums));
   check(vsolve_leaf(T.C.M, t_, T.R1, T.sums, kLeaf, mono_, T.leafM, T.poly, out, ld_out, fixed_, first, work, status,
                     s_));
 }
