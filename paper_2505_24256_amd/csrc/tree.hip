@@ -21,10 +21,11 @@
 // both evaluate the same polynomial identities exactly.
 //
 // Whole solve, quadratic against tree, one MI355X: t = 9 997, R = 30: 1.07 ->
-// 0.41 ms; t = 100 003, R = 17: 49.6 -> 1.68 ms; t = 300 007, R = 40: 781 -> 8.6 ms
-// (rows 4.1 ms, bound by integer issue; columns and Chinese remainder 2.5 ms, by the
-// residues' traffic; the leaves' dot products 1.1 ms).  256 uneven systems of 10 to
-// 20 000 unknowns, R = 30, the large ones through one tree: 52.0 -> 9.3 ms.
+// 0.39 ms; t = 100 003, R = 17: 49.6 -> 1.66 ms; t = 300 007, R = 40: 781 -> 8.7 ms
+// (rows of nodes above 4096 points 2.5 ms, bound by integer issue; rows of smaller nodes
+// 1.3 ms, columns 2.3 and Chinese remainder 0.3 ms, near the copy rate by the residues'
+// traffic; the leaves' dot products 1.1 ms).  256 uneven systems of 10 to 20 000
+// unknowns, R = 30, the large ones through one tree: 52.0 -> 9.0 ms.
 //
 // A node of 2^k rows uses cyclic products of length N = 2^k: sums over i + k <= n
 // do not wrap for the coefficients wanted, the upper half of the product of the
