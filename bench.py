@@ -27,6 +27,7 @@ used for the roofline (see include/zippel_microbench.h).
 from __future__ import annotations
 
 import argparse
+import hashlib
 import json
 import math
 import os
@@ -54,6 +55,11 @@ MUL32_PER_MULMOD = 4
 # csrc/tree.hpp).  Which systems go through it is read from the launches that ran.
 TREE_PRIMES, MUL32_PER_MONT, TREE_LEAF_LOG = 5, 3, 8
 
+# HBM bytes of the descent per solve, from counters (profiles/subproduct_tree_t500000_r40.md),
+# valid for the sources and the system they were taken with.
+TREE_SOURCES = ("field.hpp", "ntt.hpp", "tree.hpp", "tree.hip")
+TREE_TRAFFIC = {"sources_sha16": "663f20d724f9bbe0", "system": (500_000, 40), "bytes": 39530823360}
+
 HEADLINE_STAGE = 8  # the last variable of the n = 8 workload
 
 
@@ -63,6 +69,17 @@ def _system_sizes(w):
     variable (stages 2..n)."""
     e = np.asarray(w.hidden.exps)
     return [int(len(np.unique(e[:, :k], axis=0))) for k in range(1, e.shape[1])]
+
+
+def _tree_traffic(t, R):
+    """HBM bytes of one descent, None when the counters were taken with other sources or
+    for another system."""
+    h = hashlib.sha256()
+    for f in TREE_SOURCES:
+        with open(os.path.join(ROOT, "paper_2505_24256_amd", "csrc", f), "rb") as fh:
+            h.update(fh.read())
+    same = h.hexdigest()[:16] == TREE_TRAFFIC["sources_sha16"] and (t, R) == TREE_TRAFFIC["system"]
+    return TREE_TRAFFIC["bytes"] if same else None
 
 
 def _tree_launches(zr):
@@ -700,7 +717,8 @@ def main():
     roofline = {"bound": "alu", "achieved": round(alu, 3), "peak": round(MUL32_PEAK_TOPS, 3),
                 "unit": "TOP/s (32x32-bit multiplies performed; a Montgomery product mod a 30-bit prime = 3, a 64x64-bit "
                         "product of the dot products = 4)",
-                "frac": round(alu / MUL32_PEAK_TOPS, 4), "traffic": None,
+                "frac": round(alu / MUL32_PEAK_TOPS, 4), "traffic": _tree_traffic(t_sys, R) if down else None,
+                "traffic_unit": "bytes per step (HBM, rocprofv3 counters of the descent, calibrated)",
                 "kernel": "descent of the subproduct tree (k_tree_col_fwd, k_tree_descend, k_tree_col_inv, k_tree_crt)"
                           if down else "dot-product pass",
                 "ms_per_step": (round(down["ms_total"] / args.warmup, 3) if down

@@ -36,3 +36,10 @@ def test_descent_products_per_series():
     # one level of 512 points: 1.5 * 9 Montgomery products a point for the transforms, 2 pointwise
     assert bench._tree_down_mul32(512, 1) == 512 * 5 * (1.5 * 9 + 2) * 3
     assert bench._tree_down_mul32(512, 7) == 7 * bench._tree_down_mul32(512, 1)
+
+
+def test_traffic_is_keyed_to_sources_and_system(monkeypatch):
+    t, R = bench.TREE_TRAFFIC["system"]
+    assert bench._tree_traffic(t + 1, R) is None and bench._tree_traffic(t, R + 1) is None
+    monkeypatch.setitem(bench.TREE_TRAFFIC, "sources_sha16", "0" * 16)
+    assert bench._tree_traffic(t, R) is None
