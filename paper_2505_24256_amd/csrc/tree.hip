@@ -785,8 +785,6 @@ void TreeSpace::add(size_t V, uint32_t logTop, uint32_t R1, bool sums) {
   if (lg > kRowLog) twLog = std::max(twLog, lg);
 }
 
-size_t TreeSpace::bytes() const { return 4 * (poly + g + X + Y + K + Ks + (twLog ? (size_t)2 * kNp << twLog : 0)); }
-
 size_t TreeSpace::bound(size_t rows, uint32_t logTop, uint32_t R1) {
   const size_t V = std::min<size_t>(rows, kTreeMaxRows), row = 4 * kNp;
   const size_t residues = std::max(4 * row * V, std::min(3 * row * V * R1, kTreeResidueBytes));

@@ -54,8 +54,7 @@ struct TreeSpace {
   uint32_t twLog = 0;               // log2 of the longest transform
   // a tree of V rows (at most kTreeMaxRows) whose largest node has 2^logTop, with R1 series
   void add(size_t V, uint32_t logTop, uint32_t R1, bool sums);
-  size_t bytes() const;
-  // bytes() at most, for trees with power sums over `rows` rows in all, whatever their
+  // its bytes at most, for trees with power sums over `rows` rows in all, whatever their
   // division into trees
   static size_t bound(size_t rows, uint32_t logTop, uint32_t R1);
 };
